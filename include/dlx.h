@@ -155,6 +155,19 @@ enum {
  * results up to rounding. DLX_FLAG_DENSE_MFT selects the dense products
  * instead (for comparison; same results up to rounding). */
 
+/* A star's tilt moves its image without changing it, so every star of every
+ * frame shows one polychromatic image, shifted. Where a problem with several
+ * frames, integer dithers or a bicubic map has enough stars and frames for it
+ * to pay, the plan transforms the on-axis pupil once per wavelength onto a
+ * table finer than the image's own bandwidth, interpolates every star's image
+ * from the band's sum there (FP64, error about 1e-9 of the local intensity),
+ * and sends the gradient back the same way: same results up to rounding, for
+ * any star position. Its products are FP32 in both arithmetics. Such a plan
+ * holds the table for stars anywhere in the pupil grid's own field (a third of
+ * the free device memory at most); a plan with a workspace limit, with
+ * DLX_FLAG_DENSE_MFT or DLX_FLAG_GROUPED keeps one transform per star, frame
+ * and wavelength, and so does a DLX_BF16X3 plan of fewer than 16 wavelengths. */
+
 /* DLX_FLAG_PIXEL_KERNEL gives every detector pixel its own intra-pixel kernel
  * (Section 6: intra-pixel sensitivity, recoverable at this sampling): every
  * `intrapixel` argument is then [Nd][Nd][Q][Q] (pixel p's kernel K_p[a][b])
@@ -378,7 +391,8 @@ dlx_status dlx_plan_profile(dlx_plan* plan, int32_t enable);
 
 /* Diagnostics: synchronise on the recorded events and return, per stage
  * (arrays of DLX_N_STAGES, host memory), the summed device time in ms, the
- * number of launches and the number of PSFs those launches processed since
+ * number of launches and the number of PSFs those launches processed (F1, F2,
+ * B3, B4 of a plan on a shared PSF table: one per wavelength) since
  * profiling was enabled or these counters were last read; then reset them. */
 dlx_status dlx_plan_stage_times(dlx_plan* plan, double* total_ms, int64_t* launches, int64_t* psfs);
 

@@ -34,8 +34,8 @@ hipError_t launch_loss_final(dlx_plan* p, int n_chunks, double* loss, hipStream_
 hipError_t launch_bin_loss(dlx_plan* p, int f0, int nf, int chunk, const float* sources, const float* intrapixel,
                            const float* flat, const float* data, int kind, double mu, double sigma, float* binned,
                            float* model, float* r, double* gflat, hipStream_t st);
-hipError_t launch_grad_reduce(dlx_plan* p, const float* Z, const float* Bm, double* gz, double* gmap, double* gsrc,
-                              double* loss, int loss_chunks, double* gK, hipStream_t st);
+hipError_t launch_grad_reduce(dlx_plan* p, const dlx_plan* o, const float* Z, const float* Bm, double* gz,
+                              double* gmap, double* gsrc, double* loss, int loss_chunks, double* gK, hipStream_t st);
 hipError_t launch_kgrad(dlx_plan* p, int f0, int nf, const float* sources, const float* flat, const float* resid,
                         double* gK, hipStream_t st);
 int loss_block_count(long long npix);
@@ -92,7 +92,38 @@ struct Pool {
   }
 };
 
+// The images' and stars' arrays of a plan whose optics live in its table's own plan.
+void layout_images(dlx_plan* p, Pool& pool) {
+  const size_t No = p->No, ldNo = p->ldNo, fc = p->frames_per_chunk, nd2 = (size_t)p->Nd * p->Nd;
+  TableArgs& t = p->ta;
+  const size_t nt2 = (size_t)t.Nt * t.Nt;
+  p->d_G = pool.take<float>(fc * No * ldNo);
+  t.G = p->d_G;
+  p->d_bs = pool.take<float>(fc * p->S * nd2);
+  if (p->dither) {
+    p->d_Bbig = pool.take<float>(nd2);
+    p->d_win = pool.take<int>(p->win.size());
+  }
+  p->d_flux = pool.take<double>((size_t)p->F * p->S * p->seed_blocks);
+  p->d_kpart = pool.take<double>((size_t)p->F * p->seed_blocks * p->Q * p->Q);
+  p->d_lossblk = pool.take<double>((size_t)p->loss_blocks * p->n_chunks);
+  p->d_status = pool.take<int>(1);
+  t.I = pool.take<double>(nt2);
+  t.Ix = pool.take<double>(nt2);
+  t.Iy = pool.take<double>(nt2);
+  t.wt = pool.take<double>((size_t)t.nfs * 2 * 16 * t.K);
+  t.base = pool.take<int>(2 * (size_t)t.nfs);
+  t.far = pool.take<int>(t.nfs);
+  t.range = pool.take<int>(2);
+  t.planes = pool.take<float>(fc * p->S * No * ldNo);
+  t.Hpart = pool.take<double>(t.groups * nt2);
+  t.H = pool.take<float>((1 + (size_t)p->L) * nt2);
+  t.pos = pool.take<double>((size_t)t.nfs * t.slots * 2);
+  p->d_tune = pool.take<float>(3);   // the table's one star {0, 0, 1}
+}
+
 void layout(dlx_plan* p, Pool& pool) {
+  if (p->ta.Nt > 0) return layout_images(p, pool);
   const size_t L = p->L, Ni = p->Ni, No = p->No, ldNi = p->ldNi, ldNo = p->ldNo, CP = p->chunk_psf;
   p->d_wl = pool.take<WlInfo>(L);
   p->d_MN = pool.take<float>(2 * L * No * ldNi);
@@ -108,8 +139,10 @@ void layout(dlx_plan* p, Pool& pool) {
   p->d_T = pool.take<float>(2 * CP * No * ldNi);
   p->d_Y = pool.take<float>(2 * CP * No * ldNo);
   p->d_UT = pool.take<float>(2 * CP * Ni * ldNo);
-  p->d_G = pool.take<float>((size_t)p->frames_per_chunk * No * ldNo);
-  p->d_bs = pool.take<float>((size_t)p->frames_per_chunk * p->S * p->Nd * p->Nd);
+  // a table's own plan forms no images: its seed weights are the outer plan's
+  const bool images = !p->range;
+  p->d_G = pool.take<float>(images ? (size_t)p->frames_per_chunk * No * ldNo : 1);
+  p->d_bs = pool.take<float>(images ? (size_t)p->frames_per_chunk * p->S * p->Nd * p->Nd : 1);
   if (p->dither) {
     p->d_Bbig = pool.take<float>((size_t)p->Nd * p->Nd);
     p->d_win = pool.take<int>(p->win.size());
@@ -158,6 +191,7 @@ GemmArgs base_args(const dlx_plan* p, int f0, int nframes) {
   a.ldp = p->ldNi;
   a.wl = p->d_wl;
   a.xcoord = p->d_x;
+  a.range = p->range;
   return a;
 }
 
@@ -179,6 +213,21 @@ Operand op_UT(const dlx_plan* p) {
 }
 
 int wg_count(const GemmArgs& a) { return a.tiles_m * a.tiles_n * a.n_items; }
+
+// Workgroups of a stage; on a PSF table those of the rows and columns in use when the stars lie within
+// the detector (fgemm_table_kernel strides over any more).
+int stage_wgs(const dlx_plan* p, int kind, const GemmArgs& a, TileShape ts) {
+  if (!p->range) return wg_count(a);
+  const int lo = p->lo_reg, bm = ts.bm(), bn = ts.bn();
+  int m = a.tiles_m, n = a.tiles_n;
+  if (kind == KIND_F1) m -= lo / bm;
+  if (kind == KIND_F2) {
+    m = ceil_div(a.M - lo, bm) - lo / bm;
+    n -= lo / bn;
+  }
+  if (kind == KIND_B3) n = ceil_div(a.N - lo, bn) - lo / bn;
+  return m * n * a.n_items;
+}
 
 // ---- stage timing (diagnostics): event pairs bracket each stage on the call's stream
 constexpr int kEventPool = 512;
@@ -255,7 +304,7 @@ GemmArgs args_f1(dlx_plan* p, int f0, int nf) {
 
 hipError_t run_f1(dlx_plan* p, int f0, int nf, hipStream_t st) {
   const GemmArgs a = args_f1(p, f0, nf);
-  return launch_gemm(KIND_F1, p->bf16(), p->ts_f1, a, wg_count(a), st);
+  return launch_gemm(KIND_F1, p->bf16(), p->ts_f1, a, stage_wgs(p, KIND_F1, a, p->ts_f1), st);
 }
 
 GemmArgs e_args(dlx_plan* p, int f0, int nf, TileShape ts);
@@ -279,7 +328,7 @@ GemmArgs args_f2(dlx_plan* p, int f0, int nf) {
 
 hipError_t run_f2(dlx_plan* p, int f0, int nf, hipStream_t st) {
   const GemmArgs a = args_f2(p, f0, nf);
-  return launch_gemm(KIND_F2, p->bf16(), p->ts_f2, a, wg_count(a), st);
+  return launch_gemm(KIND_F2, p->bf16(), p->ts_f2, a, stage_wgs(p, KIND_F2, a, p->ts_f2), st);
 }
 
 // B3 over frames [f0, f0 + nf): U^T = conj(M)^T Y^T with the seed Y = w phi G E
@@ -297,6 +346,7 @@ GemmArgs args_b3(dlx_plan* p, int f0, int nf, const float* sources) {
   a.sources = sources;
   a.seedw = p->seed_pass ? nullptr : p->d_G;
   a.seedw_by_frame = (long long)p->No * p->ldNo;
+  a.seedw_by_wl = (long long)p->No * p->ldNo;   // on a PSF table with far stars: planes 1 + wavelength
   a.out = p->d_UT;
   a.out_plane = op_UT(p).plane;
   a.out_by_psf = op_UT(p).by_psf;
@@ -307,7 +357,7 @@ GemmArgs args_b3(dlx_plan* p, int f0, int nf, const float* sources) {
 
 hipError_t run_b3(dlx_plan* p, int f0, int nf, const float* sources, hipStream_t st) {
   const GemmArgs a = args_b3(p, f0, nf, sources);
-  return launch_gemm(KIND_B3, p->bf16(), p->ts_b3, a, wg_count(a), st);
+  return launch_gemm(KIND_B3, p->bf16(), p->ts_b3, a, stage_wgs(p, KIND_B3, a, p->ts_b3), st);
 }
 
 // B4 over frames [f0, f0 + nf) of chunk c: W = c M^H U, phase gradient and position sums.
@@ -334,7 +384,7 @@ GemmArgs args_b4(dlx_plan* p, int c, int f0, int nf) {
 
 hipError_t run_b4(dlx_plan* p, int c, int f0, int nf, hipStream_t st) {
   const GemmArgs a = args_b4(p, c, f0, nf);
-  return launch_gemm(KIND_B4, p->bf16(), p->ts_b4, a, wg_count(a), st);
+  return launch_gemm(KIND_B4, p->bf16(), p->ts_b4, a, stage_wgs(p, KIND_B4, a, p->ts_b4), st);
 }
 
 // B3 and B4 of chunk c.
@@ -472,7 +522,7 @@ TuneKey tune_key(const dlx_plan* p) {
   int dev = 0;
   (void)hipGetDevice(&dev);
   return {dev, (long long)p->prec, p->Ni, p->No, p->Q, p->L, p->S, p->F, p->frames_per_chunk, p->Nz, p->Nmap,
-          (p->seed_pass ? 1 : 0) | (p->fold ? 2 : 0)};
+          (p->seed_pass ? 1 : 0) | (p->fold ? 2 : 0) | (p->range ? 4 + 8LL * p->lo_reg : 0)};
 }
 
 // "dlx-tune-v2 <arch> <CUs> <prec Ni No Q L S F frames_per_chunk Nz Nmap flags>" of the cache file:
@@ -1076,6 +1126,11 @@ dlx_status group_eval(dlx_plan* p, const dlx_eval_args* a, hipStream_t st) {
   return DLX_OK;
 }
 
+struct TableInner;
+bool table_allowed(const dlx_problem_desc& d);
+dlx_status create_one(const dlx_problem_desc& d, dlx_precision precision, int32_t flags, size_t workspace_limit_bytes,
+                      bool allow_table, const TableInner* inner, dlx_plan** out);
+
 constexpr int kSideStreams = 4;
 
 // One plan per problem; problem k's arrays sit at offs[k] in every packed array.
@@ -1091,8 +1146,8 @@ dlx_status create_multi(const dlx_problem_desc* probs, int32_t n, dlx_precision 
   dlx_offsets o{};
   for (int k = 0; k < n; ++k) {
     dlx_plan* sub = nullptr;
-    const dlx_status s = dlx_plan_create(&probs[k], 1, prec, grouped ? (flags | DLX_FLAG_NO_AUTOTUNE) : flags, limit,
-                                         &sub);
+    const dlx_status s = create_one(probs[k], prec, grouped ? (flags | DLX_FLAG_NO_AUTOTUNE) : flags, limit,
+                                    !grouped && table_allowed(probs[k]), nullptr, &sub);
     if (s != DLX_OK) {
       dlx_plan_destroy(p);
       return s;
@@ -1185,22 +1240,156 @@ T* at(T* base, long long off) {
   return base ? base + off : nullptr;
 }
 
-}  // namespace
+// What a PSF table's own plan takes from the outer one.
+struct TableInner {
+  const int* range;
+  int lo_reg;
+  float* H;
+  double du;   // the focal grid's pitch: the field's factor dx du / lambda is that grid's, not the table's
+};
 
-extern "C" {
+// Problems that run on a PSF table when that is the cheaper form. One-frame problems without a phase map
+// or integer dithers keep their own transforms: the grouped launches of a multi-problem plan run them so,
+// and give the same images bit for bit.
+bool table_allowed(const dlx_problem_desc& d) { return d.n_frames > 1 || d.frame_dithers || d.n_map > 0; }
 
-dlx_status dlx_plan_create(const dlx_problem_desc* probs, int32_t n_probs, dlx_precision precision, int32_t flags,
-                           size_t workspace_limit_bytes, dlx_plan** out) {
-  if (!out) return DLX_ERR_INVALID_ARG;
+constexpr double kTableBeta = 20.0;   // interpolation error about exp(-beta)
+
+// The table's pitch, taps and sizes for a problem, or false where one transform pair per star, frame and
+// wavelength is the cheaper form. A finer pitch (h16 up) needs fewer taps but more samples to transform;
+// the estimate weighs the folded products at their measured rate (85 TFLOP/s executed, 70 on a table,
+// whose launches are smaller) against the FP64 matrix instructions of the interpolation and its adjoint
+// (32 flops per cycle and SIMD, 60% reached) and the passes over memory.
+bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
+  // The table's products are FP32 in both arithmetics (they are a small part of the evaluation). A split
+  // plan of few wavelengths keeps its own products: its error in the faintest pixels, 2e-5 to 6e-5 of the
+  // residual (2e-6 to 1e-5 where 16 or more wavelengths average it), would make the two forms of one
+  // problem differ by as much.
+  if (p->prec == DLX_BF16X3 && p->L < 16) return false;
+  const double Ni = p->Ni, No = p->No, L = p->L, nfs = (double)p->F * p->S;
+  const double lmin = *std::min_element(p->lam.begin(), p->lam.end());
+  const double lmax = *std::max_element(p->lam.begin(), p->lam.end());
+  const double direct = 4.0 * p->n_psf * (No * Ni * Ni + No * No * Ni) / 85e6 + p->n_psf * No * No * 8.0 / 4.5e6;
+  double least = 0.85 * direct;
+  bool found = false;
+  const int nb = ceil_div(p->No, 16);
+  for (int h16 = 1; h16 <= 40; ++h16) {
+    const double h = h16 / 16.0, tau = p->du / h, sigma = lmin / (2.0 * p->D) / tau;
+    if (!(sigma >= 1.2)) continue;
+    if (sigma > 4.0 && found) break;
+    const int W = (int)std::ceil(2.0 * kTableBeta / (3.14159265358979 * (1.0 - 1.0 / sigma)));
+    if (W > 72) continue;
+    const int K = round_up((int)std::floor(15.0 * h) + W + 1, 8);
+    // samples in use for stars within the middle of the detector, with the taps and the stencil around them
+    const int n_reg = round_up((int)std::ceil(No * h * (nfs > 1 ? 1.25 : 1.02) + 2 * W + 10), 64);
+    const double half = 0.5 * (No - 1) * h + 0.5 * lmax / p->dx / tau + W + 6;
+    if (half > 16000.0) continue;
+    const int Nt = std::max(n_reg, round_up((int)std::ceil(2.0 * half), 64));
+    const double n = n_reg;
+    const double tiles = (n / 32) * (n / 32);
+    const double fwd = (std::ceil((3 * h16 + K) / 16.0) * K / 4 + 4.0 * (K / 16.0 + 1) * 4) / 4 * nb * nb;
+    const double nx = std::min((32.0 + K) / h16, (double)nb);
+    const double adj = tiles * nx * (nx * 6.0 + 16.0);
+    const double est = 4.0 * L * (n * Ni * Ni + n * n * Ni) / 70e6 + L * n * n * 8.0 / 3e6 +
+                       nfs * (fwd + adj) * 64.0 / (1024 * 2400.0 * 0.6) + nfs * No * No * 12.0 / 3e6 + 30.0;
+    if (est >= least) continue;
+    least = est;
+    found = true;
+    TableArgs t = {};
+    t.Nt = Nt;
+    t.No = p->No;
+    t.ldg = p->ldNo;
+    t.nb = nb;
+    t.h16 = h16;
+    t.W = W;
+    t.K = K;
+    t.L = p->L;
+    t.S = p->S;
+    t.nfs = p->F * p->S;
+    t.slots = 4 * ceil_div((long long)std::min(tiles, 4096.0), 4);
+    t.tau = tau;
+    t.c0 = 0.5 * (Nt - 1) - 0.5 * (No - 1) * h;
+    t.beta = kTableBeta;
+    t.half_min = 0.5 * lmin / p->dx;
+    t.dx = p->dx;
+    *best = t;
+    *best_reg = n_reg;
+  }
+  return found;
+}
+
+// A plan on a PSF table: the images' arrays here, the optics in the table's own one-star plan.
+// DLX_ERR_UNSUPPORTED (with nothing kept) where the problem takes the other form.
+dlx_status create_with_table(dlx_plan* p, const dlx_problem_desc& d, int flags) {
+  TableArgs t;
+  int n_reg = 0;
+  if (!choose_table(p, &t, &n_reg)) return DLX_ERR_UNSUPPORTED;
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return DLX_ERR_HIP;
+  const size_t nt2 = (size_t)t.Nt * t.Nt, frame = sizeof(float) * p->S * p->No * (size_t)p->ldNo + per_frame_bytes(p);
+  // one grid layer per star of a chunk: at most 65535
+  if (p->S > 65535) return DLX_ERR_UNSUPPORTED;
+  const size_t most = std::min<size_t>(kDefaultChunkBudget / frame, 65535 / p->S);
+  const int fc = (int)std::max<size_t>(1, std::min<size_t>(p->F, most));
+  if (p->store_fields && fc < p->F) return DLX_ERR_UNSUPPORTED;
+  t.groups = std::max(1, std::min(fc * p->S, ceil_div(2048, t.slots)));
+  t.per_group = ceil_div((long long)fc * p->S, t.groups);
+  // the table for stars anywhere in the pupil grid's own field: fields, seed weights, transform buffers and
+  // matrices (a third of the free memory at most, else the other form)
+  const size_t optics = sizeof(float) * (size_t)p->L * (2 * nt2 + nt2 + 8 * (size_t)t.Nt * p->ldNi);
+  if (optics + 8 * (3 + t.groups) * nt2 + fc * frame > free_b / 3) return DLX_ERR_UNSUPPORTED;
+
+  p->ta = t;
+  p->frames_per_chunk = fc;
+  p->n_chunks = ceil_div(p->F, fc);
+  p->chunk_psf = fc * p->S * p->L;
+  p->n_reg = n_reg;
+  p->loss_blocks = loss_block_count((long long)p->Nd_img * p->Nd_img);
+  p->seed_blocks = seed_block_count((long long)p->Nd * p->Nd);
+  Pool sizing{nullptr, 0};
+  layout(p, sizing);
+  p->pool_bytes = sizing.off + 256;
+  dlx_status s = DLX_ERR_UNSUPPORTED;
+  if (hipMalloc(&p->pool, p->pool_bytes) == hipSuccess) {
+    Pool pool{reinterpret_cast<char*>(p->pool), 0};
+    layout(p, pool);
+    const int lo_reg = (t.Nt - n_reg) / 2;
+    const int range[2] = {lo_reg, 0};
+    const float unit[3] = {0.f, 0.f, 1.f};
+    hipError_t e = hipMemset(p->pool, 0, p->pool_bytes);
+    if (e == hipSuccess) e = hipMemcpy(p->ta.range, range, sizeof range, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(p->d_tune, unit, sizeof unit, hipMemcpyHostToDevice);
+    if (e == hipSuccess && p->dither)
+      e = hipMemcpy(p->d_win, p->win.data(), sizeof(int) * p->win.size(), hipMemcpyHostToDevice);
+    dlx_problem_desc td = d;
+    td.n_focal = t.Nt;
+    td.oversample = 1;
+    td.n_sources = td.n_frames = 1;
+    td.focal_pixel_rad = t.tau;
+    td.frame_dithers = nullptr;
+    const TableInner inner{p->ta.range, lo_reg, p->ta.H, p->du};
+    s = e != hipSuccess ? DLX_ERR_HIP
+                        : create_one(td, DLX_FP32, flags & DLX_FLAG_NO_AUTOTUNE, 0, false, &inner, &p->tab);
+    if (s == DLX_ERR_OOM) s = DLX_ERR_UNSUPPORTED;
+  }
+  if (s != DLX_OK) {
+    if (p->pool) (void)hipFree(p->pool);
+    p->pool = nullptr;
+    p->ta = TableArgs{};
+    p->tab = nullptr;
+    return s;
+  }
+  p->ta.wl = p->tab->d_wl;
+  p->ta.E = p->tab->d_Y;
+  p->ta.e_plane = (long long)p->L * t.Nt * t.Nt;
+  p->ta.e_by_wl = (long long)t.Nt * t.Nt;
+  p->pool_bytes += p->tab->pool_bytes;
+  return DLX_OK;
+}
+
+dlx_status create_one(const dlx_problem_desc& d, dlx_precision precision, int32_t flags, size_t workspace_limit_bytes,
+                      bool allow_table, const TableInner* inner, dlx_plan** out) {
   *out = nullptr;
-  dlx_status v = dlx_validate(probs, n_probs);
-  if (v != DLX_OK) return v;
-  if (precision != DLX_FP32 && precision != DLX_BF16X3) return DLX_ERR_INVALID_ARG;
-  if ((flags & ~(DLX_FLAG_NO_AUTOTUNE | DLX_FLAG_SEED_PASS | DLX_FLAG_STORE_FIELDS | DLX_FLAG_PIXEL_KERNEL |
-                 DLX_FLAG_DENSE_MFT | DLX_FLAG_GROUPED)) != 0)
-    return DLX_ERR_INVALID_ARG;
-  if (n_probs > 1) return create_multi(probs, n_probs, precision, flags, workspace_limit_bytes, out);
-  const dlx_problem_desc& d = probs[0];
 
   dlx_plan* p = new (std::nothrow) dlx_plan();
   if (!p) return DLX_ERR_OOM;
@@ -1237,6 +1426,10 @@ dlx_status dlx_plan_create(const dlx_problem_desc* probs, int32_t n_probs, dlx_p
   p->ldNo = round_up(p->No, 16);
   p->fold = (flags & DLX_FLAG_DENSE_MFT) == 0;
   p->n_psf = p->F * p->S * p->L;
+  if (inner) {
+    p->range = inner->range;
+    p->lo_reg = inner->lo_reg;
+  }
 
   // chunk of whole frames whose intermediates fit the budget (stored fields: every frame in one chunk)
   p->store_fields = (flags & DLX_FLAG_STORE_FIELDS) != 0;
@@ -1244,6 +1437,17 @@ dlx_status dlx_plan_create(const dlx_problem_desc* probs, int32_t n_probs, dlx_p
   if (p->k_per_pixel && p->dither) {   // the windows would need a frame-dependent binning
     delete p;
     return DLX_ERR_UNSUPPORTED;
+  }
+  if (allow_table && p->fold && !workspace_limit_bytes) {
+    const dlx_status ts = create_with_table(p, d, flags);
+    if (ts == DLX_OK) {
+      *out = p;
+      return DLX_OK;
+    }
+    if (ts != DLX_ERR_UNSUPPORTED) {
+      delete p;
+      return ts;
+    }
   }
   size_t budget = workspace_limit_bytes ? workspace_limit_bytes : kDefaultChunkBudget;
   if (p->store_fields && !workspace_limit_bytes) {
@@ -1325,12 +1529,13 @@ dlx_status dlx_plan_create(const dlx_problem_desc* probs, int32_t n_probs, dlx_p
   }
   Pool pool{reinterpret_cast<char*>(p->pool), 0};
   layout(p, pool);
+  if (inner) p->d_G = inner->H;
 
   std::vector<WlInfo> wl(p->L);
   for (int l = 0; l < p->L; ++l) {
     wl[l].lam = p->lam[l];
     wl[l].w = (float)p->wts[l];
-    wl[l].scale = (float)(p->dx * p->du / p->lam[l]);
+    wl[l].scale = (float)(p->dx * (inner ? inner->du : p->du) / p->lam[l]);
     wl[l].kphase = (float)(kTwoPi / p->lam[l]);
     wl[l].pad = 0.f;
   }
@@ -1349,6 +1554,116 @@ dlx_status dlx_plan_create(const dlx_problem_desc* probs, int32_t n_probs, dlx_p
   }
   *out = p;
   return DLX_OK;
+}
+
+// ---- the stages of a plan on a PSF table (p->tab: the table's own plan, p->ta: its images' side)
+
+// The stars' weights and the table's fields: one transform pair per wavelength.
+dlx_status table_fields(dlx_plan* p, const float* transmission, const float* zernike_basis, const float* map_basis,
+                        const float* zernike_coeffs, const float* phase_map, const float* sources, hipStream_t st) {
+  dlx_plan* q = p->tab;
+  {
+    Stage sg(p, st, DLX_STAGE_PREP, q->n_psf);
+    DLX_HIP(launch_table_weights(p->ta, sources, st));
+    DLX_HIP(launch_prep(q, transmission, zernike_basis, map_basis, zernike_coeffs, phase_map, p->d_tune, st));
+  }
+  {
+    Stage sg(p, st, DLX_STAGE_F1, q->n_psf);
+    DLX_HIP(run_f1(q, 0, 1, st));
+  }
+  Stage sg(p, st, DLX_STAGE_F2, q->n_psf);
+  DLX_HIP(run_f2(q, 0, 1, st));
+  return DLX_OK;
+}
+
+// Images of frames [f0, f0 + nf): per star, and (where given) binned and times the pixel response.
+dlx_status table_images(dlx_plan* p, int f0, int nf, const float* sources, const float* intrapixel, const float* flat,
+                        float* binned, float* model, hipStream_t st) {
+  Stage sg(p, st, DLX_STAGE_BIN, (long long)nf * p->S * p->L);
+  if (f0 == 0) DLX_HIP(launch_table_image(p->ta, p->n_reg, false, st));
+  DLX_HIP(launch_table_shift(p->ta, sources, f0, nf, st));
+  const long long kst = p->k_per_pixel ? (long long)p->Q * p->Q : 0;
+  const bool big = p->dither && binned;   // bin the enlarged plane once, then cut every frame's window
+  DLX_HIP(launch_table_bin(p->ta, p->Q, p->Nd, f0, nf, sources, intrapixel, kst, big ? nullptr : flat, p->d_bs,
+                           big ? p->d_Bbig : binned, big ? nullptr : model, st));
+  if (big) DLX_HIP(launch_window(p, flat, binned, model, st));
+  return DLX_OK;
+}
+
+// The seed weights of frames [f0, f0 + nf) onto the table, and dL/dK.
+dlx_status table_spread(dlx_plan* p, int f0, int nf, const float* sources, const float* flat, const float* resid,
+                        double* grad_intrapixel, hipStream_t st) {
+  Stage sg(p, st, DLX_STAGE_SEED, (long long)nf * p->S * p->L);
+  if (grad_intrapixel)
+    DLX_HIP(launch_table_kgrad(p->ta, p->Q, p->Nd, f0, nf, sources, flat, resid, p->dither ? p->d_win : nullptr,
+                               p->F_img, p->Nd_img, p->d_kpart, p->k_per_pixel ? grad_intrapixel : nullptr, f0 == 0,
+                               st));
+  if (f0 == 0) DLX_HIP(launch_table_image(p->ta, p->n_reg, true, st));
+  DLX_HIP(launch_table_adjoint(p->ta, sources, f0, nf, f0 == 0, st));
+  return DLX_OK;
+}
+
+// The adjoint transforms, once every frame is on the table, and the final reductions.
+dlx_status table_gradient(dlx_plan* p, const float* zernike_basis, const float* map_basis, double* grad_zernike,
+                          double* grad_map, double* grad_sources, double* grad_intrapixel, double* loss,
+                          hipStream_t st) {
+  dlx_plan* q = p->tab;
+  {
+    Stage sg(p, st, DLX_STAGE_SEED, q->n_psf);
+    DLX_HIP(launch_table_seed(p->ta, p->n_reg, st));
+  }
+  {
+    Stage sg(p, st, DLX_STAGE_B3, q->n_psf);
+    DLX_HIP(run_b3(q, 0, 1, p->d_tune, st));
+  }
+  {
+    Stage sg(p, st, DLX_STAGE_B4, q->n_psf);
+    DLX_HIP(run_b4(q, 0, 0, 1, st));
+  }
+  Stage sg(p, st, DLX_STAGE_GRAD, p->n_psf);
+  DLX_HIP(launch_grad_reduce(q, p, zernike_basis, map_basis, grad_zernike, grad_map, grad_sources, loss, p->n_chunks,
+                             grad_intrapixel, st));
+  return DLX_OK;
+}
+
+dlx_status table_eval(dlx_plan* p, const dlx_eval_args* a, hipStream_t st) {
+  dlx_status s = table_fields(p, a->transmission, a->zernike_basis, a->map_basis, a->zernike_coeffs, a->phase_map,
+                              a->sources, st);
+  for (int c = 0; c < p->n_chunks && s == DLX_OK; ++c) {
+    const int f0 = c * p->frames_per_chunk;
+    const int nf = std::min(p->frames_per_chunk, p->F - f0);
+    s = table_images(p, f0, nf, a->sources, a->intrapixel, a->flat, a->binned, a->model, st);
+    if (s != DLX_OK) return s;
+    {
+      Stage sg(p, st, DLX_STAGE_LOSS, (long long)nf * p->S * p->L);
+      DLX_HIP(launch_loss(p, p->dither ? 0 : f0, p->dither ? p->F_img : nf, c, a->model, a->binned, a->data, a->flat,
+                          (int)a->loss_kind, a->prior_mu, a->prior_sigma, a->dloss_dmodel, a->grad_flat,
+                          p->dither ? nullptr : &a->intrapixel, st));
+      if (p->dither) DLX_HIP(launch_seed_gather(p, a->flat, a->dloss_dmodel, a->intrapixel, st));
+    }
+    s = table_spread(p, f0, nf, a->sources, a->flat, a->dloss_dmodel, a->grad_intrapixel, st);
+  }
+  if (s != DLX_OK) return s;
+  return table_gradient(p, a->zernike_basis, a->map_basis, a->grad_zernike, a->grad_map, a->grad_sources,
+                        a->grad_intrapixel, a->loss, st);
+}
+
+}  // namespace
+
+extern "C" {
+
+dlx_status dlx_plan_create(const dlx_problem_desc* probs, int32_t n_probs, dlx_precision precision, int32_t flags,
+                           size_t workspace_limit_bytes, dlx_plan** out) {
+  if (!out) return DLX_ERR_INVALID_ARG;
+  *out = nullptr;
+  dlx_status v = dlx_validate(probs, n_probs);
+  if (v != DLX_OK) return v;
+  if (precision != DLX_FP32 && precision != DLX_BF16X3) return DLX_ERR_INVALID_ARG;
+  if ((flags & ~(DLX_FLAG_NO_AUTOTUNE | DLX_FLAG_SEED_PASS | DLX_FLAG_STORE_FIELDS | DLX_FLAG_PIXEL_KERNEL |
+                 DLX_FLAG_DENSE_MFT | DLX_FLAG_GROUPED)) != 0)
+    return DLX_ERR_INVALID_ARG;
+  if (n_probs > 1) return create_multi(probs, n_probs, precision, flags, workspace_limit_bytes, out);
+  return create_one(probs[0], precision, flags, workspace_limit_bytes, table_allowed(probs[0]), nullptr, out);
 }
 
 dlx_status dlx_plan_destroy(dlx_plan* p) {
@@ -1377,9 +1692,10 @@ dlx_status dlx_plan_destroy(dlx_plan* p) {
   if (p->graph_exec) (void)hipGraphExecDestroy(p->graph_exec);
   if (p->graph) (void)hipGraphDestroy(p->graph);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
+  const dlx_status e3 = dlx_plan_destroy(p->tab);
   const hipError_t e2 = p->pool ? hipFree(p->pool) : hipSuccess;
   delete p;
-  return (e1 == hipSuccess && e2 == hipSuccess) ? DLX_OK : DLX_ERR_HIP;
+  return (e3 == DLX_OK && e1 == hipSuccess && e2 == hipSuccess) ? DLX_OK : DLX_ERR_HIP;
 }
 
 size_t dlx_plan_workspace_bytes(const dlx_plan* p) { return p ? p->pool_bytes : 0; }
@@ -1401,6 +1717,7 @@ int32_t dlx_plan_problems(const dlx_plan* p) { return p ? (p->multi() ? (int32_t
 dlx_status dlx_plan_tiles(const dlx_plan* p, int32_t* tiles) {
   if (!p || !tiles) return DLX_ERR_INVALID_ARG;
   if (p->multi()) return dlx_plan_tiles(p->subs[0], tiles);
+  if (p->tab) return dlx_plan_tiles(p->tab, tiles);
   const TileShape t[4] = {p->ts_f1, p->ts_f2, p->ts_b3, p->ts_b4};
   for (int k = 0; k < 4; ++k) {
     tiles[2 * k] = t[k].wm;
@@ -1485,6 +1802,7 @@ dlx_status dlx_plan_set_phase_screen(dlx_plan* p, int32_t problem, const float* 
     return dlx_plan_set_phase_screen(p->subs[problem], 0, screen, stream);
   }
   if (problem != 0) return DLX_ERR_INVALID_ARG;
+  if (p->tab) return dlx_plan_set_phase_screen(p->tab, 0, screen, stream);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const long long n = (long long)p->Ni * p->Ni;
   if (screen) {
@@ -1536,6 +1854,14 @@ dlx_status dlx_psf_forward(dlx_plan* p, const float* transmission, const float* 
   if (p->Nz > 0 && (!zernike_basis || !zernike_coeffs)) return DLX_ERR_INVALID_ARG;
   if ((p->Nmap > 0) != (map_basis != nullptr) || (p->Nmap > 0) != (phase_map != nullptr)) return DLX_ERR_INVALID_ARG;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  if (p->tab) {
+    dlx_status s = table_fields(p, transmission, zernike_basis, map_basis, zernike_coeffs, phase_map, sources, st);
+    for (int f0 = 0; f0 < p->F && s == DLX_OK; f0 += p->frames_per_chunk)
+      s = table_images(p, f0, std::min(p->frames_per_chunk, p->F - f0), sources, intrapixel, flat, binned_out,
+                       model_out, st);
+    p->fields_valid = s == DLX_OK && p->store_fields;
+    return s;
+  }
   {
     Stage sg(p, st, DLX_STAGE_PREP, p->n_psf);
     DLX_HIP(launch_prep(p, transmission, zernike_basis, map_basis, zernike_coeffs, phase_map, sources, st));
@@ -1615,6 +1941,26 @@ dlx_status dlx_psf_backward(dlx_plan* p, const float* transmission, const float*
   // images of every PSF in the workspace (one chunk); only the adjoint runs
   const bool reuse = p->store_fields && p->fields_valid;
   p->fields_valid = false;
+  if (p->tab) {
+    dlx_status s = DLX_OK;
+    if (!reuse) s = table_fields(p, transmission, zernike_basis, map_basis, zernike_coeffs, phase_map, sources, st);
+    for (int f0 = 0; f0 < p->F && s == DLX_OK; f0 += p->frames_per_chunk) {
+      const int nf = std::min(p->frames_per_chunk, p->F - f0);
+      if (!reuse) s = table_images(p, f0, nf, sources, intrapixel, flat, nullptr, nullptr, st);
+      if (s != DLX_OK) return s;
+      {
+        Stage sg(p, st, DLX_STAGE_SEED, (long long)nf * p->S * p->L);
+        if (p->dither)
+          DLX_HIP(launch_seed_gather(p, flat, dloss_dmodel, intrapixel, st));
+        else
+          DLX_HIP(launch_seed(p, f0, nf, flat, dloss_dmodel, intrapixel, st));
+      }
+      s = table_spread(p, f0, nf, sources, flat, dloss_dmodel, grad_intrapixel, st);
+    }
+    if (s != DLX_OK) return s;
+    return table_gradient(p, zernike_basis, map_basis, grad_zernike, grad_map, grad_sources, grad_intrapixel, nullptr,
+                          st);
+  }
   if (!reuse) {
     Stage sg(p, st, DLX_STAGE_PREP, p->n_psf);
     DLX_HIP(launch_prep(p, transmission, zernike_basis, map_basis, zernike_coeffs, phase_map, sources, st));
@@ -1649,7 +1995,7 @@ dlx_status dlx_psf_backward(dlx_plan* p, const float* transmission, const float*
     DLX_HIP(run_adjoint(p, c, f0, nf, sources, st));
   }
   Stage sg(p, st, DLX_STAGE_GRAD, p->n_psf);
-  DLX_HIP(launch_grad_reduce(p, zernike_basis, map_basis, grad_zernike, grad_map, grad_sources, nullptr, 0,
+  DLX_HIP(launch_grad_reduce(p, p, zernike_basis, map_basis, grad_zernike, grad_map, grad_sources, nullptr, 0,
                              grad_intrapixel, st));
   return DLX_OK;
 }
@@ -1711,6 +2057,7 @@ dlx_status dlx_eval(dlx_plan* p, const dlx_eval_args* a, void* stream) {
     return DLX_ERR_INVALID_ARG;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   p->fields_valid = false;
+  if (p->tab) return table_eval(p, a, st);
   {
     Stage sg(p, st, DLX_STAGE_PREP, p->n_psf);
     DLX_HIP(launch_prep(p, a->transmission, a->zernike_basis, a->map_basis, a->zernike_coeffs, a->phase_map,
@@ -1769,7 +2116,7 @@ dlx_status dlx_eval(dlx_plan* p, const dlx_eval_args* a, void* stream) {
     DLX_HIP(run_adjoint(p, c, f0, nf, a->sources, st));
   }
   Stage sg(p, st, DLX_STAGE_GRAD, p->n_psf);
-  DLX_HIP(launch_grad_reduce(p, a->zernike_basis, a->map_basis, a->grad_zernike, a->grad_map, a->grad_sources, a->loss,
+  DLX_HIP(launch_grad_reduce(p, p, a->zernike_basis, a->map_basis, a->grad_zernike, a->grad_map, a->grad_sources, a->loss,
                              p->n_chunks, a->grad_intrapixel, st));
   return DLX_OK;
 }

@@ -106,6 +106,52 @@ struct GemmArgs {
   // grouped launches of a multi-problem plan: offset of the problem's star table in the call's
   // packed sources (the launch passes the base; `sources` above is unused there)
   long long src_off;
+  // PSF table (see TableArgs): range[0] is the first table row and column in use (the last is
+  // mirror-symmetric), range[1] is nonzero when every wavelength has its own seed weights
+  const int* range;
+  long long seedw_by_wl;
+};
+
+// ---- The shared PSF table. A star at angular offset (alpha, beta) tilts the pupil field by a phase
+// that is linear in the pupil coordinate, so its focal field is the on-axis field moved by (alpha, beta),
+// and its image summed over the band is the on-axis polychromatic image I(u) = sum_l w_l |E_l(u)|^2 moved
+// likewise: every star of every frame is one image, shifted. |E_l|^2 has no frequency above D / lambda, so
+// I is computed once per evaluation on a table of pitch tau < lambda_min / (2 D) (one transform pair per
+// wavelength instead of one per star, frame and wavelength) and each star's samples are interpolated from
+// it in FP64 by a windowed sinc of W taps,
+//   phi(t) = sinc(t) exp(beta (sqrt(1 - (2 t / W)^2) - 1)),  |t| < W / 2,
+// whose error (about exp(-beta), beta = 20) lies two orders below the FP32 transforms' own. The adjoint
+// is the transpose: the seed weights of every frame are spread onto the table with the same weights and
+// summed over the stars, and one adjoint transform per wavelength follows.
+// The table pitch is chosen so that 16 focal samples advance by a whole number h16 of table samples: the
+// weights of a block of 16 outputs are then the same for every block of a star's image.
+struct TableArgs {
+  int Nt;          // table samples per side, a multiple of 64
+  int No, ldg;     // focal samples per side, row length of the planes and seed weights
+  int nb;          // blocks of 16 focal samples per side
+  int h16;         // table samples per 16 focal samples
+  int W, K;        // taps; table samples a block of 16 outputs may touch (multiple of 8)
+  int L, S, nfs;   // wavelengths, stars per frame, stars in all
+  int slots;       // position-gradient partials per star
+  int groups, per_group;   // star groups of the adjoint (each sums its stars into its own plane)
+  double tau, c0, beta;    // pitch (radians); table coordinate of focal sample 0 of a star on the axis
+  double half_min;         // lambda_min / (2 dx): beyond it a tilt is reduced by each wavelength's period
+  double dx;
+  const WlInfo* wl;
+  const float* E;          // table fields [L][Nt][Nt] planar
+  long long e_plane, e_by_wl;
+  double* I;               // polychromatic table, and its derivatives along x and y
+  double* Ix;
+  double* Iy;
+  double* wt;              // weights [nfs][2][16][K] (x, y)
+  int* base;               // first table sample of block 0 [nfs][2]
+  int* far;                // [nfs] 1: a tilt beyond half_min
+  int* range;              // {lo, any far star}
+  float* planes;           // star images on the focal grid [chunk frames * S][No][ldg]
+  const float* G;          // seed weights [chunk frames][No][ldg]
+  double* Hpart;           // [groups][Nt][Nt]
+  float* H;                // table seed weights [1 + L][Nt][Nt]
+  double* pos;             // [nfs][slots][2]
 };
 
 // Tile shape of one GEMM launch: 4 waves (2 x 2), each WM x WN blocks of 16 x 16.
@@ -212,6 +258,18 @@ hipError_t launch_loss_plain(int nf, long long npix, const float* model, const f
                              const float* flat, int kind, double mu, double sigma, float* r, double* gflat,
                              double* blk, int* status, double* loss, hipStream_t st);
 hipError_t launch_gemm(int kind, int prec, TileShape ts, const GemmArgs& a, int n_wg, hipStream_t st);
+hipError_t launch_table_weights(const TableArgs& t, const float* sources, hipStream_t st);
+hipError_t launch_table_image(const TableArgs& t, int n_reg, bool derivatives, hipStream_t st);
+hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, int nf, hipStream_t st);
+hipError_t launch_table_bin(const TableArgs& t, int Q, int Nd, int f0, int nf, const float* sources,
+                            const float* intrapixel, long long kst, const float* flat, float* bs, float* binned,
+                            float* model, hipStream_t st);
+hipError_t launch_table_adjoint(const TableArgs& t, const float* sources, int f0, int nf, bool first,
+                                hipStream_t st);
+hipError_t launch_table_seed(const TableArgs& t, int n_reg, hipStream_t st);
+hipError_t launch_table_kgrad(const TableArgs& t, int Q, int Nd, int f0, int nf, const float* sources,
+                              const float* flat, const float* resid, const int* win, int F_img, int Nd_img,
+                              double* part, double* gpix, bool first, hipStream_t st);
 // One folded stage over many problems: n_wg workgroups, tab[g] = (problem, its logical workgroup),
 // args = per-problem arguments in device memory, sources = the call's packed star table.
 hipError_t launch_gemm_group(int kind, int prec, TileShape ts, const GemmArgs* args, const int2* tab, int n_wg,
@@ -317,6 +375,17 @@ struct dlx_plan {
   bool k_per_pixel = false;   // one intra-pixel kernel per detector pixel ([Nd][Nd][Q][Q])
   bool store_fields = false;  // keep E and the per-star binned images from forward to backward
   bool fields_valid = false;  // the workspace holds the fields of the last dlx_psf_forward
+  // shared PSF table: its one-star plan (fields, adjoint, dL/dOPD), which also holds the optics of the
+  // evaluation, and the table's own arrays
+  dlx_plan* tab = nullptr;
+  void* tab_pool = nullptr;
+  dlx::TableArgs ta = {};
+  int n_reg = 0;                 // table samples per side in use when the stars lie within the detector
+  const int* range = nullptr;    // a table's own plan: the outer plan's range
+  int lo_reg = 0;                // and the first row in use for n_reg
+  // stored columns of the seed weights: natural order with a table, else the fold's
+  int ghNo() const { return tab ? No : hNo(); }
+  int gsNo() const { return tab ? 0 : sNo(); }
   // captured evaluation
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;

@@ -577,8 +577,15 @@ __device__ __forceinline__ f4 rev4(f4 v) { return f4{v[3], v[2], v[1], v[0]}; }
 // it and are not compiled (fold_tile_ok).
 // The folded stage for the workgroup at logical index `lin` of its problem's own grid; `src` is the
 // problem's [F][S][3] star table (read by B3 for w phi).
+// `tr` restricts a launch to part of the product (the rows and columns of the PSF table in use).
+struct TileRange {
+  int tm0, tn0;           // first tile row and column
+  int tiles_m, tiles_n;   // tile rows and columns
+  int k0;                 // first contracted index
+};
+
 template <int KIND, int WM, int WN, int PREC>
-__device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const float* src) {
+__device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const float* src, const TileRange tr) {
   constexpr bool DA = KIND != KIND_F2;   // DFT operand on the A side (rows i), data on the B side
   constexpr int BM = 32 * WM, BN = 32 * WN;
   constexpr int BK = PREC == 0 ? 16 : 32;
@@ -601,7 +608,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;
-  const int tiles = a.tiles_m * a.tiles_n;
+  const int tiles = tr.tiles_m * tr.tiles_n;
   const int item = lin / tiles;
   if (item >= a.n_items) return;
   const int tile = lin - item * tiles;
@@ -610,9 +617,9 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
   // L2. F1 and F2 keep the DFT tile fixed while the data tiles vary: F2's data rows (T) are already
   // shared by the workgroups of one row tile, and F1's (the pupil field) by every PSF of a wavelength.
   constexpr bool DFT_FAST = KIND == KIND_B3 || KIND == KIND_B4;
-  const int tm = DFT_FAST ? tile % a.tiles_m : tile / a.tiles_n;
-  const int tn = DFT_FAST ? tile / a.tiles_m : tile - tm * a.tiles_n;
-  const int row0 = tm * BM, col0 = tn * BN;
+  const int tm = DFT_FAST ? tile % tr.tiles_m : tile / tr.tiles_n;
+  const int tn = DFT_FAST ? tile / tr.tiles_m : tile - tm * tr.tiles_n;
+  const int row0 = (tr.tm0 + tm) * BM, col0 = (tr.tn0 + tn) * BN;
   const int M = a.M, N = a.N, K = a.K;
   const int rowD0 = DA ? row0 : col0, rowX0 = DA ? col0 : row0;
   const int nD = DA ? M : N, nX = DA ? N : M;
@@ -641,11 +648,11 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
       shi[bm][bn] = f4{0.f, 0.f, 0.f, 0.f};
     }
 
-  int k_lo = 0, k_hi = K;
+  int k_lo = tr.k0, k_hi = K;
   if constexpr (KIND == KIND_B4) {
     const int ks = item % a.ksplit;
-    const int kc = ((K + a.ksplit * BK - 1) / (a.ksplit * BK)) * BK;
-    k_lo = ks * kc;
+    const int kc = ((K - tr.k0 + a.ksplit * BK - 1) / (a.ksplit * BK)) * BK;
+    k_lo = tr.k0 + ks * kc;
     k_hi = min(K, k_lo + kc);
   }
   const int nk = k_hi > k_lo ? (k_hi - k_lo + BK - 1) / BK : 0;
@@ -676,6 +683,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
         const int fs = gb / a.L;
         wphi = a.wl[wl].w * src[fs * 3 + 2];
         gwb = a.seedw + (long long)(fs / a.S - a.frame0) * a.seedw_by_frame;
+        if (a.range && a.range[1]) gwb += (1 + wl) * a.seedw_by_wl;
       }
     }
   };
@@ -1369,7 +1377,38 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
 
 template <int KIND, int WM, int WN, int PREC>
 __global__ __launch_bounds__(256, PREC == 0 ? 2 : 1) void fgemm_kernel(const GemmArgs a) {
-  fgemm_body<KIND, WM, WN, PREC>(a, xcd_remap(blockIdx.x, gridDim.x), a.sources);
+  fgemm_body<KIND, WM, WN, PREC>(a, xcd_remap(blockIdx.x, gridDim.x), a.sources,
+                                 TileRange{0, 0, a.tiles_m, a.tiles_n, 0});
+}
+
+// A folded stage on the PSF table: only rows and columns [lo, Nt - lo) are in use, lo = a.range[0] (a
+// multiple of 32) being set on the device by the stars' positions. The tiles in use are enumerated
+// compactly; the grid is sized for stars within the detector and each workgroup strides over the rest.
+template <int KIND, int WM, int WN, int PREC>
+__global__ __launch_bounds__(256, PREC == 0 ? 2 : 1) void fgemm_table_kernel(const GemmArgs a) {
+  constexpr int BM = 32 * WM, BN = 32 * WN;
+  const int lo = a.range[0];
+  TileRange tr{0, 0, a.tiles_m, a.tiles_n, 0};
+  if constexpr (KIND == KIND_F1) {   // rows: the folded half of the table
+    tr.tm0 = lo / BM;
+    tr.tiles_m -= tr.tm0;
+  } else if constexpr (KIND == KIND_F2) {   // rows: the whole table; columns: the folded half
+    tr.tm0 = lo / BM;
+    tr.tiles_m = (a.M - lo + BM - 1) / BM - tr.tm0;
+    tr.tn0 = lo / BN;
+    tr.tiles_n -= tr.tn0;
+  } else if constexpr (KIND == KIND_B3) {   // columns: the whole table; contracted: the folded half
+    tr.tn0 = lo / BN;
+    tr.tiles_n = (a.N - lo + BN - 1) / BN - tr.tn0;
+    tr.k0 = lo;
+  } else {
+    tr.k0 = lo;
+  }
+  const int total = tr.tiles_m * tr.tiles_n * a.n_items;
+  for (int w = blockIdx.x; w < total; w += gridDim.x) {
+    fgemm_body<KIND, WM, WN, PREC>(a, xcd_remap(w, total), a.sources, tr);
+    __syncthreads();   // the next tile reuses the LDS buffers
+  }
 }
 
 // One launch of a folded stage over the problems of a multi-problem plan: workgroup g runs logical
@@ -1382,7 +1421,8 @@ __global__ __launch_bounds__(256, PREC == 0 ? 2 : 1) void fgemm_group_kernel(con
                                                                             const float* sources) {
   const int2 e = tab[blockIdx.x];
   const GemmArgs& a = args[e.x];
-  fgemm_body<KIND, WM, WN, PREC>(a, e.y, sources ? sources + a.src_off : nullptr);
+  fgemm_body<KIND, WM, WN, PREC>(a, e.y, sources ? sources + a.src_off : nullptr,
+                                 TileRange{0, 0, a.tiles_m, a.tiles_n, 0});
 }
 
 // Folded tile shapes compiled: those that keep their accumulators in registers. FP32 (two
@@ -1396,7 +1436,10 @@ constexpr bool fold_tile_ok(int kind, int prec, int wm, int wn) {
 template <int KIND, int WM, int WN, int PREC>
 hipError_t launch_fold(dim3 grid, dim3 block, const GemmArgs& a, hipStream_t st) {
   if constexpr (fold_tile_ok(KIND, PREC, WM, WN)) {
-    hipLaunchKernelGGL((fgemm_kernel<KIND, WM, WN, PREC>), grid, block, 0, st, a);
+    if (a.range)
+      hipLaunchKernelGGL((fgemm_table_kernel<KIND, WM, WN, PREC>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((fgemm_kernel<KIND, WM, WN, PREC>), grid, block, 0, st, a);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;

@@ -1001,7 +1001,7 @@ hipError_t launch_seed(dlx_plan* p, int f0, int nf, const float* flat, const flo
                        hipStream_t st) {
   p->flux_blocks = p->seed_blocks;
   hipLaunchKernelGGL(seed_weight_kernel, dim3(p->seed_blocks, nf), dim3(kSeedThreads), 0, st, resid, flat, intrapixel,
-                     kstride(p), p->d_bs, f0, p->Q, p->Nd, p->S, p->ldNo, p->hNo(), p->sNo(), (long long)p->No * p->ldNo,
+                     kstride(p), p->d_bs, f0, p->Q, p->Nd, p->S, p->ldNo, p->ghNo(), p->gsNo(), (long long)p->No * p->ldNo,
                      p->d_G, p->seed_blocks, p->d_flux);
   return hipGetLastError();
 }
@@ -1027,7 +1027,7 @@ hipError_t launch_seed_gather(dlx_plan* p, const float* flat, const float* resid
                               hipStream_t st) {
   p->flux_blocks = p->seed_blocks;
   hipLaunchKernelGGL(seed_gather_kernel, dim3(p->seed_blocks), dim3(kSeedThreads), 0, st, resid, flat, intrapixel,
-                     p->d_bs, p->d_win, p->F_img, p->Nd_img, p->Nd, p->Q, p->S, p->ldNo, p->hNo(), p->sNo(), p->d_G,
+                     p->d_bs, p->d_win, p->F_img, p->Nd_img, p->Nd, p->Q, p->S, p->ldNo, p->ghNo(), p->gsNo(), p->d_G,
                      p->d_flux);
   return hipGetLastError();
 }
@@ -1073,7 +1073,7 @@ hipError_t launch_loss(dlx_plan* p, int f0, int nf, int chunk, const float* mode
   p->lossblk_chunk = nb;
   if (seed_intrapixel_or_none) {
     p->flux_blocks = nb;
-    const SeedOut so{*seed_intrapixel_or_none, kstride(p), p->d_bs, p->Q, p->Nd, p->S, p->ldNo, p->hNo(), p->sNo(),
+    const SeedOut so{*seed_intrapixel_or_none, kstride(p), p->d_bs, p->Q, p->Nd, p->S, p->ldNo, p->ghNo(), p->gsNo(),
                      (long long)p->No * p->ldNo, p->d_G, p->d_flux};
     hipLaunchKernelGGL(loss_kernel<true>, dim3(nb), dim3(kLossThreads), 0, st, model, binned, data, flat, f0, f0 + nf,
                        npix, kind, mu, inv_s2, r, gflat, chunk > 0 ? 1 : 0, blk, p->d_status, so);
@@ -1167,9 +1167,10 @@ int zproj_chunks(long long npix, int Nz) {
 }
 
 // dL/dOPD, its projections and the source gradients; with `loss` also the
-// loss of dlx_eval's n_chunks block-partial slots.
-hipError_t launch_grad_reduce(dlx_plan* p, const float* Z, const float* Bm, double* gz, double* gmap, double* gsrc,
-                              double* loss, int loss_chunks, double* gK, hipStream_t st) {
+// loss of dlx_eval's n_chunks block-partial slots. `p` holds the optics (with a PSF table, the
+// table's own plan), `o` the images' and stars' partial sums.
+hipError_t launch_grad_reduce(dlx_plan* p, const dlx_plan* o, const float* Z, const float* Bm, double* gz,
+                              double* gmap, double* gsrc, double* loss, int loss_chunks, double* gK, hipStream_t st) {
   const long long npix = (long long)p->Ni * p->Ni;
   const int G = p->b4_groups_max * p->b4_ksplit;
   hipLaunchKernelGGL(gopd_reduce_kernel, dim3((unsigned)((npix + 255) / 256)), dim3(256), 0, st, p->d_gpart, G, npix,
@@ -1187,14 +1188,15 @@ hipError_t launch_grad_reduce(dlx_plan* p, const float* Z, const float* Bm, doub
     hipLaunchKernelGGL(map_grad2_kernel, dim3(p->Nmap), dim3(64 * kMapWaves), 0, st, p->d_tmp2, Bm, p->Ni, p->Nmap,
                        gmap);
   }
-  const int FS = p->F * p->S;
-  const int Q2 = p->Q * p->Q;
+  const int FS = o->F * o->S;
+  const int Q2 = o->Q * o->Q;
   // one kernel per pixel: launch_kgrad already wrote gK in full
-  if (p->k_per_pixel) gK = nullptr;
+  if (o->k_per_pixel) gK = nullptr;
+  const double* pos = o->tab ? o->ta.pos : p->d_pos;
+  const int pos_tiles = o->tab ? o->ta.slots : p->tiles_b4 * p->b4_ksplit, pos_l = o->tab ? 1 : p->L;
   hipLaunchKernelGGL(finalize_kernel, dim3(p->Nz + FS + (loss ? 1 : 0) + (gK ? Q2 : 0)), dim3(256), 0, st,
-                     p->d_zpart, p->Nz, nch, gz, p->d_flux, p->flux_blocks, p->d_pos, p->tiles_b4 * p->b4_ksplit, p->L,
-                     FS, gsrc, p->d_lossblk, p->lossblk_chunk * loss_chunks, loss, p->d_kpart, p->F * p->seed_blocks, Q2,
-                     gK);
+                     p->d_zpart, p->Nz, nch, gz, o->d_flux, o->flux_blocks, pos, pos_tiles, pos_l, FS, gsrc,
+                     o->d_lossblk, o->lossblk_chunk * loss_chunks, loss, o->d_kpart, o->F * o->seed_blocks, Q2, gK);
   return hipGetLastError();
 }
 

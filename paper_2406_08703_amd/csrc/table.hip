@@ -1,0 +1,619 @@
+// The shared PSF table (see TableArgs): every star's image interpolated from one polychromatic image,
+// and the transpose for the gradient. The products are banded: a block of 16 x 16 focal samples reads a
+// K x K window of the table through two [16][K] weight matrices, the same for every block of the star, so
+// both directions run as chained FP64 matrix instructions (v_mfma_f64_16x16x4_f64, whose output register
+// r of lane group g holds row 4 r + g: an output is the next product's operand as it lies in registers).
+//
+// The interpolation is FP64 because it is linear in the intensity: a faint sample next to a star's core
+// is a sum of terms as large as the core times the weights, and FP32 products would leave 1e-8 of the
+// core there, where the FP32 fields squared leave 1e-8 sqrt(core x sample).
+#include <algorithm>
+#include <cmath>
+
+#include "dlx_internal.h"
+
+namespace dlx {
+namespace {
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ d4 mfma_f64(double a, double b, d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ int iclamp(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
+
+__device__ __forceinline__ int floor_div(int a, int b) { return (a >= 0 ? a : a - b + 1) / b; }
+
+// The window of the interpolation kernel at distance t (table samples), zero from W / 2 on.
+__device__ __forceinline__ double window(double t, int W, double beta) {
+  const double z = 2.0 * t / (double)W;
+  const double s = 1.0 - z * z;
+  return s > 0.0 ? exp(beta * (sqrt(s) - 1.0)) : (s <= 0.0 ? 0.0 : s);   // NaN stays NaN
+}
+
+__device__ __forceinline__ double kernel_weight(double t, int W, double beta) {
+  const double w = window(t, W, beta);
+  if (t == 0.0) return w;
+  return w * sinpi(t) / (3.14159265358979323846 * t);
+}
+
+// First table sample of block 0 for a star at offset `pos`, and focal sample 0's distance from it. A
+// position that is not finite gets the axis' window and NaN weights.
+__device__ __forceinline__ double star_origin(const TableArgs& t, double pos, int& base) {
+  const double x = t.c0 - pos / t.tau;
+  const double b = ceil(x - 0.5 * (double)t.W);
+  const bool ok = fabs(b) < 1e9;
+  base = ok ? (int)b : (int)ceil(t.c0 - 0.5 * (double)t.W);
+  return ok ? x - b : x - x;
+}
+
+// A tilt beyond half a cycle per pupil sample at some wavelength, reduced by that wavelength's period
+// lambda / dx (the field of the sampled pupil repeats with it).
+__device__ __forceinline__ double reduced(const TableArgs& t, double pos, int l) {
+  const double per = t.wl[l].lam / t.dx;
+  return pos - rint(pos / per) * per;
+}
+
+// wt[fs][axis][a][q] = phi(distance of focal sample 16 b + a from table sample h16 b + base + q), any b.
+// Block 0 sets range[0], the first table row in use: the largest offset of a star, half the focal grid,
+// and W samples on either side (half for the interpolation, half for the derivative's stencil).
+__global__ __launch_bounds__(256) void table_weights_kernel(const TableArgs t, const float* sources) {
+  if (blockIdx.x == 0) {
+    __shared__ double sm[4];
+    __shared__ int sf[4];
+    double m = 0.0;
+    int any = 0;
+    for (int fs = threadIdx.x; fs < t.nfs; fs += 256) {
+      const double a = sources[fs * 3], b = sources[fs * 3 + 1];
+      const bool fin = isfinite(a) && isfinite(b);
+      const bool far = fin && (fabs(a) > t.half_min || fabs(b) > t.half_min);
+      t.far[fs] = far;
+      if (far) {
+        any = 1;
+        for (int l = 0; l < t.L; ++l) m = fmax(m, fmax(fabs(reduced(t, a, l)), fabs(reduced(t, b, l))));
+      } else if (fin) {
+        m = fmax(m, fmax(fabs(a), fabs(b)));
+      }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      m = fmax(m, __shfl_xor(m, o, 64));
+      any |= __shfl_xor(any, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+      sm[threadIdx.x >> 6] = m;
+      sf[threadIdx.x >> 6] = any;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      m = fmax(fmax(sm[0], sm[1]), fmax(sm[2], sm[3]));
+      const double half = 0.5 * (double)(t.No - 1) * t.h16 / 16.0 + m / t.tau + t.W + 4.0;
+      const double lo = floor((0.5 * t.Nt - half) / 32.0) * 32.0;
+      t.range[0] = lo > 0.0 ? (int)lo : 0;
+      t.range[1] = sf[0] | sf[1] | sf[2] | sf[3];
+    }
+    return;
+  }
+  const int i = blockIdx.x - 1, fs = i >> 1, axis = i & 1;
+  int base;
+  const double f = star_origin(t, sources[fs * 3 + axis], base);
+  if (threadIdx.x == 0) t.base[i] = base;
+  double* w = t.wt + (long long)i * 16 * t.K;
+  for (int e = threadIdx.x; e < 16 * t.K; e += 256) {
+    const int a = e / t.K, q = e - a * t.K;
+    w[e] = kernel_weight(f + (double)(a * t.h16) / 16.0 - (double)q, t.W, t.beta);
+  }
+}
+
+// w_l |E_l|^2 of one table sample, FP64
+__device__ __forceinline__ double power(float er, float ei) {
+  return fma((double)er, (double)er, (double)ei * (double)ei);
+}
+
+// I = sum_l w_l |E_l|^2 on the rows and columns in use, four columns per thread. HBM- or L2-bound: every
+// field of the table is read once.
+__global__ __launch_bounds__(256) void table_image_kernel(const TableArgs t) {
+  const int lo = t.range[0], n = t.Nt - 2 * lo, nq = n / 4;
+  const long long total = (long long)n * nq;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+    const int r = (int)(i / nq), c = (int)(i - (long long)r * nq);
+    const long long o = (long long)(lo + r) * t.Nt + lo + 4 * c;
+    const float* e = t.E + o;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int l = 0; l < t.L; ++l) {
+      const f4 er = *reinterpret_cast<const f4*>(e + l * t.e_by_wl);
+      const f4 ei = *reinterpret_cast<const f4*>(e + l * t.e_by_wl + t.e_plane);
+      const double w = (double)t.wl[l].w;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[k] = fma(w, power(er[k], ei[k]), acc[k]);
+    }
+    *reinterpret_cast<d2*>(t.I + o) = d2{acc[0], acc[1]};
+    *reinterpret_cast<d2*>(t.I + o + 2) = d2{acc[2], acc[3]};
+  }
+}
+
+// Derivatives of the table image at its own samples, Ix[j] = sum_n phi'(n) I[j - n] and likewise along y
+// (phi'(n) = (-1)^n / n times the window: the interpolation kernel's derivative at whole distances).
+// Samples outside the range in use count as the edge's: only nodes no star's samples touch see them.
+constexpr int kMaxHalfTaps = 48;
+
+template <class F>
+__device__ __forceinline__ void stencil(const double* cf, int nh, int r, int c, int lo, int hi, F at, double& dx,
+                                        double& dy) {
+  dx = dy = 0.0;
+  for (int n = 1; n <= nh; ++n) {
+    const int cm = iclamp(c - n, lo, hi), cp = iclamp(c + n, lo, hi);
+    const int rm = iclamp(r - n, lo, hi), rp = iclamp(r + n, lo, hi);
+    dx = fma(cf[n], at(r, cm) - at(r, cp), dx);
+    dy = fma(cf[n], at(rm, c) - at(rp, c), dy);
+  }
+}
+
+__device__ __forceinline__ void stencil_weights(double* cf, const TableArgs& t) {
+  for (int n = threadIdx.x + 1; n <= t.W / 2; n += blockDim.x)
+    cf[n] = ((n & 1) ? -1.0 : 1.0) / (double)n * window((double)n, t.W, t.beta);
+}
+
+__global__ __launch_bounds__(256) void table_slope_kernel(const TableArgs t) {
+  __shared__ double cf[kMaxHalfTaps + 1];
+  stencil_weights(cf, t);
+  __syncthreads();
+  const int lo = t.range[0], n = t.Nt - 2 * lo, hi = t.Nt - lo - 1;
+  const long long total = (long long)n * n;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+    const int r = lo + (int)(i / n), c = lo + (int)(i % n);
+    double dx, dy;
+    stencil(cf, t.W / 2, r, c, lo, hi, [&](int y, int x) { return t.I[(long long)y * t.Nt + x]; }, dx, dy);
+    t.Ix[(long long)r * t.Nt + c] = dx;
+    t.Iy[(long long)r * t.Nt + c] = dy;
+  }
+}
+
+// LDS copies of a star's weights: rows of the padded length, zeros around them, so that a shifted window
+// reads zeros where it leaves the K samples.
+constexpr int kPadL = 16;
+__host__ __device__ inline int wrow(int K) { return K + kPadL + 18; }
+
+__device__ __forceinline__ void load_weights(const TableArgs& t, int fs, double* wx, double* wy) {
+  const int KS = wrow(t.K);
+  const double* gx = t.wt + (long long)fs * 2 * 16 * t.K;
+  for (int e = threadIdx.x; e < 16 * KS; e += 256) {
+    const int a = e / KS, q = e - a * KS - kPadL;
+    const bool in = q >= 0 && q < t.K;
+    wx[e] = in ? gx[a * t.K + q] : 0.0;
+    wy[e] = in ? gx[(16 + a) * t.K + q] : 0.0;
+  }
+}
+
+// the same for one wavelength of a star whose tilt is reduced per wavelength
+__device__ __forceinline__ void far_weights(const TableArgs& t, const float* src, int l, double* wx, double* wy,
+                                            int& jx, int& jy) {
+  const int KS = wrow(t.K);
+  const double fx = star_origin(t, reduced(t, src[0], l), jx), fy = star_origin(t, reduced(t, src[1], l), jy);
+  for (int e = threadIdx.x; e < 16 * KS; e += 256) {
+    const int a = e / KS, q = e - a * KS - kPadL;
+    const bool in = q >= 0 && q < t.K;
+    const double s = (double)(a * t.h16) / 16.0 - (double)q;
+    wx[e] = in ? kernel_weight(fx + s, t.W, t.beta) : 0.0;
+    wy[e] = in ? kernel_weight(fy + s, t.W, t.beta) : 0.0;
+  }
+}
+
+// Star images on the focal grid, plane[f][s][k] = I(u_k - position), FP64 products of the table rounded
+// to FP32 at the end. A wave forms 16 columns x 64 rows: for each 16 table rows its window touches, the
+// product with the column weights (K / 4 instructions), whose output feeds the products with the row
+// weights of the four blocks below each other. Bound by the FP64 matrix rate.
+__global__ __launch_bounds__(256) void table_shift_kernel(const TableArgs t, const float* sources, int fs0) {
+  extern __shared__ double sh[];
+  const int KS = wrow(t.K);
+  double *wx = sh, *wy = sh + 16 * KS;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
+  const int fs = fs0 + blockIdx.z;
+  const int lo = t.range[0], hi = t.Nt - lo - 1;
+  const int xb = blockIdx.x * 4 + wave, yb0 = blockIdx.y * 4;
+  const int ny = t.nb - yb0 < 4 ? t.nb - yb0 : 4;
+  d4 acc[4];
+#pragma unroll
+  for (int y = 0; y < 4; ++y) acc[y] = d4{0.0, 0.0, 0.0, 0.0};
+
+  auto add = [&](auto pair, int jx, int jy) {
+    const int cx = jx + t.h16 * xb, ry = jy + t.h16 * yb0;
+    const int rbs = (t.h16 * (ny - 1) + t.K + 15) / 16;
+    for (int rb = 0; rb < rbs; ++rb) {
+      const int row = iclamp(ry + 16 * rb + n, lo, hi);
+      d4 d = d4{0.0, 0.0, 0.0, 0.0};
+      for (int p = 0; p < t.K; p += 8) {
+        const d2 v = pair(row, iclamp(cx + p + 2 * g, lo, hi - 1));
+        const d2 w = *reinterpret_cast<const d2*>(&wx[n * KS + kPadL + p + 2 * g]);
+        d = mfma_f64(v[0], w[0], d);
+        d = mfma_f64(v[1], w[1], d);
+      }
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        const int rel = 16 * rb - t.h16 * y;
+        if (y < ny && rel > -16 && rel < t.K) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[y] = mfma_f64(wy[n * KS + kPadL + rel + 4 * r + g], d[r], acc[y]);
+        }
+      }
+    }
+  };
+
+  if (!t.far[fs]) {
+    load_weights(t, fs, wx, wy);
+    __syncthreads();
+    if (xb < t.nb)
+      add([&](int r, int c) {
+        d2 v;
+        __builtin_memcpy(&v, t.I + (long long)r * t.Nt + c, sizeof v);
+        return v;
+      }, t.base[2 * fs], t.base[2 * fs + 1]);
+  } else {
+    for (int l = 0; l < t.L; ++l) {
+      int jx, jy;
+      __syncthreads();
+      far_weights(t, sources + fs * 3, l, wx, wy, jx, jy);
+      __syncthreads();
+      const float* e = t.E + l * t.e_by_wl;
+      const double w = (double)t.wl[l].w;
+      if (xb < t.nb)
+        add([&](int r, int c) {
+          const float* q = e + (long long)r * t.Nt + c;
+          return d2{w * power(q[0], q[t.e_plane]), w * power(q[1], q[t.e_plane + 1])};
+        }, jx, jy);
+    }
+  }
+  float* o = t.planes + (long long)blockIdx.z * t.No * t.ldg;
+  const int x = 16 * xb + n;
+  if (x < t.No) {
+#pragma unroll
+    for (int y = 0; y < 4; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int yy = 16 * (yb0 + y) + 4 * r + g;
+        if (y < ny && yy < t.No) o[(long long)yy * t.ldg + x] = (float)acc[y][r];
+      }
+  }
+}
+
+// Binning of the star images (Section 3): per star bs = sum K I over a detector pixel, FP64, and
+// binned = sum_s phi_s bs, model = flat binned. One pixel of one frame per thread.
+__global__ __launch_bounds__(256) void table_bin_kernel(const TableArgs t, int Qn, int Nd, int f0, const float* sources,
+                                                        const float* intrapixel, long long kst, const float* flat,
+                                                        float* bs, float* binned, float* model) {
+  const long long npix = (long long)Nd * Nd;
+  const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (p >= npix) return;
+  const int fl = blockIdx.y, f = f0 + fl;
+  const int pr = (int)(p / Nd), pc = (int)(p - (long long)pr * Nd);
+  const float* kp = intrapixel ? intrapixel + p * kst : nullptr;
+  double total = 0.0;
+  for (int s = 0; s < t.S; ++s) {
+    const float* e = t.planes + ((long long)fl * t.S + s) * t.No * t.ldg + (long long)(Qn * pr) * t.ldg + Qn * pc;
+    double v = 0.0;
+    for (int a = 0; a < Qn; ++a)
+      for (int b = 0; b < Qn; ++b) {
+        const double x = e[(long long)a * t.ldg + b];
+        v = kp ? fma(x, (double)kp[a * Qn + b], v) : v + x;
+      }
+    bs[((long long)fl * t.S + s) * npix + p] = (float)v;
+    total = fma((double)sources[((long long)f * t.S + s) * 3 + 2], v, total);
+  }
+  const float bv = (float)total;
+  if (binned) binned[(long long)f * npix + p] = bv;
+  if (model) model[(long long)f * npix + p] = flat[p] * bv;
+}
+
+// The transpose: the seed weights G of frames [f0, f0 + nf) spread onto the table,
+//   D_fs[j] = sum_k phi(t_k - j) G_f[k],   H += phi_s D_fs,
+// and the position gradient -phi_s / tau sum_j D_fs[j] I'[j] (the derivative field is interpolated with
+// the same weights). A wave owns 32 x 32 table samples and runs every star of its group: for each 16 focal
+// columns, the rows of G that reach its rows (A = G transposed, B = row weights), then the product with
+// the column weights. FAR: the stars reduced per wavelength, one wavelength after the other, each into
+// that wavelength's own plane of H (table_seed_kernel adds the common one).
+template <bool FAR>
+__global__ __launch_bounds__(256) void table_adjoint_kernel(const TableArgs t, const float* sources, int f0, int nf,
+                                                            int first) {
+  extern __shared__ double sh[];
+  __shared__ double cf[kMaxHalfTaps + 1];
+  if (FAR && !t.range[1]) return;
+  const int KS = wrow(t.K);
+  double *wx = sh, *wy = sh + 16 * KS;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
+  const int lo = t.range[0], hi = t.Nt - lo - 1;
+  const int nt = (t.Nt - 2 * lo) / 32, ntile = nt * nt;
+  const int slot = blockIdx.x * 4 + wave;
+  int fs_begin = f0 * t.S, fs_end = (f0 + nf) * t.S;
+  if (!FAR) {
+    fs_begin += blockIdx.y * t.per_group;
+    fs_end = min(fs_end, fs_begin + t.per_group);
+    // this wave's partials of every star start at zero (a far star's are added to by the far pass)
+    for (int i = 2 * fs_begin + lane; i < 2 * fs_end; i += 64)
+      t.pos[((long long)(i >> 1) * t.slots + slot) * 2 + (i & 1)] = 0.0;
+  } else {
+    stencil_weights(cf, t);
+  }
+  for (int l = 0; l < (FAR ? t.L : 1); ++l) {
+    for (int t0 = blockIdx.x * 4; t0 < ntile; t0 += gridDim.x * 4) {
+      const bool live = t0 + wave < ntile;
+      const int tile = live ? t0 + wave : 0;
+      const int R0 = lo + 32 * (tile / nt), C0 = lo + 32 * (tile % nt);
+      d4 H[2][2], gx[2][2], gy[2][2];
+      if (FAR) __syncthreads();   // the stencil's weights
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          H[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = R0 + 16 * i + 4 * r + g, col = C0 + 16 * j + n;
+            const long long o = (long long)row * t.Nt + col;
+            if constexpr (!FAR) {
+              gx[i][j][r] = t.Ix[o];
+              gy[i][j][r] = t.Iy[o];
+            } else {
+              const float* e = t.E + l * t.e_by_wl;
+              const double w = (double)t.wl[l].w;
+              double dx, dy;
+              stencil(cf, t.W / 2, row, col, lo, hi, [&](int y, int x) {
+                const long long q = (long long)y * t.Nt + x;
+                return w * power(e[q], e[q + t.e_plane]);
+              }, dx, dy);
+              gx[i][j][r] = dx;
+              gy[i][j][r] = dy;
+            }
+          }
+        }
+      for (int fs = fs_begin; fs < fs_end; ++fs) {
+        if ((t.far[fs] != 0) != FAR) continue;
+        int jx = t.base[2 * fs], jy = t.base[2 * fs + 1];
+        __syncthreads();
+        if constexpr (FAR)
+          far_weights(t, sources + fs * 3, l, wx, wy, jx, jy);
+        else
+          load_weights(t, fs, wx, wy);
+        __syncthreads();
+        const float* G = t.G + (long long)(fs / t.S - f0) * t.No * t.ldg;
+        d4 D[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) D[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        const int xb1 = min(t.nb - 1, floor_div(C0 + 31 - jx, t.h16));
+        const int yb1 = min(t.nb - 1, floor_div(R0 + 31 - jy, t.h16));
+        const int yb0 = max(0, floor_div(R0 - t.K - jy, t.h16) + 1);
+        for (int xb = max(0, floor_div(C0 - t.K - jx, t.h16) + 1); live && xb <= xb1; ++xb) {
+          const int x = 16 * xb + n;
+          const float* gc = G + (x < t.No ? x : t.No - 1);
+          d4 V[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+          for (int yb = yb0; yb <= yb1; ++yb) {
+            double v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const int y = 16 * yb + 4 * k + g;
+              const float q = gc[(long long)(y < t.No ? y : t.No - 1) * t.ldg];
+              v[k] = x < t.No && y < t.No ? (double)q : 0.0;
+            }
+            const int rel = R0 - (jy + t.h16 * yb);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              const int ri = rel + 16 * i;
+              if (ri > -16 && ri < t.K) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) V[i] = mfma_f64(v[k], wy[(4 * k + g) * KS + kPadL + ri + n], V[i]);
+              }
+            }
+          }
+          const int rel = C0 - (jx + t.h16 * xb);
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int rj = rel + 16 * j;
+            if (rj > -16 && rj < t.K) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const double w = wx[(4 * r + g) * KS + kPadL + rj + n];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) D[i][j] = mfma_f64(V[i][r], w, D[i][j]);
+              }
+            }
+          }
+        }
+        const double phi = (double)sources[fs * 3 + 2];
+        double px = 0.0, py = 0.0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const double d = phi * D[i][j][r];
+              H[i][j][r] += d;
+              px = fma(d, gx[i][j][r], px);
+              py = fma(d, gy[i][j][r], py);
+            }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+          px += __shfl_xor(px, o, 64);
+          py += __shfl_xor(py, o, 64);
+        }
+        if (lane < 2 && live) {   // the lanes that zeroed these partials
+          double* o = t.pos + ((long long)fs * t.slots + slot) * 2 + lane;
+          *o -= (lane ? py : px) / t.tau;
+        }
+      }
+      if (live) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const long long o = (long long)(R0 + 16 * i + 4 * r + g) * t.Nt + C0 + 16 * j + n;
+              if constexpr (FAR) {
+                float* h = t.H + (1 + l) * (long long)t.Nt * t.Nt;
+                h[o] = (float)((first ? 0.0 : (double)h[o]) + H[i][j][r]);
+              } else {
+                double* h = t.Hpart + blockIdx.y * (long long)t.Nt * t.Nt;
+                h[o] = (first ? 0.0 : h[o]) + H[i][j][r];
+              }
+            }
+      }
+    }
+  }
+}
+
+// H = sum of the groups' planes, FP32, on the samples in use; with far stars, added to every
+// wavelength's own plane
+__global__ __launch_bounds__(256) void table_seed_kernel(const TableArgs t) {
+  const int lo = t.range[0], n = t.Nt - 2 * lo;
+  const long long total = (long long)n * n, plane = (long long)t.Nt * t.Nt;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+    const long long o = (long long)(lo + i / n) * t.Nt + lo + i % n;
+    double v = 0.0;
+    for (int k = 0; k < t.groups; ++k) v += t.Hpart[k * plane + o];
+    t.H[o] = (float)v;
+    if (t.range[1])
+      for (int l = 0; l < t.L; ++l) t.H[(1 + l) * plane + o] = (float)((double)t.H[(1 + l) * plane + o] + v);
+  }
+}
+
+// dL/dK from the star images (see kgrad_kernel): v[a][b] = h sum_s phi_s I_s at the pixel's samples.
+template <int QT>
+__global__ __launch_bounds__(256) void table_kgrad_kernel(const TableArgs t, int Nd, int f0, int nf,
+                                                          const float* sources, const float* flat, const float* resid,
+                                                          const int* win, int F_img, int Nd_img, double* part,
+                                                          double* gpix, int first) {
+  constexpr int Q2 = QT * QT;
+  __shared__ double sh[Q2][4];
+  const long long npix = (long long)Nd * Nd;
+  const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
+  double acc[Q2];
+#pragma unroll
+  for (int k = 0; k < Q2; ++k) acc[k] = 0.0;
+  const int fl0 = gpix ? 0 : blockIdx.y, fl1 = gpix ? nf : blockIdx.y + 1;
+  for (int fl = fl0; fl < fl1 && p < npix; ++fl) {
+    const int f = f0 + fl;
+    const int pr = (int)(p / Nd), pc = (int)(p - (long long)pr * Nd);
+    float h = 0.f;
+    if (win) {
+      const long long nimg = (long long)Nd_img * Nd_img;
+      for (int q = 0; q < F_img; ++q) {
+        const int ir = pr - win[2 * q], ic = pc - win[2 * q + 1];
+        if (ir >= 0 && ir < Nd_img && ic >= 0 && ic < Nd_img) {
+          const long long i = (long long)ir * Nd_img + ic;
+          h += flat[i] * resid[(long long)q * nimg + i];
+        }
+      }
+    } else {
+      h = flat[p] * resid[(long long)f * npix + p];
+    }
+    for (int s = 0; s < t.S; ++s) {
+      const float* e = t.planes + ((long long)fl * t.S + s) * t.No * t.ldg + (long long)(QT * pr) * t.ldg + QT * pc;
+      const double w = (double)sources[((long long)f * t.S + s) * 3 + 2] * (double)h;
+#pragma unroll
+      for (int a = 0; a < QT; ++a)
+#pragma unroll
+        for (int b = 0; b < QT; ++b) acc[a * QT + b] = fma(w, (double)e[(long long)a * t.ldg + b], acc[a * QT + b]);
+    }
+  }
+  if (gpix) {
+    if (p < npix) {
+#pragma unroll
+      for (int k = 0; k < Q2; ++k) gpix[p * Q2 + k] = (first ? 0.0 : gpix[p * Q2 + k]) + acc[k];
+    }
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < Q2; ++k) {
+    double v = acc[k];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < Q2) {
+    double v = 0.0;
+    for (int w = 0; w < 4; ++w) v += sh[threadIdx.x][w];
+    part[((long long)(f0 + blockIdx.y) * gridDim.x + blockIdx.x) * Q2 + threadIdx.x] = v;
+  }
+}
+
+unsigned blocks(long long n, int per, unsigned most) {
+  return (unsigned)std::max<long long>(1, std::min<long long>((n + per - 1) / per, most));
+}
+
+}  // namespace
+
+hipError_t launch_table_weights(const TableArgs& t, const float* sources, hipStream_t st) {
+  hipLaunchKernelGGL(table_weights_kernel, dim3(1 + 2 * t.nfs), dim3(256), 0, st, t, sources);
+  return hipGetLastError();
+}
+
+// The polychromatic table image and, for the gradient, its derivatives. n_reg: samples per side the grids
+// are sized for (the kernels stride over any more).
+hipError_t launch_table_image(const TableArgs& t, int n_reg, bool derivatives, hipStream_t st) {
+  const long long n = (long long)n_reg * n_reg;
+  if (!derivatives)
+    hipLaunchKernelGGL(table_image_kernel, dim3(blocks(n / 4, 256, 1u << 20)), dim3(256), 0, st, t);
+  else
+    hipLaunchKernelGGL(table_slope_kernel, dim3(blocks(n, 256, 1u << 20)), dim3(256), 0, st, t);
+  return hipGetLastError();
+}
+
+hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, int nf, hipStream_t st) {
+  const unsigned nb4 = (t.nb + 3) / 4;
+  hipLaunchKernelGGL(table_shift_kernel, dim3(nb4, nb4, nf * t.S), dim3(256), 2 * 16 * wrow(t.K) * sizeof(double), st,
+                     t, sources, f0 * t.S);
+  return hipGetLastError();
+}
+
+hipError_t launch_table_bin(const TableArgs& t, int Q, int Nd, int f0, int nf, const float* sources,
+                            const float* intrapixel, long long kst, const float* flat, float* bs, float* binned,
+                            float* model, hipStream_t st) {
+  hipLaunchKernelGGL(table_bin_kernel, dim3(blocks((long long)Nd * Nd, 256, 1u << 30), nf), dim3(256), 0, st, t, Q, Nd,
+                     f0, sources, intrapixel, kst, flat, bs, binned, model);
+  return hipGetLastError();
+}
+
+// Seed weights of frames [f0, f0 + nf) onto the groups' planes (`first`: overwriting them), and those of
+// far stars onto the wavelengths' planes (which leaves at once when there are none).
+hipError_t launch_table_adjoint(const TableArgs& t, const float* sources, int f0, int nf, bool first,
+                                hipStream_t st) {
+  const size_t lds = 2 * 16 * wrow(t.K) * sizeof(double);
+  hipLaunchKernelGGL(table_adjoint_kernel<false>, dim3(t.slots / 4, t.groups), dim3(256), lds, st, t, sources, f0, nf,
+                     first ? 1 : 0);
+  hipLaunchKernelGGL(table_adjoint_kernel<true>, dim3(t.slots / 4), dim3(256), lds, st, t, sources, f0, nf,
+                     first ? 1 : 0);
+  return hipGetLastError();
+}
+
+// The table's seed weights, once every frame is in the groups' planes.
+hipError_t launch_table_seed(const TableArgs& t, int n_reg, hipStream_t st) {
+  hipLaunchKernelGGL(table_seed_kernel, dim3(blocks((long long)n_reg * n_reg, 256, 1u << 20)), dim3(256), 0, st, t);
+  return hipGetLastError();
+}
+
+hipError_t launch_table_kgrad(const TableArgs& t, int Q, int Nd, int f0, int nf, const float* sources,
+                              const float* flat, const float* resid, const int* win, int F_img, int Nd_img,
+                              double* part, double* gpix, bool first, hipStream_t st) {
+  const dim3 grid(blocks((long long)Nd * Nd, 256, 1u << 30), gpix ? 1 : nf), blk(256);
+#define DLX_TKGRAD(QT)                                                                                             \
+  hipLaunchKernelGGL(table_kgrad_kernel<QT>, grid, blk, 0, st, t, Nd, f0, nf, sources, flat, resid, win, F_img, \
+                     Nd_img, part, gpix, first ? 1 : 0)
+  switch (Q) {
+    case 1: DLX_TKGRAD(1); break;
+    case 2: DLX_TKGRAD(2); break;
+    case 3: DLX_TKGRAD(3); break;
+    case 4: DLX_TKGRAD(4); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef DLX_TKGRAD
+  return hipGetLastError();
+}
+
+}  // namespace dlx

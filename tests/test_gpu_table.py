@@ -1,0 +1,208 @@
+"""Plans on a shared PSF table: many stars and frames whose images are one polychromatic image, shifted.
+
+Sizes are chosen so that the plan takes the table (checked: its transforms count one per wavelength)
+while the FP64 oracle stays affordable: odd pupils and detectors, focal grids that are no multiple of
+the interpolation's blocks, every oversampling, integer dithers, a phase map, one kernel per pixel. The
+tolerances are those of the per-star transforms. Stars whose tilt exceeds half a cycle per pupil
+sample (reduced by each wavelength's own period), frames in several chunks and a position that is
+not finite are checked against the same plan's per-star form.
+"""
+import dataclasses
+import functools
+
+import numpy as np
+import pytest
+
+import oracle as O
+from synth import make_dithered_workload, make_workload
+from tests.helpers import oracle_problem, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # Q = 3, odd pupil, focal grid 93 = 5 x 16 + 13, intra-pixel kernel
+    "q3-odd": ("c3", dict(n_pupil=97, n_focal=93, n_wavelengths=32, n_frames=30, noll=tuple(range(2, 12)))),
+    # Q = 4 and Q = 2 with a phase map
+    "q4": ("c3", dict(n_pupil=80, n_focal=160, oversample=4, n_wavelengths=24, n_frames=24, noll=tuple(range(2, 9)))),
+    "q2-map": ("c5", dict(n_pupil=100, n_focal=136, n_wavelengths=24, n_frames=48, noll=tuple(range(2, 12)), n_map=8)),
+}
+
+
+@functools.lru_cache(maxsize=None)
+def workload(case):
+    name, ov = CASES[case]
+    w = make_workload(name, **ov)
+    prob = oracle_problem(w)
+    return w.with_data(O.forward(prob, w.coeffs_true, w.map_true, w.sources_true, w.flat_true)[1]), prob
+
+
+@functools.lru_cache(maxsize=None)
+def reference(case, kind):
+    w, prob = workload(case)
+    p = w.eval_params()
+    return O.value_and_grad(prob, p["coeffs"], p["phase_map"], p["sources"], p["flat"], w.data, kind, w.prior_mu,
+                            w.prior_sigma)
+
+
+def transforms(plan, fn):
+    """Forward transforms that the calls of fn() ran."""
+    from paper_2406_08703_amd import dlx as C
+    C.dlx_plan_profile(plan.plan, True)
+    out = fn()
+    n = C.dlx_plan_stage_times(plan.plan)["F1"][2]
+    C.dlx_plan_profile(plan.plan, False)
+    return n, out
+
+
+@pytest.mark.parametrize("fused,kind", [(True, "poisson"), (False, "chi2")])
+@pytest.mark.parametrize("case", list(CASES))
+def test_table_matches_oracle(case, fused, kind):
+    from tests.gpu_helpers import make_plan, run_eval, run_gpu
+    from tests.test_gpu_parity import compare
+    print(f"table {case} fused={fused} {kind}", flush=True)
+    w, _ = workload(case)
+    plan = make_plan(w)
+    n, got = transforms(plan, lambda: (run_eval if fused else run_gpu)(w, kind=kind, plan=plan))
+    plan.close()
+    assert n == (1 if fused else 2) * len(w.problem.wavelengths)   # the separate calls recompute the fields
+    assert got["status"] == 0
+    compare(got, reference(case, kind), q=w.problem.oversample, kind=kind)
+
+
+def test_table_graph_replays_and_stored_fields_give_the_same_bits():
+    import torch
+    from paper_2406_08703_amd import CapturedEval, PsfPlan
+    from tests.gpu_helpers import dev, geometry, make_plan, run_eval, run_gpu
+    print("table graph and stored fields", flush=True)
+    w, _ = workload("q3-odd")
+    p = w.eval_params()
+    plan = make_plan(w)
+    eager, sep = run_eval(w, plan=plan), run_gpu(w, plan=plan)
+    cap = CapturedEval(plan, dev(p["coeffs"]), None, dev(p["sources"]), dev(p["flat"]), dev(w.data), "poisson",
+                       w.prior_mu, w.prior_sigma)
+    for _ in range(3):
+        o = cap.replay()
+        torch.cuda.synchronize()
+        for k, v in (("model", o.model), ("r", o.r), ("grad_flat", o.grad_flat), ("grad_sources", o.grad_sources),
+                     ("grad_coeffs", o.grad_zernike[:w.problem.n_zernike])):
+            np.testing.assert_array_equal(v.cpu().numpy(), eager[k])
+        run_gpu(w, plan=plan)   # other work on the plan between replays
+    plan.close()
+    stored = PsfPlan(geometry(w), dev(w.transmission), dev(w.zbasis), None, dev(w.intrapixel), store_fields=True)
+    n, got = transforms(stored, lambda: run_gpu(w, plan=stored))
+    stored.close()
+    assert n == len(w.problem.wavelengths)
+    for k in ("model", "r", "grad_coeffs", "grad_sources"):
+        np.testing.assert_array_equal(got[k], sep[k])
+
+
+@pytest.mark.parametrize("q,nd,pixel", [(1, 150, 8.0), (2, 61, 70.0)])
+def test_table_in_integer_dither_mode_matches_oracle(q, nd, pixel):
+    """One enlarged plane, many stars; Q = 1 pixels far finer than the resolution (few table samples per
+    block), and Q = 2 with an intra-pixel kernel and its gradient."""
+    from paper_2406_08703_amd import evaluate
+    from tests.gpu_helpers import dev
+    from tests.test_gpu_dither import oracle_big, plan_for, run
+    from tests.test_gpu_parity import compare
+    print(f"table dither q={q}", flush=True)
+    w = make_dithered_workload(n_pupil=88, n_det=nd, oversample=q, margin=3, n_sources=24, det_pixel_mas=pixel,
+                               wavelengths=tuple(np.linspace(545e-9, 645e-9, 32)), dithers=((0, 0), (3, -2), (-3, 1)), flux=(1e6, 1e7))
+    if q > 1:
+        w = dataclasses.replace(w, intrapixel=(1.0 + 0.004 * np.arange(q * q).reshape(q, q)).astype(np.float32))
+    big = oracle_big(w)
+    w = w.with_data(O.forward_dithered(big, w.coeffs_true, None, w.sources_true, w.flat_true, w.dithers, w.margin)[1])
+    p = w.eval_params()
+    ref = O.value_and_grad_dithered(big, p["coeffs"], None, p["sources"], p["flat"], w.data, w.dithers, w.margin,
+                                    "poisson", w.prior_mu, w.prior_sigma)
+    plan = plan_for(w)
+    n, got = transforms(plan, lambda: run(w, plan, True))
+    assert n == len(w.problem.wavelengths)
+    compare(got, ref, q=q)
+    if q > 1:
+        want = O.intrapixel_grad_dithered(big, p["coeffs"], None, p["sources"], p["flat"], ref["r"], w.dithers, w.margin)
+        gk = evaluate(plan, dev(p["coeffs"]), None, dev(p["sources"]), dev(p["flat"]), dev(w.data), "poisson",
+                      w.prior_mu, w.prior_sigma, intrapixel_grad=True).grad_intrapixel.cpu().numpy()
+        scale = np.sum(np.abs(np.asarray(p["flat"], np.float64)[None] * ref["r"]) * ref["binned"]) / (q * q)
+        assert np.max(np.abs(gk - want)) / scale < 1e-5
+    plan.close()
+
+
+def test_table_with_one_kernel_per_pixel_matches_oracle():
+    from paper_2406_08703_amd import PsfPlan, evaluate
+    from tests.gpu_helpers import dev, geometry
+    print("table with per-pixel kernels", flush=True)
+    w, _ = workload("q3-odd")
+    P, p = w.problem, w.eval_params()
+    K = (1.0 + 0.02 * np.random.default_rng(3).normal(size=(P.n_det, P.n_det, 3, 3))).astype(np.float32)
+    prob = dataclasses.replace(oracle_problem(w), intrapixel=K.astype(np.float64))
+    B, m = O.forward(prob, p["coeffs"], None, p["sources"], p["flat"])
+    r = O.loss_grad(m, B, w.data, p["flat"], "poisson", w.prior_mu, w.prior_sigma)[1]
+    want = O.intrapixel_grad(prob, p["coeffs"], None, p["sources"], p["flat"], r)
+    plan = PsfPlan(geometry(w), dev(w.transmission), dev(w.zbasis), None, dev(K), pixel_kernel=True)
+    n, o = transforms(plan, lambda: evaluate(plan, dev(p["coeffs"]), None, dev(p["sources"]), dev(p["flat"]),
+                                             dev(w.data), "poisson", w.prior_mu, w.prior_sigma, intrapixel_grad=True))
+    assert plan.sync() == 0 and n == len(P.wavelengths)
+    plan.close()
+    scale = np.max(np.sum(np.abs(r) * B, axis=0)) / 9
+    assert np.max(np.abs(o.model.cpu().numpy() - m)) / np.max(m) < 1e-5
+    assert np.max(np.abs(o.grad_intrapixel.cpu().numpy() - want)) / scale < 1e-5
+
+
+def _against_per_star_form(w, sources, tol):
+    """The plan on its table and the same problem with dense per-star products: every output to tol."""
+    from tests.gpu_helpers import make_plan, run_eval
+    out = []
+    for dense in (False, True):
+        plan = make_plan(w, dense_mft=dense)
+        n, got = transforms(plan, lambda: run_eval(w, params=dict(w.eval_params(), sources=sources), kind="chi2",
+                                                   plan=plan))
+        plan.close()
+        P = w.problem
+        assert n == (P.n_psf if dense else len(P.wavelengths))
+        out.append(got)
+    a, b = out
+    for k in ("binned", "model", "r", "grad_flat", "grad_coeffs", "grad_sources"):
+        assert rel_l2(a[k], b[k]) < tol, (k, rel_l2(a[k], b[k]))
+    return a, b
+
+
+def test_table_with_stars_beyond_the_pupil_grids_field():
+    """Positions from inside the detector to several times lambda / (2 dx), where a tilt repeats with each
+    wavelength's own period: the same images and gradients as the per-star transforms."""
+    print("table far stars", flush=True)
+    w, _ = workload("q4")
+    P = w.problem
+    src = np.array(w.eval_params()["sources"])
+    reach = float(np.min(P.wavelengths)) * P.n_pupil / (2 * P.diameter)
+    src[1, 0, 0] = 0.7 * reach       # far outside the detector, still a regular tilt
+    src[2, 1, 1] = -1.3 * reach      # beyond half a cycle per pupil sample at the shortest wavelength
+    src[5, 0, :2] = (2.6 * reach, -3.1 * reach)
+    src[9, 1, 0] = -2.02 * reach     # its period puts it back near the axis
+    _against_per_star_form(w, src.astype(np.float32), 1e-5)
+
+
+def test_table_with_frames_in_several_chunks():
+    """More stars than one launch takes (65,535): the frames run in two chunks that add to one table."""
+    print("table chunks", flush=True)
+    w = make_workload("c3", n_pupil=32, n_focal=32, oversample=4, n_wavelengths=48, n_frames=33000,
+                      noll=tuple(range(2, 6)))
+    w = dataclasses.replace(w, data=np.full((33000, 8, 8), 1e6, np.float32))
+    _against_per_star_form(w, w.eval_params()["sources"], 1e-5)
+
+
+def test_table_reports_a_position_that_is_not_finite():
+    from tests.gpu_helpers import make_plan, run_eval
+    print("table non-finite position", flush=True)
+    w, _ = workload("q4")
+    src = np.array(w.eval_params()["sources"])
+    src[3, 0, 1] = np.nan
+    plan = make_plan(w)
+    bad = run_eval(w, params=dict(w.eval_params(), sources=src), plan=plan)
+    assert bad["status"] == 5   # DLX_ERR_NONFINITE
+    assert np.all(np.isnan(bad["model"][3])) and np.all(np.isfinite(np.delete(bad["model"], 3, axis=0)))
+    assert np.all(np.isnan(bad["grad_coeffs"])) and np.all(np.isnan(bad["grad_sources"][3, :, :2]))
+    good = run_eval(w, plan=plan)   # nothing of it stays behind
+    plan.close()
+    assert good["status"] == 0
+    from tests.test_gpu_parity import compare
+    compare(good, reference("q4", "poisson"), q=4)
