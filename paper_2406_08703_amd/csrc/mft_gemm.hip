@@ -584,7 +584,16 @@ struct TileRange {
   int k0;                 // first contracted index
 };
 
-template <int KIND, int WM, int WN, int PREC>
+// TAB: the products of a PSF table, whose one star is on the axis: no tilts and no position gradient. Its
+// fields serve every star and frame, so their rounding errors do not average over frames as those of one
+// transform per frame do, and are kept smaller instead: F1's pupil field arrives as the pair sums and
+// differences, rounded once (pupil_body), and F1 contracts from the centre of the pupil outwards, where the
+// partial sums of the wings' oscillating terms stay smaller; F2, which sets the core's error, adds up
+// partial sums of 64 terms. (Image error in the core, 4 frames of 2048^2 samples, 16 wavelengths: 3.8e-8, and
+// 3.7e-7 of the flat-field gradient's norm; 9e-8 and 9e-7 in one running sum, 6.6e-8 and 6.7e-7 with one
+// transform per frame. F2 takes 939 us with the partial sums, whose registers leave two workgroups per CU,
+// 865 us without.)
+template <int KIND, int WM, int WN, int PREC, bool TAB = false>
 __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const float* src, const TileRange tr) {
   constexpr bool DA = KIND != KIND_F2;   // DFT operand on the A side (rows i), data on the B side
   constexpr int BM = 32 * WM, BN = 32 * WN;
@@ -626,6 +635,10 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
   const Operand& OD = DA ? a.A : a.B;
   const Operand& OX = DA ? a.B : a.A;
   const bool conj_d = DA ? a.conj_a : a.conj_b;
+  constexpr bool PAIRS = TAB && KIND == KIND_F1;   // the data operand holds sums and differences
+  constexpr bool REV = TAB && KIND == KIND_F1;     // k from the middle outwards
+  constexpr bool PARTS = TAB && KIND == KIND_F2;   // a sum of partial sums over kPartStages k-stages
+  constexpr int kPartStages = 4;
   const int kmid = a.kodd ? K - 1 : -1;   // the unpaired middle term of an odd contracted length
 
   int p_begin, p_end, grp = 0;
@@ -792,7 +805,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
         xm[r][v] = *reinterpret_cast<const u4*>(pm + 4 * v);
         xm[r][V + v] = *reinterpret_cast<const u4*>(pm + OX.plane + 4 * v);
       }
-      if constexpr (KIND == KIND_F1) {
+      if constexpr (KIND == KIND_F1 && !TAB) {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
           w0[r][v] = *reinterpret_cast<const u4*>(tyl + gkc + 4 * v);
@@ -881,7 +894,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
           // the mirror of natural element 4v + e is element 3 - e of mirror vector V - 1 - v
           f4 yr = rev4(__builtin_bit_cast(f4, xm[r][V - 1 - v]));
           f4 yi = rev4(__builtin_bit_cast(f4, xm[r][2 * V - 1 - v]));
-          if constexpr (KIND == KIND_F1) {
+          if constexpr (KIND == KIND_F1 && !TAB) {
             // P[k] = P0[k] ty[k]; at the mirror row the tilt is conj(ty[k])
             const f4 tr = __builtin_bit_cast(f4, w0[r][v]), ti = __builtin_bit_cast(f4, w1[r][v]);
             const f4 ar = xr * tr - xi * ti, ai = xr * ti + xi * tr;
@@ -915,10 +928,10 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
               }
             }
           }
-          er[v] = xr + yr;
-          ei[v] = xi + yi;
-          odr[v] = xr - yr;
-          odi[v] = xi - yi;
+          er[v] = PAIRS ? xr : xr + yr;
+          ei[v] = PAIRS ? xi : xi + yi;
+          odr[v] = PAIRS ? yr : xr - yr;
+          odi[v] = PAIRS ? yi : xi - yi;
         }
         if constexpr (PREC == 0) {
           const int o = 4 * (kq ^ lds_swz(row));
@@ -960,7 +973,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
       constexpr int NMF = WM * WN * 16;
       constexpr int NDSR = 2 * WD + 4 * WX;
       constexpr int NDSW = 2 * D_U + 4 * X_U;
-      constexpr int NVM = 2 * D_U + (KIND == KIND_F1 || KIND == KIND_B3 ? 6 : 4) * X_U;
+      constexpr int NVM = 2 * D_U + ((KIND == KIND_F1 && !TAB) || KIND == KIND_B3 ? 6 : 4) * X_U;
       // B3 (the loader with the most VALU work) starts its store after two MFMAs
       constexpr int Q1 = KIND == KIND_B3 ? 2 : NMF / 4;
       constexpr int Q2 = KIND == KIND_B3 ? NMF * 3 / 4 - 2 : NMF / 2;
@@ -1142,28 +1155,89 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
       // is told to spread it, and the loads, between the MFMAs, so the pair sums and the LDS and
       // global traffic issue while the matrix pipe is busy. (One workgroup runs one PSF here.)
       set_loader(it);
-      load_tile_c(k_lo);
-      if (nfull > 0)
-        store_tile(smem, std::false_type{});
-      else
+      if constexpr (REV) {   // the same pipeline from the last tile to the first: the partial ones come first
+        auto at = [&](int t) { return k_lo + max(nk - 1 - t, 0) * BK; };
+        load_tile_c(at(0));
         store_tile(smem, std::true_type{});
-      load_tile_c(k_lo + BK);
-      __syncthreads();
-      int kt = 0;
-      for (; kt + 1 < nfull; ++kt) {   // the next tile is full: one basic block per stage
-        mma(smem + (kt & 1) * BUF_EL);
-        store_tile(smem + ((kt + 1) & 1) * BUF_EL, std::false_type{});
-        load_tile_c(k_lo + (kt + 2) * BK);
-        pipe_schedule();
+        load_tile_c(at(1));
         __syncthreads();
-      }
-      for (; kt < nk; ++kt) {   // the last one or two stages
-        mma(smem + (kt & 1) * BUF_EL);
-        if (kt + 1 < nk) {
+        int kt = 0;
+        for (; kt + 1 < nk - nfull; ++kt) {
+          mma(smem + (kt & 1) * BUF_EL);
           store_tile(smem + ((kt + 1) & 1) * BUF_EL, std::true_type{});
-          load_tile_c(k_lo + (kt + 2) * BK);
+          load_tile_c(at(kt + 2));
+          __syncthreads();
         }
+        for (; kt + 1 < nk; ++kt) {
+          mma(smem + (kt & 1) * BUF_EL);
+          store_tile(smem + ((kt + 1) & 1) * BUF_EL, std::false_type{});
+          load_tile_c(at(kt + 2));
+          pipe_schedule();
+          __syncthreads();
+        }
+        mma(smem + (kt & 1) * BUF_EL);
+      } else {
+        load_tile_c(k_lo);
+        if (nfull > 0)
+          store_tile(smem, std::false_type{});
+        else
+          store_tile(smem, std::true_type{});
+        load_tile_c(k_lo + BK);
         __syncthreads();
+        f4 tot[PARTS ? WM : 1][PARTS ? WN : 1][4];
+        if constexpr (PARTS) {
+#pragma unroll
+          for (int bm = 0; bm < WM; ++bm)
+#pragma unroll
+            for (int bn = 0; bn < WN; ++bn)
+#pragma unroll
+              for (int c = 0; c < 4; ++c) tot[bm][bn][c] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+        auto move = [&](f4& from, f4& to) {
+          to += from;
+          from = f4{0.f, 0.f, 0.f, 0.f};
+        };
+        auto flush = [&]() {
+#pragma unroll
+          for (int bm = 0; bm < WM; ++bm)
+#pragma unroll
+            for (int bn = 0; bn < WN; ++bn) {
+              move(pr_[bm][bn], tot[bm][bn][0]);
+              move(pi_[bm][bn], tot[bm][bn][1]);
+              move(rr_[bm][bn], tot[bm][bn][2]);
+              move(ri_[bm][bn], tot[bm][bn][3]);
+            }
+        };
+        int kt = 0;
+        for (; kt + 1 < nfull; ++kt) {   // the next tile is full: one basic block per stage
+          mma(smem + (kt & 1) * BUF_EL);
+          store_tile(smem + ((kt + 1) & 1) * BUF_EL, std::false_type{});
+          load_tile_c(k_lo + (kt + 2) * BK);
+          pipe_schedule();
+          __syncthreads();
+          if constexpr (PARTS)
+            if (kt % kPartStages == kPartStages - 1) flush();
+        }
+        for (; kt < nk; ++kt) {   // the last one or two stages
+          mma(smem + (kt & 1) * BUF_EL);
+          if (kt + 1 < nk) {
+            store_tile(smem + ((kt + 1) & 1) * BUF_EL, std::true_type{});
+            load_tile_c(k_lo + (kt + 2) * BK);
+          }
+          __syncthreads();
+        }
+        if constexpr (PARTS) {
+          flush();
+#pragma unroll
+          for (int bm = 0; bm < WM; ++bm)
+#pragma unroll
+            for (int bn = 0; bn < WN; ++bn) {
+              pr_[bm][bn] = tot[bm][bn][0];
+              pi_[bm][bn] = tot[bm][bn][1];
+              rr_[bm][bn] = tot[bm][bn][2];
+              ri_[bm][bn] = tot[bm][bn][3];
+            }
+        }
       }
     } else if (nk > 0) {
       // B4: the same pipeline over a stream of tiles that runs through the workgroup's PSFs and
@@ -1236,7 +1310,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
         for (int bn = 0; bn < WN; ++bn) {
           const int j = col0 + wc * 16 * WN + bn * 16 + (lane & 15);
           float cr = 1.f, ci = 0.f;
-          if constexpr (KIND == KIND_F1) {
+          if constexpr (KIND == KIND_F1 && !TAB) {
             if (j < N) {
               cr = txb[j];
               ci = txb[a.tilt_plane + j];
@@ -1267,7 +1341,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
                 const int im = a.mirror_n - 1 - i;
                 const int jc = j < a.out_h ? j : j + a.out_s;
                 float ar = lr, ai = li, br = hr, bi = hi;
-                if constexpr (KIND == KIND_F1) {   // column tilt tx[n]
+                if constexpr (KIND == KIND_F1 && !TAB) {   // column tilt tx[n]
                   ar = lr * cr - li * ci;
                   ai = lr * ci + li * cr;
                   br = hr * cr - hi * ci;
@@ -1303,13 +1377,29 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
             const f4 qi = *reinterpret_cast<const f4*>(q + a.p0_plane + i0);
             const f4 mr = rev4(*reinterpret_cast<const f4*>(q + (a.ldp - 4 - i0)));
             const f4 mi = rev4(*reinterpret_cast<const f4*>(q + a.p0_plane + (a.ldp - 4 - i0)));
-            const f4 yr = *reinterpret_cast<const f4*>(tyb + i0);
-            const f4 yi = *reinterpret_cast<const f4*>(tyb + a.tilt_plane + i0);
-            const float xr = txb[j], xi = txb[a.tilt_plane + j];
-            const f4 tr = yr * xr - yi * xi, ti = yr * xi + yi * xr;   // ty[m] tx[n]
-            const f4 ur = yr * xr + yi * xi, ui = yr * xi - yi * xr;   // conj(ty[m]) tx[n]
-            const f4 plr = qr * tr - qi * ti, pli = qr * ti + qi * tr;
-            const f4 phr = mr * ur - mi * ui, phi = mr * ui + mi * ur;
+            f4 plr, pli, phr, phi;
+            if constexpr (TAB) {   // the rows from their sum and difference (an unpaired middle row: itself)
+              plr = 0.5f * (qr + mr);
+              pli = 0.5f * (qi + mi);
+              phr = 0.5f * (qr - mr);
+              phi = 0.5f * (qi - mi);
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                if (a.mirror_n - 1 - (i0 + r) == i0 + r) {
+                  plr[r] = qr[r];
+                  pli[r] = qi[r];
+                }
+            } else {
+              const f4 yr = *reinterpret_cast<const f4*>(tyb + i0);
+              const f4 yi = *reinterpret_cast<const f4*>(tyb + a.tilt_plane + i0);
+              const float xr = txb[j], xi = txb[a.tilt_plane + j];
+              const f4 tr = yr * xr - yi * xi, ti = yr * xi + yi * xr;   // ty[m] tx[n]
+              const f4 ur = yr * xr + yi * xi, ui = yr * xi - yi * xr;   // conj(ty[m]) tx[n]
+              plr = qr * tr - qi * ti;
+              pli = qr * ti + qi * tr;
+              phr = mr * ur - mi * ui;
+              phi = mr * ui + mi * ur;
+            }
             const double xj = a.xcoord[j];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -1321,12 +1411,15 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
                 const float gm = im != i ? kp * c * (phr[r] * (Pi - Rr) - phi[r] * (Pr + Ri)) : 0.f;
                 slo[bm][bn][r] += g;
                 shi[bm][bn][r] += gm;
-                px += xj * ((double)g + (double)gm);
-                py += a.xcoord[i] * (double)g + a.xcoord[im] * (double)gm;
+                if constexpr (!TAB) {
+                  px += xj * ((double)g + (double)gm);
+                  py += a.xcoord[i] * (double)g + a.xcoord[im] * (double)gm;
+                }
               }
             }
           }
         }
+      if constexpr (TAB) continue;   // no position gradient: nothing more for this wavelength
       px = wave_sum(px);
       py = wave_sum(py);
       // the PSF's wave sums wait in an LDS slot; they are added (in wave order) and written when
@@ -1384,8 +1477,8 @@ __global__ __launch_bounds__(256, PREC == 0 ? 2 : 1) void fgemm_kernel(const Gem
 // A folded stage on the PSF table: only rows and columns [lo, Nt - lo) are in use, lo = a.range[0] (a
 // multiple of 32) being set on the device by the stars' positions. The tiles in use are enumerated
 // compactly; the grid is sized for stars within the detector and each workgroup strides over the rest.
-template <int KIND, int WM, int WN, int PREC>
-__global__ __launch_bounds__(256, PREC == 0 ? 2 : 1) void fgemm_table_kernel(const GemmArgs a) {
+template <int KIND, int WM, int WN>
+__global__ __launch_bounds__(256, 2) void fgemm_table_kernel(const GemmArgs a) {
   constexpr int BM = 32 * WM, BN = 32 * WN;
   const int lo = a.range[0];
   TileRange tr{0, 0, a.tiles_m, a.tiles_n, 0};
@@ -1406,7 +1499,7 @@ __global__ __launch_bounds__(256, PREC == 0 ? 2 : 1) void fgemm_table_kernel(con
   }
   const int total = tr.tiles_m * tr.tiles_n * a.n_items;
   for (int w = blockIdx.x; w < total; w += gridDim.x) {
-    fgemm_body<KIND, WM, WN, PREC>(a, xcd_remap(w, total), a.sources, tr);
+    fgemm_body<KIND, WM, WN, 0, true>(a, xcd_remap(w, total), a.sources, tr);
     __syncthreads();   // the next tile reuses the LDS buffers
   }
 }
@@ -1436,10 +1529,14 @@ constexpr bool fold_tile_ok(int kind, int prec, int wm, int wn) {
 template <int KIND, int WM, int WN, int PREC>
 hipError_t launch_fold(dim3 grid, dim3 block, const GemmArgs& a, hipStream_t st) {
   if constexpr (fold_tile_ok(KIND, PREC, WM, WN)) {
-    if (a.range)
-      hipLaunchKernelGGL((fgemm_table_kernel<KIND, WM, WN, PREC>), grid, block, 0, st, a);
-    else
+    if (!a.range) {
       hipLaunchKernelGGL((fgemm_kernel<KIND, WM, WN, PREC>), grid, block, 0, st, a);
+    } else {
+      if constexpr (PREC == 0)   // a table's products are FP32
+        hipLaunchKernelGGL((fgemm_table_kernel<KIND, WM, WN>), grid, block, 0, st, a);
+      else
+        return hipErrorInvalidValue;
+    }
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;

@@ -86,31 +86,36 @@ __global__ void map_tmp_kernel(const float* C, const float* Bm, float* tmp, int 
 // (32 x 32 tile, nl consecutive wavelengths from l0), transposed through LDS; the tile's OPD,
 // screen and transmission are read once for all of its wavelengths. Row n stores column m at m for
 // m < h and at m + ldp - Ni for h <= m < Ni (the folded layout; h = Ni: natural), zeros elsewhere.
-template <int NLMAX>   // nl <= NLMAX (1: the single-wavelength body, with no loop state)
+// PAIRS (the field of a PSF table): column m < h stores P[m] + P[Ni - 1 - m], its mirror column the
+// difference P[m] - P[Ni - 1 - m], formed in FP64 and rounded once (an unpaired middle column: P itself).
+template <int NLMAX, bool PAIRS = false>   // nl <= NLMAX (1: the single-wavelength body, with no loop state)
 __device__ __forceinline__ void pupil_body(int bx, int by, int l0, int nl, int L, const float* A, const double* opd,
                                            const float* screen, const double* norm_part, int n_norm,
                                            const WlInfo* wl, int Ni, int ldp, int h, float* P0T, long long plane,
                                            long long by_wl) {
-  __shared__ float tr[32][33], ti[32][33];
+  constexpr int HALVES = PAIRS ? 2 : 1;
+  __shared__ float tr[HALVES][32][33], ti[HALVES][32][33];
   __shared__ double sparts[256];   // n_norm <= 256
   const int tx = threadIdx.x, ty = threadIdx.y;  // 32 x 8
   const int m0 = by * 32, n0 = bx * 32;
   // the partial sums of A^2 are read in parallel, next to the pixels' loads
   for (int i = ty * 32 + tx; i < n_norm; i += 256) sparts[i] = norm_part[i];
-  double od[4], sc[4], av[4];
-  bool in[4];
+  double od[HALVES][4], sc[HALVES][4], av[HALVES][4];
+  bool in[HALVES][4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int m = m0 + ty + 8 * q, n = n0 + tx;
-    in[q] = m < Ni && n < Ni;
-    od[q] = sc[q] = av[q] = 0.0;
-    if (in[q]) {
-      const long long p = (long long)m * Ni + n;
-      od[q] = opd[p];
-      sc[q] = (double)screen[p] * 0.15915494309189533577;   // the static screen in cycles (achromatic)
-      av[q] = (double)A[p];
+  for (int e = 0; e < HALVES; ++e)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int mq = m0 + ty + 8 * q, m = e ? Ni - 1 - mq : mq, n = n0 + tx;
+      in[e][q] = PAIRS ? mq < h && n < Ni && !(e && m == mq) : m < Ni && n < Ni;
+      od[e][q] = sc[e][q] = av[e][q] = 0.0;
+      if (in[e][q]) {
+        const long long p = (long long)m * Ni + n;
+        od[e][q] = opd[p];
+        sc[e][q] = (double)screen[p] * 0.15915494309189533577;   // the static screen in cycles (achromatic)
+        av[e][q] = (double)A[p];
+      }
     }
-  }
   __syncthreads();
   double s2 = 0.0;   // every thread adds the partials in the same order
   for (int i = 0; i < n_norm; ++i) s2 += sparts[i];
@@ -123,37 +128,60 @@ __device__ __forceinline__ void pupil_body(int bx, int by, int l0, int nl, int L
     const double inv = 1.0 / wl[l].lam;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      double sn = 0.0, cs = 0.0;
-      if (in[q]) {
-        const double t0 = od[q] * inv + sc[q];   // phase in cycles
-        const double fr = t0 - rint(t0);
-        sincospi(2.0 * fr, &sn, &cs);
+      double pr[HALVES], pi[HALVES];
+#pragma unroll
+      for (int e = 0; e < HALVES; ++e) {
+        double sn = 0.0, cs = 0.0;
+        if (in[e][q]) {
+          const double t0 = od[e][q] * inv + sc[e][q];   // phase in cycles
+          const double fr = t0 - rint(t0);
+          sincospi(2.0 * fr, &sn, &cs);
+        }
+        const double amp = av[e][q] * nrm;
+        pr[e] = amp * cs;
+        pi[e] = amp * sn;
       }
-      const double amp = av[q] * nrm;
-      tr[ty + 8 * q][tx] = (float)(amp * cs);
-      ti[ty + 8 * q][tx] = (float)(amp * sn);
+      if constexpr (PAIRS) {
+        tr[0][ty + 8 * q][tx] = (float)(pr[0] + pr[1]);
+        ti[0][ty + 8 * q][tx] = (float)(pi[0] + pi[1]);
+        tr[1][ty + 8 * q][tx] = (float)(pr[0] - pr[1]);
+        ti[1][ty + 8 * q][tx] = (float)(pi[0] - pi[1]);
+      } else {
+        tr[0][ty + 8 * q][tx] = (float)pr[0];
+        ti[0][ty + 8 * q][tx] = (float)pi[0];
+      }
     }
     __syncthreads();
     for (int q = 0; q < 4; ++q) {
       const int n = n0 + ty + 8 * q, m = m0 + tx;  // output row n, column m
-      if (n < Ni && m < ldp) {
+      float* o = P0T + l * by_wl + (long long)n * ldp;
+      if constexpr (PAIRS) {
+        if (n < Ni && m < h + ldp - Ni) {   // the ldp - Ni padding columns follow column h - 1
+          o[m] = tr[0][tx][ty + 8 * q];
+          o[plane + m] = ti[0][tx][ty + 8 * q];
+          if (m < Ni - h) {
+            o[ldp - 1 - m] = tr[1][tx][ty + 8 * q];
+            o[plane + ldp - 1 - m] = ti[1][tx][ty + 8 * q];
+          }
+        }
+      } else if (n < Ni && m < ldp) {
         const bool inside = m < Ni;
         // the ldp - Ni padding columns m >= Ni fill the gap [h, h + ldp - Ni)
         const int c = m < h ? m : (inside ? m + (ldp - Ni) : h + (m - Ni));
-        P0T[l * by_wl + (long long)n * ldp + c] = inside ? tr[tx][ty + 8 * q] : 0.f;
-        P0T[l * by_wl + plane + (long long)n * ldp + c] = inside ? ti[tx][ty + 8 * q] : 0.f;
+        o[c] = inside ? tr[0][tx][ty + 8 * q] : 0.f;
+        o[plane + c] = inside ? ti[0][tx][ty + 8 * q] : 0.f;
       }
     }
     if (i + 1 < NLMAX && l + 1 < l_end) __syncthreads();   // the next wavelength rewrites the tile
   }
 }
 
-template <int NLMAX>
+template <int NLMAX, bool PAIRS>
 __global__ __launch_bounds__(256) void pupil_kernel(const float* A, const double* opd, const float* screen,
                                                     const double* norm_part, int n_norm, const WlInfo* wl, int Ni,
                                                     int ldp, int h, float* P0T, long long plane, long long by_wl,
                                                     int nl, int L) {
-  pupil_body<NLMAX>(blockIdx.x, blockIdx.y, blockIdx.z * nl, nl, L, A, opd, screen, norm_part, n_norm, wl, Ni, ldp, h,
+  pupil_body<NLMAX, PAIRS>(blockIdx.x, blockIdx.y, blockIdx.z * nl, nl, L, A, opd, screen, norm_part, n_norm, wl, Ni, ldp, h,
                     P0T, plane, by_wl);
 }
 
@@ -309,7 +337,8 @@ hipError_t launch_prep(dlx_plan* p, const float* A, const float* Z, const float*
                        p->Nmap, p->Ni);
   }
   const int nb_opd = (int)((npix + 255) / 256);
-  const long long nt = (long long)p->n_psf * p->ldNi;
+  const bool pairs = p->range != nullptr;   // a PSF table: one star on the axis, its field as pair sums
+  const long long nt = pairs ? 0 : (long long)p->n_psf * p->ldNi;
   const int nb_tilt = (int)((nt + 255) / 256);
   hipLaunchKernelGGL(prep_kernel, dim3(nb_opd + p->n_norm_part + nb_tilt), dim3(256), 0, st, Z, c, p->Nz, npix, p->Ni,
                      Bm, p->d_maptmp, p->Nmap, p->d_opd, nb_opd, A, p->d_norm, p->n_norm_part, sources, p->d_wl,
@@ -317,18 +346,26 @@ hipError_t launch_prep(dlx_plan* p, const float* A, const float* Z, const float*
   const long long p0_by_wl = 2LL * p->Ni * p->ldNi;
   // wavelengths per block: up to 8 (each tile's loads and norm serve them all) while the launch
   // keeps at least 2048 blocks
-  const long long tiles = (long long)((p->Ni + 31) / 32) * ((p->ldNi + 31) / 32);
+  const int h = p->fold ? p->hNi() : p->Ni, cols = pairs ? h + p->ldNi - p->Ni : p->ldNi;
+  const long long tiles = (long long)((p->Ni + 31) / 32) * ((cols + 31) / 32);
   int nl = 8;
   while (nl > 1 && tiles * ((p->L + nl - 1) / nl) < 2048) nl /= 2;
-  const dim3 pgrid((p->Ni + 31) / 32, (p->ldNi + 31) / 32, (p->L + nl - 1) / nl);
-  if (nl == 1)
-    hipLaunchKernelGGL(pupil_kernel<1>, pgrid, dim3(32, 8), 0, st, A, p->d_opd, p->d_screen, p->d_norm,
-                       p->n_norm_part, p->d_wl, p->Ni, p->ldNi, p->fold ? p->hNi() : p->Ni, p->d_P0T,
-                       (long long)p->Ni * p->ldNi, p0_by_wl, nl, p->L);
-  else
-    hipLaunchKernelGGL(pupil_kernel<8>, pgrid, dim3(32, 8), 0, st, A, p->d_opd, p->d_screen, p->d_norm,
-                       p->n_norm_part, p->d_wl, p->Ni, p->ldNi, p->fold ? p->hNi() : p->Ni, p->d_P0T,
-                       (long long)p->Ni * p->ldNi, p0_by_wl, nl, p->L);
+  const dim3 pgrid((p->Ni + 31) / 32, (cols + 31) / 32, (p->L + nl - 1) / nl);
+#define DLX_PUPIL(NL, PAIRS)                                                                                         \
+  hipLaunchKernelGGL((pupil_kernel<NL, PAIRS>), pgrid, dim3(32, 8), 0, st, A, p->d_opd, p->d_screen, p->d_norm,      \
+                     p->n_norm_part, p->d_wl, p->Ni, p->ldNi, h, p->d_P0T, (long long)p->Ni * p->ldNi, p0_by_wl, nl, \
+                     p->L)
+  if (pairs) {
+    if (nl == 1)
+      DLX_PUPIL(1, true);
+    else
+      DLX_PUPIL(8, true);
+  } else if (nl == 1) {
+    DLX_PUPIL(1, false);
+  } else {
+    DLX_PUPIL(8, false);
+  }
+#undef DLX_PUPIL
   return hipGetLastError();
 }
 
