@@ -97,7 +97,7 @@ void layout_images(dlx_plan* p, Pool& pool) {
   const size_t No = p->No, ldNo = p->ldNo, fc = p->frames_per_chunk, nd2 = (size_t)p->Nd * p->Nd;
   TableArgs& t = p->ta;
   const size_t nt2 = (size_t)t.Nt * t.Nt;
-  p->d_G = pool.take<float>(fc * No * ldNo);
+  p->d_G = pool.take<float>(fc * ldNo * ldNo);
   t.G = p->d_G;
   p->d_bs = pool.take<float>(fc * p->S * nd2);
   if (p->dither) {
@@ -109,9 +109,9 @@ void layout_images(dlx_plan* p, Pool& pool) {
   p->d_lossblk = pool.take<double>((size_t)p->loss_blocks * p->n_chunks);
   p->d_status = pool.take<int>(1);
   t.I = pool.take<double>(nt2);
-  t.Ix = pool.take<double>(nt2);
-  t.Iy = pool.take<double>(nt2);
-  t.wt = pool.take<double>((size_t)t.nfs * 2 * 16 * t.K);
+  t.Ix = pool.take<float>(nt2);
+  t.Iy = pool.take<float>(nt2);
+  t.wt = pool.take<double>((size_t)t.nfs * table_weight_count(t.K));
   t.base = pool.take<int>(2 * (size_t)t.nfs);
   t.far = pool.take<int>(t.nfs);
   t.range = pool.take<int>(2);
@@ -1257,9 +1257,13 @@ constexpr double kTableBeta = 20.0;   // interpolation error about exp(-beta)
 
 // The table's pitch, taps and sizes for a problem, or false where one transform pair per star, frame and
 // wavelength is the cheaper form. A finer pitch (h16 up) needs fewer taps but more samples to transform;
-// the estimate weighs the folded products at their measured rate (85 TFLOP/s executed, 70 on a table,
-// whose launches are smaller) against the FP64 matrix instructions of the interpolation and its adjoint
-// (32 flops per cycle and SIMD, 60% reached) and the passes over memory.
+// the estimate weighs the folded products at their measured rate (85 TFLOP/s executed, after 15 us a launch; 120 on a table, which
+// leaves out the rows and columns no star reaches) against the FP64 matrix
+// instructions of the interpolation and its adjoint (64 cycles a SIMD each, times 2.3 and 2.2 to 2.6
+// measured) and the passes over memory. (512 pupil, 768 focal samples, 32 wavelengths: 128 stars 2297 us at
+// h16 = 10, 2117 at 12, 2384 at 14; 24 stars 1038 at 9, 1088 at 12.)
+constexpr int kAdjointWgs = 2048;
+
 bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
   // The table's products are FP32 in both arithmetics (they are a small part of the evaluation). A split
   // plan of few wavelengths keeps its own products: its error in the faintest pixels, 2e-5 to 6e-5 of the
@@ -1269,7 +1273,7 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
   const double Ni = p->Ni, No = p->No, L = p->L, nfs = (double)p->F * p->S;
   const double lmin = *std::min_element(p->lam.begin(), p->lam.end());
   const double lmax = *std::max_element(p->lam.begin(), p->lam.end());
-  const double direct = 4.0 * p->n_psf * (No * Ni * Ni + No * No * Ni) / 85e6 + p->n_psf * No * No * 8.0 / 4.5e6;
+  const double direct = 4.0 * p->n_psf * (No * Ni * Ni + No * No * Ni) / 85e6 + 60.0 + p->n_psf * No * No * 8.0 / 4.5e6;
   double least = 0.85 * direct;
   bool found = false;
   const int nb = ceil_div(p->No, 16);
@@ -1285,13 +1289,17 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
     const double half = 0.5 * (No - 1) * h + 0.5 * lmax / p->dx / tau + W + 6;
     if (half > 16000.0) continue;
     const int Nt = std::max(n_reg, round_up((int)std::ceil(2.0 * half), 64));
-    const double n = n_reg;
-    const double tiles = (n / 32) * (n / 32);
-    const double fwd = (std::ceil((3 * h16 + K) / 16.0) * K / 4 + 4.0 * (K / 16.0 + 1) * 4) / 4 * nb * nb;
-    const double nx = std::min((32.0 + K) / h16, (double)nb);
-    const double adj = tiles * nx * (nx * 6.0 + 16.0);
-    const double est = 4.0 * L * (n * Ni * Ni + n * n * Ni) / 70e6 + L * n * n * 8.0 / 3e6 +
-                       nfs * (fwd + adj) * 64.0 / (1024 * 2400.0 * 0.6) + nfs * No * No * 12.0 / 3e6 + 30.0;
+    const int waves = table_adjoint_waves(h16, K);
+    if (!waves) continue;
+    const double n = n_reg, own = std::min(n, No * h + W), cols = 16.0 * waves;   // own: samples a star reaches
+    const double nwg = (n / 32) * std::ceil(n / cols);
+    const double fwd = (std::ceil((7 * h16 + K) / 16.0) * K / 4 + 8.0 * (K / 4 + 1)) / 8 * nb * nb;
+    const double quads = (17.0 + W + 3 * h) / (h16 / 4.0);   // groups of four focal rows that reach 16 samples
+    const double adj = std::min(n / 32, own / 32 + 1) * std::min(std::ceil(n / cols), own / cols + 1) * waves * 2 *
+                       quads * (std::ceil(((cols + K - 1) / h16 + 1) / waves) + 1);
+    const double est = 4.0 * L * (n * Ni * Ni + n * n * Ni) / 120e6 + 60.0 + L * n * n * 8.0 / 3e6 +
+                       nfs * (2.3 * fwd + (table_adjoint_pair(h16, K) ? 2.2 : 2.6) * adj) * 64.0 / (1024 * 2400.0) +
+                       nfs * No * No * 12.0 / 3e6 + 40.0;
     if (est >= least) continue;
     least = est;
     found = true;
@@ -1306,7 +1314,8 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
     t.L = p->L;
     t.S = p->S;
     t.nfs = p->F * p->S;
-    t.slots = 4 * ceil_div((long long)std::min(tiles, 4096.0), 4);
+    t.slots = waves * (int)std::min(nwg, 4096.0);
+    t.waves = waves;
     t.tau = tau;
     t.c0 = 0.5 * (Nt - 1) - 0.5 * (No - 1) * h;
     t.beta = kTableBeta;
@@ -1332,8 +1341,17 @@ dlx_status create_with_table(dlx_plan* p, const dlx_problem_desc& d, int flags) 
   const size_t most = std::min<size_t>(kDefaultChunkBudget / frame, 65535 / p->S);
   const int fc = (int)std::max<size_t>(1, std::min<size_t>(p->F, most));
   if (p->store_fields && fc < p->F) return DLX_ERR_UNSUPPORTED;
-  t.groups = std::max(1, std::min(fc * p->S, ceil_div(2048, t.slots)));
-  t.per_group = ceil_div((long long)fc * p->S, t.groups);
+  // Star groups of the adjoint: as few as give its workgroups about eight rounds of the chip, a multiple of
+  // the eight XCDs where one is near (the workgroups of a group share the seed weights of its stars, so a
+  // group that runs on one XCD reads them from its L2).
+  const int nwg = t.slots / t.waves, stars = fc * p->S;
+  t.per_group = std::max(1, stars / ceil_div(kAdjointWgs, nwg));
+  for (int per = t.per_group; 2 * per >= t.per_group && per > 0; --per)
+    if (ceil_div(stars, per) % 8 == 0) {
+      t.per_group = per;
+      break;
+    }
+  t.groups = ceil_div(stars, t.per_group);
   // the table for stars anywhere in the pupil grid's own field: fields, seed weights, transform buffers and
   // matrices (a third of the free memory at most, else the other form)
   const size_t optics = sizeof(float) * (size_t)p->L * (2 * nt2 + nt2 + 8 * (size_t)t.Nt * p->ldNi);

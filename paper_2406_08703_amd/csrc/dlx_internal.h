@@ -133,6 +133,7 @@ struct TableArgs {
   int W, K;        // taps; table samples a block of 16 outputs may touch (multiple of 8)
   int L, S, nfs;   // wavelengths, stars per frame, stars in all
   int slots;       // position-gradient partials per star
+  int waves;       // waves of an adjoint workgroup
   int groups, per_group;   // star groups of the adjoint (each sums its stars into its own plane)
   double tau, c0, beta;    // pitch (radians); table coordinate of focal sample 0 of a star on the axis
   double half_min;         // lambda_min / (2 dx): beyond it a tilt is reduced by each wavelength's period
@@ -141,14 +142,14 @@ struct TableArgs {
   const float* E;          // table fields [L][Nt][Nt] planar
   long long e_plane, e_by_wl;
   double* I;               // polychromatic table, and its derivatives along x and y
-  double* Ix;
-  double* Iy;
-  double* wt;              // weights [nfs][2][16][K] (x, y)
+  float* Ix;
+  float* Iy;
+  double* wt;              // weights [nfs][2][16][K and padding] (x, y)
   int* base;               // first table sample of block 0 [nfs][2]
   int* far;                // [nfs] 1: a tilt beyond half_min
   int* range;              // {lo, any far star}
   float* planes;           // star images on the focal grid [chunk frames * S][No][ldg]
-  const float* G;          // seed weights [chunk frames][No][ldg]
+  const float* G;          // seed weights [chunk frames][ldg][ldg], zero past the focal grid
   double* Hpart;           // [groups][Nt][Nt]
   float* H;                // table seed weights [1 + L][Nt][Nt]
   double* pos;             // [nfs][slots][2]
@@ -267,6 +268,9 @@ hipError_t launch_table_bin(const TableArgs& t, int Q, int Nd, int f0, int nf, c
 hipError_t launch_table_adjoint(const TableArgs& t, const float* sources, int f0, int nf, bool first,
                                 hipStream_t st);
 hipError_t launch_table_seed(const TableArgs& t, int n_reg, hipStream_t st);
+int table_adjoint_waves(int h16, int K);
+bool table_adjoint_pair(int h16, int K);
+size_t table_weight_count(int K);   // weights of one star
 hipError_t launch_table_kgrad(const TableArgs& t, int Q, int Nd, int f0, int nf, const float* sources,
                               const float* flat, const float* resid, const int* win, int F_img, int Nd_img,
                               double* part, double* gpix, bool first, hipStream_t st);
@@ -386,6 +390,7 @@ struct dlx_plan {
   // stored columns of the seed weights: natural order with a table, else the fold's
   int ghNo() const { return tab ? No : hNo(); }
   int gsNo() const { return tab ? 0 : sNo(); }
+  long long g_by_frame() const { return (long long)(tab ? ldNo : No) * ldNo; }
   // captured evaluation
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;

@@ -1001,7 +1001,7 @@ hipError_t launch_seed(dlx_plan* p, int f0, int nf, const float* flat, const flo
                        hipStream_t st) {
   p->flux_blocks = p->seed_blocks;
   hipLaunchKernelGGL(seed_weight_kernel, dim3(p->seed_blocks, nf), dim3(kSeedThreads), 0, st, resid, flat, intrapixel,
-                     kstride(p), p->d_bs, f0, p->Q, p->Nd, p->S, p->ldNo, p->ghNo(), p->gsNo(), (long long)p->No * p->ldNo,
+                     kstride(p), p->d_bs, f0, p->Q, p->Nd, p->S, p->ldNo, p->ghNo(), p->gsNo(), p->g_by_frame(),
                      p->d_G, p->seed_blocks, p->d_flux);
   return hipGetLastError();
 }
@@ -1074,7 +1074,7 @@ hipError_t launch_loss(dlx_plan* p, int f0, int nf, int chunk, const float* mode
   if (seed_intrapixel_or_none) {
     p->flux_blocks = nb;
     const SeedOut so{*seed_intrapixel_or_none, kstride(p), p->d_bs, p->Q, p->Nd, p->S, p->ldNo, p->ghNo(), p->gsNo(),
-                     (long long)p->No * p->ldNo, p->d_G, p->d_flux};
+                     p->g_by_frame(), p->d_G, p->d_flux};
     hipLaunchKernelGGL(loss_kernel<true>, dim3(nb), dim3(kLossThreads), 0, st, model, binned, data, flat, f0, f0 + nf,
                        npix, kind, mu, inv_s2, r, gflat, chunk > 0 ? 1 : 0, blk, p->d_status, so);
   } else {

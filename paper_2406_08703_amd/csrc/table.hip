@@ -25,7 +25,20 @@ __device__ __forceinline__ d4 mfma_f64(double a, double b, d4 c) {
 
 __device__ __forceinline__ int iclamp(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
+// The wave's number in its workgroup, as a scalar (what follows from it stays off the vector units).
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+
+// Workgroups go round-robin to the 8 XCDs; renumbered so that a contiguous range runs on one XCD.
+__device__ __forceinline__ int xcd_order(int w, int n) {
+  const int q = n >> 3, r = n & 7, xcd = w & 7, k = w >> 3;
+  return (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + k;
+}
+
 __device__ __forceinline__ int floor_div(int a, int b) { return (a >= 0 ? a : a - b + 1) / b; }
+
+// Row length of a star's weights: K, and zeros on both sides.
+constexpr int kPadL = 16;
+__host__ __device__ constexpr int wrow(int K) { return K + kPadL + 18; }
 
 // The window of the interpolation kernel at distance t (table samples), zero from W / 2 on.
 __device__ __forceinline__ double window(double t, int W, double beta) {
@@ -57,7 +70,9 @@ __device__ __forceinline__ double reduced(const TableArgs& t, double pos, int l)
   return pos - rint(pos / per) * per;
 }
 
-// wt[fs][axis][a][q] = phi(distance of focal sample 16 b + a from table sample h16 b + base + q), any b.
+// wt[fs][axis][a][kPadL + q] = phi(distance of focal sample 16 b + a from table sample h16 b + base + q),
+// any b, 0 <= q < K, with zeros around them, so that a shifted window reads zeros where it leaves the K
+// samples.
 // Block 0 sets range[0], the first table row in use: the largest offset of a star, half the focal grid,
 // and W samples on either side (half for the interpolation, half for the derivative's stencil).
 __global__ __launch_bounds__(256) void table_weights_kernel(const TableArgs t, const float* sources) {
@@ -101,10 +116,11 @@ __global__ __launch_bounds__(256) void table_weights_kernel(const TableArgs t, c
   int base;
   const double f = star_origin(t, sources[fs * 3 + axis], base);
   if (threadIdx.x == 0) t.base[i] = base;
-  double* w = t.wt + (long long)i * 16 * t.K;
-  for (int e = threadIdx.x; e < 16 * t.K; e += 256) {
-    const int a = e / t.K, q = e - a * t.K;
-    w[e] = kernel_weight(f + (double)(a * t.h16) / 16.0 - (double)q, t.W, t.beta);
+  const int KS = wrow(t.K);
+  double* w = t.wt + (long long)i * 16 * KS;
+  for (int e = threadIdx.x; e < 16 * KS; e += 256) {
+    const int a = e / KS, q = e - a * KS - kPadL;
+    w[e] = q >= 0 && q < t.K ? kernel_weight(f + (double)(a * t.h16) / 16.0 - (double)q, t.W, t.beta) : 0.0;
   }
 }
 
@@ -168,25 +184,16 @@ __global__ __launch_bounds__(256) void table_slope_kernel(const TableArgs t) {
     const int r = lo + (int)(i / n), c = lo + (int)(i % n);
     double dx, dy;
     stencil(cf, t.W / 2, r, c, lo, hi, [&](int y, int x) { return t.I[(long long)y * t.Nt + x]; }, dx, dy);
-    t.Ix[(long long)r * t.Nt + c] = dx;
-    t.Iy[(long long)r * t.Nt + c] = dy;
+    t.Ix[(long long)r * t.Nt + c] = (float)dx;
+    t.Iy[(long long)r * t.Nt + c] = (float)dy;
   }
 }
 
-// LDS copies of a star's weights: rows of the padded length, zeros around them, so that a shifted window
-// reads zeros where it leaves the K samples.
-constexpr int kPadL = 16;
-__host__ __device__ inline int wrow(int K) { return K + kPadL + 18; }
-
-__device__ __forceinline__ void load_weights(const TableArgs& t, int fs, double* wx, double* wy) {
-  const int KS = wrow(t.K);
-  const double* gx = t.wt + (long long)fs * 2 * 16 * t.K;
-  for (int e = threadIdx.x; e < 16 * KS; e += 256) {
-    const int a = e / KS, q = e - a * KS - kPadL;
-    const bool in = q >= 0 && q < t.K;
-    wx[e] = in ? gx[a * t.K + q] : 0.0;
-    wy[e] = in ? gx[(16 + a) * t.K + q] : 0.0;
-  }
+// A star's weights into LDS: x, then y.
+__device__ __forceinline__ void load_weights(const TableArgs& t, int fs, double* w) {
+  const int n2 = 16 * wrow(t.K);   // pairs of both axes
+  const d2* src = reinterpret_cast<const d2*>(t.wt + (long long)fs * 2 * n2);
+  for (int e = threadIdx.x; e < n2; e += 256) reinterpret_cast<d2*>(w)[e] = src[e];
 }
 
 // the same for one wavelength of a star whose tilt is reduced per wavelength
@@ -204,47 +211,64 @@ __device__ __forceinline__ void far_weights(const TableArgs& t, const float* src
 }
 
 // Star images on the focal grid, plane[f][s][k] = I(u_k - position), FP64 products of the table rounded
-// to FP32 at the end. A wave forms 16 columns x 64 rows: for each 16 table rows its window touches, the
+// to FP32 at the end. A wave forms 16 columns x 16 NY rows: for each 16 table rows its window touches, the
 // product with the column weights (K / 4 instructions), whose output feeds the products with the row
-// weights of the four blocks below each other. Bound by the FP64 matrix rate.
-__global__ __launch_bounds__(256) void table_shift_kernel(const TableArgs t, const float* sources, int fs0) {
-  extern __shared__ double sh[];
-  const int KS = wrow(t.K);
+// weights of the NY blocks below each other. Bound by the FP64 matrix rate; the next rows' samples are
+// loaded while the current ones' products run, and the workgroups of one part of the focal grid, whatever
+// their star, follow each other on one XCD, whose L2 then holds that part of the table. KP = K / 8.
+template <int KP, int NY>
+__global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, const float* sources, int fs0, int nstar,
+                                                          int nbx) {
+  constexpr int K = 8 * KP, KS = wrow(K);
+  __shared__ __attribute__((aligned(16))) double sh[2 * 16 * KS];
   double *wx = sh, *wy = sh + 16 * KS;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
-  const int fs = fs0 + blockIdx.z;
+  const int lane = threadIdx.x & 63, wave = wave_id(), n = lane & 15, g = lane >> 4;
+  const int lin = xcd_order(blockIdx.x, gridDim.x);
+  const int tile = lin / nstar, star = lin - tile * nstar, fs = fs0 + star;
   const int lo = t.range[0], hi = t.Nt - lo - 1;
-  const int xb = blockIdx.x * 4 + wave, yb0 = blockIdx.y * 4;
-  const int ny = t.nb - yb0 < 4 ? t.nb - yb0 : 4;
-  d4 acc[4];
+  const int xb = (tile % nbx) * 4 + wave, yb0 = (tile / nbx) * NY;
+  const int ny = t.nb - yb0 < NY ? t.nb - yb0 : NY;
+  d4 acc[NY];
 #pragma unroll
-  for (int y = 0; y < 4; ++y) acc[y] = d4{0.0, 0.0, 0.0, 0.0};
+  for (int y = 0; y < NY; ++y) acc[y] = d4{0.0, 0.0, 0.0, 0.0};
 
   auto add = [&](auto pair, int jx, int jy) {
-    const int cx = jx + t.h16 * xb, ry = jy + t.h16 * yb0;
-    const int rbs = (t.h16 * (ny - 1) + t.K + 15) / 16;
+    const int cx = jx + t.h16 * xb + 2 * g, ry = jy + t.h16 * yb0 + n;
+    const int rbs = (t.h16 * (ny - 1) + K + 15) / 16;
+    d2 w[KP], v[KP], nx[KP];
+#pragma unroll
+    for (int p = 0; p < KP; ++p) w[p] = *reinterpret_cast<const d2*>(&wx[n * KS + kPadL + 8 * p + 2 * g]);
+    // the window leaves the samples in use only where a block has columns past the focal grid
+    const bool inside = cx - 2 * g >= lo && cx - 2 * g + K - 1 <= hi;
+    auto load = [&](int rb, d2* o) {
+      const int row = iclamp(ry + 16 * rb, lo, hi);
+#pragma unroll
+      for (int p = 0; p < KP; ++p) o[p] = pair(row, inside ? cx + 8 * p : iclamp(cx + 8 * p, lo, hi - 1));
+    };
+    load(0, v);
     for (int rb = 0; rb < rbs; ++rb) {
-      const int row = iclamp(ry + 16 * rb + n, lo, hi);
+      if (rb + 1 < rbs) load(rb + 1, nx);
       d4 d = d4{0.0, 0.0, 0.0, 0.0};
-      for (int p = 0; p < t.K; p += 8) {
-        const d2 v = pair(row, iclamp(cx + p + 2 * g, lo, hi - 1));
-        const d2 w = *reinterpret_cast<const d2*>(&wx[n * KS + kPadL + p + 2 * g]);
-        d = mfma_f64(v[0], w[0], d);
-        d = mfma_f64(v[1], w[1], d);
+#pragma unroll
+      for (int p = 0; p < KP; ++p) {
+        d = mfma_f64(v[p][0], w[p][0], d);
+        d = mfma_f64(v[p][1], w[p][1], d);
       }
 #pragma unroll
-      for (int y = 0; y < 4; ++y) {
+      for (int y = 0; y < NY; ++y) {
         const int rel = 16 * rb - t.h16 * y;
-        if (y < ny && rel > -16 && rel < t.K) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc[y] = mfma_f64(wy[n * KS + kPadL + rel + 4 * r + g], d[r], acc[y]);
-        }
+        for (int r = 0; r < 4; ++r)
+          if (y < ny && rel + 4 * r > -4 && rel + 4 * r < K)   // the block's window reaches these four rows
+            acc[y] = mfma_f64(wy[n * KS + kPadL + rel + 4 * r + g], d[r], acc[y]);
       }
+#pragma unroll
+      for (int p = 0; p < KP; ++p) v[p] = nx[p];
     }
   };
 
   if (!t.far[fs]) {
-    load_weights(t, fs, wx, wy);
+    load_weights(t, fs, wx);
     __syncthreads();
     if (xb < t.nb)
       add([&](int r, int c) {
@@ -267,11 +291,11 @@ __global__ __launch_bounds__(256) void table_shift_kernel(const TableArgs t, con
         }, jx, jy);
     }
   }
-  float* o = t.planes + (long long)blockIdx.z * t.No * t.ldg;
+  float* o = t.planes + (long long)star * t.No * t.ldg;
   const int x = 16 * xb + n;
   if (x < t.No) {
 #pragma unroll
-    for (int y = 0; y < 4; ++y)
+    for (int y = 0; y < NY; ++y)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int yy = 16 * (yb0 + y) + 4 * r + g;
@@ -311,39 +335,232 @@ __global__ __launch_bounds__(256) void table_bin_kernel(const TableArgs t, int Q
 // The transpose: the seed weights G of frames [f0, f0 + nf) spread onto the table,
 //   D_fs[j] = sum_k phi(t_k - j) G_f[k],   H += phi_s D_fs,
 // and the position gradient -phi_s / tau sum_j D_fs[j] I'[j] (the derivative field is interpolated with
-// the same weights). A wave owns 32 x 32 table samples and runs every star of its group: for each 16 focal
-// columns, the rows of G that reach its rows (A = G transposed, B = row weights), then the product with
-// the column weights. FAR: the stars reduced per wavelength, one wavelength after the other, each into
-// that wavelength's own plane of H (table_seed_kernel adds the common one).
-template <bool FAR>
-__global__ __launch_bounds__(256) void table_adjoint_kernel(const TableArgs t, const float* sources, int f0, int nf,
-                                                            int first) {
+// the same weights). A workgroup owns 32 table rows x 16 WAVES columns and runs every star of its group in
+// two products: its waves share out the blocks of 16 focal columns that reach its columns and contract the
+// rows of G with the row weights (V, kept in LDS as it lies in the output registers, which is how the
+// second product reads it); then each wave contracts V with the column weights for its 16 columns. Only the
+// groups of four focal rows or columns whose taps reach a tile are multiplied. (G holds whole blocks of 16
+// rows and columns, zero past the focal grid, so nothing is masked.) The FP64 matrix rate bounds it, with
+// two workgroups per CU at about half of it: G comes kAdjRows blocks at a time, one step ahead, and the
+// next star's weights during the current star. 128 stars of 768 focal samples onto 832: 520 us (1115 us
+// for 32 x 32 samples per wave, each forming its own V from G without a step ahead).
+constexpr int kAdjRows = 2;   // blocks of focal rows loaded at a time
+constexpr int kAdjLds = 150 << 10;
+
+// blocks of focal columns that reach a workgroup's 16 `waves` table columns (V holds 4 KB for each)
+int adjoint_blocks(int waves, int h16, int K) { return (16 * waves + K - 2) / h16 + 1; }
+size_t adjoint_lds(int waves, int h16, int K) {
+  return sizeof(double) * (2 * 16 * wrow(K) + (size_t)adjoint_blocks(waves, h16, K) * 2 * 4 * 64);
+}
+
+// v moved by one DPP step (no source: 0), for the sums over a wave
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+
+// Sum over the 64 lanes, valid in lane 63.
+__device__ __forceinline__ double wave_total(double v) {
+  v = dpp_add<0x111>(v);   // row_shr:1
+  v = dpp_add<0x112>(v);   // row_shr:2
+  v = dpp_add<0x114>(v);   // row_shr:4
+  v = dpp_add<0x118>(v);   // row_shr:8
+  v = dpp_add<0x142>(v);   // row_bcast:15
+  return dpp_add<0x143>(v);   // row_bcast:31
+}
+
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES / 2) void table_adjoint_kernel(const TableArgs t, const float* sources, int f0, int nf,
+                                                               int first) {
+  extern __shared__ double sh[];
+  const int K = t.K, KS = wrow(K), h16 = t.h16, ldg = t.ldg;
+  double(*V)[2][4][64] = reinterpret_cast<double(*)[2][4][64]>(sh + 2 * 16 * KS);
+  const int lane = threadIdx.x & 63, wave = wave_id(), n = lane & 15, g = lane >> 4;
+  // this lane's place in a block of G (row 4 k + g, column n) and in the weights (focal sample 4 k + g,
+  // table sample n of a tile that starts at the block's window)
+  const unsigned goff = (unsigned)(g * ldg + n);
+  const double* wx = sh + g * KS + kPadL + n;
+  const double* wy = wx + 16 * KS;
+  const int lo = t.range[0], hi = t.Nt - lo - 1;
+  constexpr int CW = 16 * WAVES, TH = 64 * WAVES, kPairs = 2048 / TH;
+  const int nrt = (t.Nt - 2 * lo) / 32, ncg = (t.Nt - 2 * lo + CW - 1) / CW;
+  const int nwg = t.slots / WAVES, lin = xcd_order(blockIdx.x, gridDim.x);
+  const int group = lin / nwg, wg = lin - group * nwg;
+  const int slot = wg * WAVES + wave;
+  const int fs0 = f0 * t.S + group * t.per_group;
+  const int fs_end = min((f0 + nf) * t.S, fs0 + t.per_group);
+  // this wave's partials of every star start at zero (a far star's are added to by the far pass)
+  for (int i = 2 * fs0 + lane; i < 2 * fs_end; i += 64)
+    t.pos[((long long)(i >> 1) * t.slots + slot) * 2 + (i & 1)] = 0.0;
+  auto next_star = [&](int fs) {
+    while (fs < fs_end && t.far[fs]) ++fs;
+    return fs;
+  };
+  // the window's samples that four focal samples 4 k .. 4 k + 3 can reach
+  auto first_tap = [&](int k) { return (k * h16) >> 2; };
+  auto last_tap = [&](int k) { return (((4 * k + 3) * h16) >> 4) + t.W + 1; };
+  const int n2 = 16 * KS;   // weights of both axes, in pairs
+  d2 nw[kPairs];
+  auto fetch_weights = [&](int fs) {
+    const d2* src = reinterpret_cast<const d2*>(t.wt + (long long)fs * 2 * n2);
+#pragma unroll
+    for (int i = 0; i < kPairs; ++i)
+      if ((int)threadIdx.x + TH * i < n2) nw[i] = src[threadIdx.x + TH * i];
+  };
+  for (int tile = wg; tile < nrt * ncg; tile += nwg) {
+    const int R0 = lo + 32 * (tile % nrt), C0 = lo + CW * (tile / nrt);
+    const int c = C0 + 16 * wave;   // this wave's columns
+    const bool live = c <= hi;
+    const long long t0 = (long long)R0 * t.Nt + (live ? c : lo);   // the tile, and this lane's place in it
+    const unsigned o0 = (unsigned)(g * t.Nt + n);
+    d4 H[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+    // the blocks of star fs that reach this tile
+    int jx, jy, xb0, xb1, yb0, yb1;
+    const float* G;
+    auto set_star = [&](int fs) {
+      jx = t.base[2 * fs];
+      jy = t.base[2 * fs + 1];
+      G = t.G + (long long)(fs / t.S - f0) * ldg * ldg;
+      xb0 = max(0, floor_div(C0 - K - jx, h16) + 1);
+      xb1 = min(t.nb - 1, floor_div(min(C0 + CW - 1, hi) - jx, h16));
+      yb0 = max(0, floor_div(R0 - K - jy, h16) + 1);
+      yb1 = min(t.nb - 1, floor_div(R0 + 31 - jy, h16));
+    };
+    float nv[4 * kAdjRows];
+    auto fetch = [&](int xb, int yc) {   // rows yc .. yc + kAdjRows - 1 (in blocks) of block column xb
+      const float* gc = G + 16 * xb;
+#pragma unroll
+      for (int i = 0; i < kAdjRows; ++i) {
+        const float* gr = gc + (long long)(16 * min(yc + i, t.nb - 1)) * ldg;   // uniform
+#pragma unroll
+        for (int k = 0; k < 4; ++k) nv[4 * i + k] = (gr + (long long)4 * k * ldg)[goff];
+      }
+    };
+    int fs = next_star(fs0);
+    if (fs < fs_end) {
+      fetch_weights(fs);
+      set_star(fs);
+      fetch(min(xb0 + wave, t.nb - 1), yb0);
+    }
+    while (fs < fs_end) {
+      const int after = next_star(fs + 1);
+      __syncthreads();   // the previous star's weights and V are done with
+#pragma unroll
+      for (int i = 0; i < kPairs; ++i)
+        if ((int)threadIdx.x + TH * i < n2) reinterpret_cast<d2*>(sh)[threadIdx.x + TH * i] = nw[i];
+      __syncthreads();
+      if (after < fs_end) fetch_weights(after);
+      for (int xb = xb0 + wave; xb <= xb1; xb += WAVES) {
+        d4 acc[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+        for (int yc = yb0; yc <= yb1; yc += kAdjRows) {
+          float v[4 * kAdjRows];
+#pragma unroll
+          for (int i = 0; i < 4 * kAdjRows; ++i) v[i] = nv[i];
+          const bool last = yc + kAdjRows > yb1;   // one step ahead: more rows, or the wave's next column
+          if (!last || xb + WAVES <= xb1) fetch(last ? xb + WAVES : xb, last ? yb0 : yc + kAdjRows);
+#pragma unroll
+          for (int i = 0; i < kAdjRows; ++i) {
+            const int rel = R0 - (jy + h16 * (yc + i));   // the tile's first row in the block's window
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              if (yc + i > yb1) continue;
+              const double a = (double)v[4 * i + k];
+              if (first_tap(k) <= rel + 15 && last_tap(k) >= rel) acc[0] = mfma_f64(a, wy[4 * k * KS + rel], acc[0]);
+              if (first_tap(k) <= rel + 31 && last_tap(k) >= rel + 16)
+                acc[1] = mfma_f64(a, wy[4 * k * KS + rel + 16], acc[1]);
+            }
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) V[xb - xb0][i][r][lane] = acc[i][r];
+      }
+      __syncthreads();
+      const double phi = (double)sources[fs * 3 + 2];
+      const int cjx = jx, cx0 = xb0, cx1 = xb1;
+      if (after < fs_end) {
+        set_star(after);
+        fetch(min(xb0 + wave, t.nb - 1), yb0);
+      }
+      d4 D[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+      float gx[8], gy[8];   // read again for every star: kept, they would cost a workgroup per CU
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        gx[k] = (t.Ix + t0 + (long long)(4 * k) * t.Nt)[o0];
+        gy[k] = (t.Iy + t0 + (long long)(4 * k) * t.Nt)[o0];
+      }
+      if (live) {
+        const int b1 = min(cx1, floor_div(c + 15 - cjx, h16));
+        for (int xb = max(cx0, floor_div(c - K - cjx, h16) + 1); xb <= b1; ++xb) {
+          const int rel = c - (cjx + h16 * xb);
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (first_tap(r) <= rel + 15 && last_tap(r) >= rel) {
+              const double w = wx[4 * r * KS + rel];
+              D[0] = mfma_f64(V[xb - cx0][0][r][lane], w, D[0]);
+              D[1] = mfma_f64(V[xb - cx0][1][r][lane], w, D[1]);
+            }
+        }
+      }
+      double px = 0.0, py = 0.0;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const double d = phi * D[i][r];
+          H[i][r] += d;
+          px = fma(d, (double)gx[4 * i + r], px);
+          py = fma(d, (double)gy[4 * i + r], py);
+        }
+      px = wave_total(px);
+      py = wave_total(py);
+      if (lane == 63) {
+        double* o = t.pos + ((long long)fs * t.slots + slot) * 2;
+        const bool again = tile != wg;
+        o[0] = (again ? o[0] : 0.0) - px / t.tau;
+        o[1] = (again ? o[1] : 0.0) - py / t.tau;
+      }
+      fs = after;
+    }
+    if (live) {
+      double* h = t.Hpart + group * (long long)t.Nt * t.Nt + t0;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          double* q = h + (long long)(16 * i + 4 * r) * t.Nt;
+          q[o0] = (first ? 0.0 : q[o0]) + H[i][r];
+        }
+    }
+  }
+}
+
+// The same for stars whose tilt is reduced per wavelength, one wavelength after the other, each into that
+// wavelength's own plane of H (table_seed_kernel adds the common one). A wave owns 32 x 32 samples; no star
+// of a sampled pupil's own field comes here, so it is kept simple.
+__global__ __launch_bounds__(256) void table_far_kernel(const TableArgs t, const float* sources, int f0, int nf,
+                                                        int first) {
   extern __shared__ double sh[];
   __shared__ double cf[kMaxHalfTaps + 1];
-  if (FAR && !t.range[1]) return;
+  if (!t.range[1]) return;
   const int KS = wrow(t.K);
   double *wx = sh, *wy = sh + 16 * KS;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
+  const int lane = threadIdx.x & 63, wave = wave_id(), n = lane & 15, g = lane >> 4;
   const int lo = t.range[0], hi = t.Nt - lo - 1;
   const int nt = (t.Nt - 2 * lo) / 32, ntile = nt * nt;
   const int slot = blockIdx.x * 4 + wave;
-  int fs_begin = f0 * t.S, fs_end = (f0 + nf) * t.S;
-  if (!FAR) {
-    fs_begin += blockIdx.y * t.per_group;
-    fs_end = min(fs_end, fs_begin + t.per_group);
-    // this wave's partials of every star start at zero (a far star's are added to by the far pass)
-    for (int i = 2 * fs_begin + lane; i < 2 * fs_end; i += 64)
-      t.pos[((long long)(i >> 1) * t.slots + slot) * 2 + (i & 1)] = 0.0;
-  } else {
-    stencil_weights(cf, t);
-  }
-  for (int l = 0; l < (FAR ? t.L : 1); ++l) {
+  stencil_weights(cf, t);
+  for (int l = 0; l < t.L; ++l) {
     for (int t0 = blockIdx.x * 4; t0 < ntile; t0 += gridDim.x * 4) {
       const bool live = t0 + wave < ntile;
       const int tile = live ? t0 + wave : 0;
       const int R0 = lo + 32 * (tile / nt), C0 = lo + 32 * (tile % nt);
       d4 H[2][2], gx[2][2], gy[2][2];
-      if (FAR) __syncthreads();   // the stencil's weights
+      __syncthreads();   // the stencil's weights
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -352,33 +569,24 @@ __global__ __launch_bounds__(256) void table_adjoint_kernel(const TableArgs t, c
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int row = R0 + 16 * i + 4 * r + g, col = C0 + 16 * j + n;
-            const long long o = (long long)row * t.Nt + col;
-            if constexpr (!FAR) {
-              gx[i][j][r] = t.Ix[o];
-              gy[i][j][r] = t.Iy[o];
-            } else {
-              const float* e = t.E + l * t.e_by_wl;
-              const double w = (double)t.wl[l].w;
-              double dx, dy;
-              stencil(cf, t.W / 2, row, col, lo, hi, [&](int y, int x) {
-                const long long q = (long long)y * t.Nt + x;
-                return w * power(e[q], e[q + t.e_plane]);
-              }, dx, dy);
-              gx[i][j][r] = dx;
-              gy[i][j][r] = dy;
-            }
+            const float* e = t.E + l * t.e_by_wl;
+            const double w = (double)t.wl[l].w;
+            double dx, dy;
+            stencil(cf, t.W / 2, row, col, lo, hi, [&](int y, int x) {
+              const long long q = (long long)y * t.Nt + x;
+              return w * power(e[q], e[q + t.e_plane]);
+            }, dx, dy);
+            gx[i][j][r] = dx;
+            gy[i][j][r] = dy;
           }
         }
-      for (int fs = fs_begin; fs < fs_end; ++fs) {
-        if ((t.far[fs] != 0) != FAR) continue;
-        int jx = t.base[2 * fs], jy = t.base[2 * fs + 1];
+      for (int fs = f0 * t.S; fs < (f0 + nf) * t.S; ++fs) {
+        if (!t.far[fs]) continue;
+        int jx, jy;
         __syncthreads();
-        if constexpr (FAR)
-          far_weights(t, sources + fs * 3, l, wx, wy, jx, jy);
-        else
-          load_weights(t, fs, wx, wy);
+        far_weights(t, sources + fs * 3, l, wx, wy, jx, jy);
         __syncthreads();
-        const float* G = t.G + (long long)(fs / t.S - f0) * t.No * t.ldg;
+        const float* G = t.G + (long long)(fs / t.S - f0) * t.ldg * t.ldg;
         d4 D[2][2];
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -454,13 +662,8 @@ __global__ __launch_bounds__(256) void table_adjoint_kernel(const TableArgs t, c
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               const long long o = (long long)(R0 + 16 * i + 4 * r + g) * t.Nt + C0 + 16 * j + n;
-              if constexpr (FAR) {
-                float* h = t.H + (1 + l) * (long long)t.Nt * t.Nt;
-                h[o] = (float)((first ? 0.0 : (double)h[o]) + H[i][j][r]);
-              } else {
-                double* h = t.Hpart + blockIdx.y * (long long)t.Nt * t.Nt;
-                h[o] = (first ? 0.0 : h[o]) + H[i][j][r];
-              }
+              float* h = t.H + (1 + l) * (long long)t.Nt * t.Nt;
+              h[o] = (float)((first ? 0.0 : (double)h[o]) + H[i][j][r]);
             }
       }
     }
@@ -566,9 +769,32 @@ hipError_t launch_table_image(const TableArgs& t, int n_reg, bool derivatives, h
 }
 
 hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, int nf, hipStream_t st) {
-  const unsigned nb4 = (t.nb + 3) / 4;
-  hipLaunchKernelGGL(table_shift_kernel, dim3(nb4, nb4, nf * t.S), dim3(256), 2 * 16 * wrow(t.K) * sizeof(double), st,
-                     t, sources, f0 * t.S);
+  const int nbx = (t.nb + 3) / 4, nstar = nf * t.S;
+  // eight blocks of rows per wave (the fewest instructions) where that still fills the chip twice
+  const int ny = (long long)nbx * ((t.nb + 7) / 8) * nstar >= 1024 ? 8 : (long long)nbx * ((t.nb + 3) / 4) * nstar >= 512 ? 4 : 1;
+  const dim3 grid((unsigned)(nbx * ((t.nb + ny - 1) / ny) * nstar)), blk(256);
+#define DLX_SHIFT(KP)                                                                                              \
+  case KP:                                                                                                         \
+    if (ny == 8)                                                                                                   \
+      hipLaunchKernelGGL((table_shift_kernel<KP, 8>), grid, blk, 0, st, t, sources, f0 * t.S, nstar, nbx);        \
+    else if (ny == 4)                                                                                              \
+      hipLaunchKernelGGL((table_shift_kernel<KP, 4>), grid, blk, 0, st, t, sources, f0 * t.S, nstar, nbx);        \
+    else                                                                                                           \
+      hipLaunchKernelGGL((table_shift_kernel<KP, 1>), grid, blk, 0, st, t, sources, f0 * t.S, nstar, nbx);        \
+    break
+  switch (t.K / 8) {
+    DLX_SHIFT(2);
+    DLX_SHIFT(3);
+    DLX_SHIFT(4);
+    DLX_SHIFT(5);
+    DLX_SHIFT(6);
+    DLX_SHIFT(7);
+    DLX_SHIFT(8);
+    DLX_SHIFT(9);
+    DLX_SHIFT(10);
+    default: return hipErrorInvalidValue;
+  }
+#undef DLX_SHIFT
   return hipGetLastError();
 }
 
@@ -584,13 +810,35 @@ hipError_t launch_table_bin(const TableArgs& t, int Q, int Nd, int f0, int nf, c
 // far stars onto the wavelengths' planes (which leaves at once when there are none).
 hipError_t launch_table_adjoint(const TableArgs& t, const float* sources, int f0, int nf, bool first,
                                 hipStream_t st) {
-  const size_t lds = 2 * 16 * wrow(t.K) * sizeof(double);
-  hipLaunchKernelGGL(table_adjoint_kernel<false>, dim3(t.slots / 4, t.groups), dim3(256), lds, st, t, sources, f0, nf,
-                     first ? 1 : 0);
-  hipLaunchKernelGGL(table_adjoint_kernel<true>, dim3(t.slots / 4), dim3(256), lds, st, t, sources, f0, nf,
-                     first ? 1 : 0);
+  const size_t lds = adjoint_lds(t.waves, t.h16, t.K), far_lds = 2 * 16 * wrow(t.K) * sizeof(double);
+#define DLX_ADJOINT(WAVES)                                                                                           \
+  case WAVES:                                                                                                        \
+    hipLaunchKernelGGL(table_adjoint_kernel<WAVES>, dim3(t.slots / WAVES * t.groups), dim3(64 * WAVES), lds, st, t, \
+                       sources, f0, nf, first ? 1 : 0);                                                              \
+    break
+  switch (t.waves) {
+    DLX_ADJOINT(4);
+    DLX_ADJOINT(8);
+    default: return hipErrorInvalidValue;
+  }
+#undef DLX_ADJOINT
+  hipLaunchKernelGGL(table_far_kernel, dim3(t.slots / 4), dim3(256), far_lds, st, t, sources, f0, nf, first ? 1 : 0);
   return hipGetLastError();
 }
+
+size_t table_weight_count(int K) { return 2 * 16 * (size_t)wrow(K); }
+
+// Waves of an adjoint workgroup (16 table columns each): 8, or 4 where the focal blocks that reach 128
+// columns do not fit the LDS; 0 where neither does. (Four where eight fit as well is slower, 703 us against
+// 665 for 128 stars at h16 = 12: the first product, shared by the waves, covers K columns more than they own.)
+int table_adjoint_waves(int h16, int K) {
+  for (int waves : {8, 4})
+    if (adjoint_lds(waves, h16, K) <= kAdjLds) return waves;
+  return 0;
+}
+
+// whether two workgroups of eight waves fit a CU
+bool table_adjoint_pair(int h16, int K) { return adjoint_lds(8, h16, K) <= 80 << 10; }
 
 // The table's seed weights, once every frame is in the groups' planes.
 hipError_t launch_table_seed(const TableArgs& t, int n_reg, hipStream_t st) {
