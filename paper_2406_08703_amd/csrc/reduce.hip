@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "dlx_internal.h"
+#include "wave.h"
 
 namespace dlx {
 namespace {
@@ -463,6 +464,23 @@ struct SeedOut {
   double* flux;           // [F][S][gridDim.x]
 };
 
+// The loss terms of one pixel and frame (Section 4): its term of L, its residual dl/dm.
+__device__ __forceinline__ double loss_term(int kind, double m, double d, double& r, int& flags) {
+  if (!isfinite(m) || !isfinite(d)) flags |= 1;
+  if (kind == DLX_LOSS_POISSON) {
+    if (m <= 0.0) {
+      if (d > 0.0) flags |= 2;
+      m = 1e-30;
+    }
+    r = 1.0 - d / m;
+    return m - (d != 0.0 ? d * log(m) : 0.0);
+  }
+  const double w = d > 1.0 ? d : 1.0;
+  const double dm = m - d;
+  r = dm / w;
+  return 0.5 * dm * dm / w;
+}
+
 // Per pixel p: loop over frames f0 <= f < f1, l = m - d ln m (or
 // (m-d)^2/(2 max(d,1))), r = dl/dm, and grad_flat[p] = sum_f r B + (F - mu)/sigma^2.
 // With `accumulate` the frame sum is added to grad_flat and the prior is left
@@ -479,32 +497,26 @@ __global__ void loss_kernel(const float* model, const float* binned, const float
   const float fp = live ? flat[p] : 0.f;
   double lsum = 0.0, gf = 0.0;
   int flags = 0;
+  float mn = 1.f, dn = 0.f, bn = 0.f;   // the next frame's values, loaded while the current ones are used
+  auto fetch = [&](int f) {
+    if (live && f < f1) {
+      const long long q = (long long)f * npix + p;
+      mn = model[q];
+      dn = data[q];
+      bn = binned[q];
+    }
+  };
+  fetch(f0);
   for (int f = f0; f < f1; ++f) {
+    const float mf = mn, df = dn, bf = bn;
+    fetch(f + 1);
     float rf = 0.f;
     if (live) {
-      const long long q = (long long)f * npix + p;
-      double m = model[q];
-      const double d = data[q];
-      const double b = binned[q];
-      if (!isfinite(m) || !isfinite(d)) flags |= 1;
-      double ell, r;
-      if (kind == DLX_LOSS_POISSON) {
-        if (m <= 0.0) {
-          if (d > 0.0) flags |= 2;
-          m = 1e-30;
-        }
-        ell = m - (d != 0.0 ? d * log(m) : 0.0);
-        r = 1.0 - d / m;
-      } else {
-        const double w = d > 1.0 ? d : 1.0;
-        const double dm = m - d;
-        ell = 0.5 * dm * dm / w;
-        r = dm / w;
-      }
-      lsum += ell;
+      double r;
+      lsum += loss_term(kind, mf, df, r, flags);
       rf = (float)r;
-      r_out[q] = rf;
-      gf += r * b;
+      r_out[(long long)f * npix + p] = rf;
+      gf += r * (double)bf;
     }
     if constexpr (SEED) {
       const int fl = f - f0;
@@ -536,6 +548,131 @@ __global__ void loss_kernel(const float* model, const float* binned, const float
   if (flags) atomicOr(status, flags);  // bit 0: non-finite, bit 1: domain
   const double t = block_sum(lsum, sh);
   if (threadIdx.x == 0) blk[blockIdx.x] = t;
+}
+
+// loss_kernel for several frames: a block covers the same 256 pixels, its waves (up to kFrameWaves) share
+// out the frames, each lane runs four pixels of a frame, and the waves' flat-field gradients are added in
+// order at the end. One wave per 64 pixels that runs the frames one after the other waits for its loads and,
+// with SEED, twice per star and frame for the block's sum: 283 us for 64 frames of 2 stars (256^2 pixels,
+// 9 samples each), 107 us here, with the seed weights written through LDS in rows of consecutive samples
+// (53 us of traffic at the copy rate).
+// QT: oversampling (0: any, and seed planes of 2^31 samples or more).
+constexpr int kFrameWaves = 16;
+
+template <bool SEED, int QT>
+__global__ __launch_bounds__(64 * kFrameWaves) void loss_frames_kernel(
+    const float* model, const float* binned, const float* data, const float* flat, int f0, int f1, long long npix,
+    int kind, double mu, double inv_s2, float* r_out, double* grad_flat, int accumulate, double* blk, int* status,
+    SeedOut so) {
+  __shared__ double sum[kFrameWaves][256];
+  __shared__ double lw[kFrameWaves];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int waves = blockDim.x >> 6;
+  float* hs = reinterpret_cast<float*>(sum[wave]);   // this wave's flat r of the frame
+  const long long base = (long long)blockIdx.x * 256;
+  const int Q = QT > 0 ? QT : so.Q;
+  float fp[4];
+  bool live[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    live[i] = base + lane + 64 * i < npix;
+    fp[i] = live[i] ? flat[base + lane + 64 * i] : 0.f;
+  }
+  // sample of the block's rows of G that this lane writes: element lane + 64 i of 256 Q columns
+  auto place = [&](int e) -> long long {
+    const long long p = base + e / Q;
+    if (p >= npix) return -1;
+    const int pr = (int)(p / so.Nd), pc = (int)(p - (long long)pr * so.Nd);
+    return (long long)(Q * pr) * so.ldg + fcol(Q * pc + e % Q, so.fh, so.fs);
+  };
+  int off[QT > 0 ? 4 * QT : 1];
+  if constexpr (SEED && QT > 0) {
+#pragma unroll
+    for (int i = 0; i < 4 * QT; ++i) off[i] = (int)place(lane + 64 * i);
+  }
+  double lsum = 0.0, gf[4] = {0.0, 0.0, 0.0, 0.0};
+  int flags = 0;
+  for (int f = f0 + wave; f < f1; f += waves) {
+    float mv[4], dv[4], bv[4], h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const long long q = (long long)f * npix + base + lane + 64 * i;
+      mv[i] = live[i] ? model[q] : 1.f;
+      dv[i] = live[i] ? data[q] : 0.f;
+      bv[i] = live[i] ? binned[q] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      h[i] = 0.f;
+      if (live[i]) {
+        double r;
+        lsum += loss_term(kind, mv[i], dv[i], r, flags);
+        const float rf = (float)r;
+        r_out[(long long)f * npix + base + lane + 64 * i] = rf;
+        gf[i] += r * (double)bv[i];
+        h[i] = fp[i] * rf;
+      }
+    }
+    if constexpr (SEED) {
+      const int fl = f - f0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) hs[lane + 64 * i] = h[i];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      float* g = so.G + fl * so.g_by_frame;
+      auto put = [&](int e, long long o) {
+        const int px = e / Q, b = e - px * Q;
+        const float hv = hs[px];
+        const float* kp = so.intrapixel ? so.intrapixel + (base + px) * so.kst + b : nullptr;
+        for (int a = 0; a < Q; ++a) g[o + (long long)a * so.ldg] = kp ? hv * kp[a * Q] : hv;
+      };
+      if constexpr (QT > 0) {
+#pragma unroll
+        for (int i = 0; i < 4 * QT; ++i)
+          if (off[i] >= 0) put(lane + 64 * i, off[i]);
+      } else {
+        for (int e = lane; e < 256 * Q; e += 64) {
+          const long long o = place(e);
+          if (o >= 0) put(e, o);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (int s = 0; s < so.S; ++s) {
+        const float* bs = so.bs + ((long long)fl * so.S + s) * npix + base + lane;
+        double v = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v += live[i] ? (double)h[i] * (double)bs[64 * i] : 0.0;
+        v = wave_total(v);
+        if (lane == 63) so.flux[((long long)f * so.S + s) * gridDim.x + blockIdx.x] = v;
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) sum[wave][lane + 64 * i] = gf[i];
+  __syncthreads();
+  for (int q = threadIdx.x; q < 256; q += blockDim.x) {
+    const long long p = base + q;
+    if (p >= npix) break;
+    double g = 0.0;
+    for (int w = 0; w < waves; ++w) g += sum[w][q];
+    if (accumulate) {
+      grad_flat[p] += g;
+    } else {
+      const double dfl = (double)flat[p] - mu;
+      lsum += 0.5 * dfl * dfl * inv_s2;
+      grad_flat[p] = g + dfl * inv_s2;
+    }
+  }
+  if (flags) atomicOr(status, flags);  // bit 0: non-finite, bit 1: domain
+  lsum = wave_total(lsum);
+  if (lane == 63) lw[wave] = lsum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int w = 0; w < waves; ++w) t += lw[w];
+    blk[blockIdx.x] = t;
+  }
 }
 
 // L = sum of block partials, one block, fixed order.
@@ -629,41 +766,67 @@ __global__ void window_kernel(const float* Bbig, int Nb, const int* win, int Nd,
 // windows gathers, for enlarged pixel q, h[q] = sum over the frames whose window
 // holds q (p = q - win_f) of flat[p] r_f[p], in frame order; then
 //   G[Q q_r + a][Q q_c + b] = K[a][b] h[q]
-// and the flux partials sum_q h[q] bs_s[q] of this block (one enlarged frame),
-// at flux[s nblk + block].
-__global__ void seed_gather_kernel(const float* resid, const float* flat, const float* intrapixel, const float* bs,
-                                   const int* win, int F, int Nd, int Nb, int Q, int S, int ldg, int fh, int fs,
-                                   float* G, double* flux) {
-  __shared__ double sh[kSeedThreads / 64];
+// and the flux partials sum_q h[q] bs_s[q] (one enlarged frame).
+// A wave runs 256 pixels, four per lane, and adds up its own flux partials, at flux[s nblk + wave of the
+// grid] (20 stars over 1064^2 pixels: 52 us; 65 us with a block's sum and its two barriers per star).
+__global__ __launch_bounds__(kSeedThreads) void seed_gather_kernel(
+    const float* resid, const float* flat, const float* intrapixel, const float* bs, const int* win, int F, int Nd,
+    int Nb, int Q, int S, int ldg, int fh, int fs, float* G, int nblk, double* flux) {
   const long long nb2 = (long long)Nb * Nb, npix = (long long)Nd * Nd;
-  const long long q = (long long)blockIdx.x * kSeedThreads + threadIdx.x;
-  float h = 0.f;
-  if (q < nb2) {
-    const int qr = (int)(q / Nb), qc = (int)(q - (long long)qr * Nb);
-    for (int f = 0; f < F; ++f) {
-      const int pr = qr - win[2 * f], pc = qc - win[2 * f + 1];
-      if (pr >= 0 && pr < Nd && pc >= 0 && pc < Nd) {
-        const long long p = (long long)pr * Nd + pc;
-        h += flat[p] * resid[(long long)f * npix + p];
-      }
+  const int lane = threadIdx.x & 63;
+  const int unit = blockIdx.x * (kSeedThreads / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (unit >= nblk) return;
+  float h[4];
+  bool live[4];
+  const long long q0 = (long long)unit * 256 + lane;
+  int qr[4], qc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const long long q = q0 + 64 * i;
+    live[i] = q < nb2;
+    h[i] = 0.f;
+    qr[i] = (int)(q / Nb);
+    qc[i] = (int)(q - (long long)qr[i] * Nb);
+  }
+  for (int f = 0; f < F; ++f) {   // the four pixels' loads in flight together
+    const int wr = win[2 * f], wc = win[2 * f + 1];
+    float a[4], r[4];
+    bool in[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int pr = qr[i] - wr, pc = qc[i] - wc;
+      in[i] = live[i] && pr >= 0 && pr < Nd && pc >= 0 && pc < Nd;
+      const long long p = in[i] ? (long long)pr * Nd + pc : 0;
+      a[i] = flat[p];
+      r[i] = resid[(long long)f * npix + p];
     }
-    float* g = G + (long long)(Q * qr) * ldg;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (in[i]) h[i] += a[i] * r[i];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (!live[i]) continue;
+    float* g = G + (long long)(Q * qr[i]) * ldg;
     for (int a = 0; a < Q; ++a)
       for (int b = 0; b < Q; ++b)
-        g[(long long)a * ldg + fcol(Q * qc + b, fh, fs)] = intrapixel ? h * intrapixel[a * Q + b] : h;
+        g[(long long)a * ldg + fcol(Q * qc[i] + b, fh, fs)] = intrapixel ? h[i] * intrapixel[a * Q + b] : h[i];
   }
-  for (int s = 0; s < S; ++s) {
-    double v = q < nb2 ? (double)h * (double)bs[(long long)s * nb2 + q] : 0.0;
+  for (int s0 = 0; s0 < S; s0 += 4) {   // four stars' loads in flight
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double t = 0.0;
-      for (int w = 0; w < kSeedThreads / 64; ++w) t += sh[w];
-      flux[(long long)s * gridDim.x + blockIdx.x] = t;
-    }
-    __syncthreads();
+    for (int k = 0; k < 4; ++k)
+      if (s0 + k < S) {
+        const float* b = bs + (long long)(s0 + k) * nb2 + q0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[k] += live[i] ? (double)h[i] * (double)b[64 * i] : 0.0;
+      }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = wave_total(v[k]);
+    if (lane == 63)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (s0 + k < S) flux[(long long)(s0 + k) * nblk + unit] = v[k];
   }
 }
 
@@ -1026,9 +1189,10 @@ hipError_t launch_window(dlx_plan* p, const float* flat, float* binned, float* m
 hipError_t launch_seed_gather(dlx_plan* p, const float* flat, const float* resid, const float* intrapixel,
                               hipStream_t st) {
   p->flux_blocks = p->seed_blocks;
-  hipLaunchKernelGGL(seed_gather_kernel, dim3(p->seed_blocks), dim3(kSeedThreads), 0, st, resid, flat, intrapixel,
-                     p->d_bs, p->d_win, p->F_img, p->Nd_img, p->Nd, p->Q, p->S, p->ldNo, p->ghNo(), p->gsNo(), p->d_G,
-                     p->d_flux);
+  static_assert(kSeedThreads == 256, "a wave of seed_gather_kernel covers one seed block");
+  hipLaunchKernelGGL(seed_gather_kernel, dim3((p->seed_blocks + 3) / 4), dim3(kSeedThreads), 0, st, resid, flat,
+                     intrapixel, p->d_bs, p->d_win, p->F_img, p->Nd_img, p->Nd, p->Q, p->S, p->ldNo, p->ghNo(),
+                     p->gsNo(), p->d_G, p->seed_blocks, p->d_flux);
   return hipGetLastError();
 }
 
@@ -1058,6 +1222,24 @@ hipError_t launch_kgrad(dlx_plan* p, int f0, int nf, const float* sources, const
 
 int loss_block_count(long long npix) { return (int)((npix + kLossThreads - 1) / kLossThreads); }
 
+// Whether the frames are shared out over the waves of a block: where one wave per 64 pixels gives a SIMD
+// fewer than four waves. (With 1024 blocks or more one wave runs its frames faster: 16 frames of 512^2 pixels
+// 25 us against 26 to 35, 5 of 1024^2 31 against 45, 4 of 1024^2 with the seed 55 against 58.)
+bool split_frames(int nf, int nb) { return nf > 1 && nb < 1024; }
+
+// The loss terms alone: one frame, or several shared out over the waves of a block.
+void launch_loss_terms(int f0, int nf, long long npix, const float* model, const float* binned, const float* data,
+                       const float* flat, int kind, double mu, double inv_s2, float* r, double* gflat, int accumulate,
+                       double* blk, int* status, hipStream_t st) {
+  const dim3 grid(loss_block_count(npix));
+  if (!split_frames(nf, grid.x))
+    hipLaunchKernelGGL(loss_kernel<false>, grid, dim3(kLossThreads), 0, st, model, binned, data, flat, f0, f0 + nf, npix,
+                       kind, mu, inv_s2, r, gflat, accumulate, blk, status, SeedOut{});
+  else
+    hipLaunchKernelGGL((loss_frames_kernel<false, 0>), grid, dim3(64 * std::min(nf, kFrameWaves)), 0, st, model, binned,
+                       data, flat, f0, f0 + nf, npix, kind, mu, inv_s2, r, gflat, accumulate, blk, status, SeedOut{});
+}
+
 // Loss terms of frames [f0, f0 + nf); block partials at slot `chunk`. The
 // loss itself is summed over the slots by launch_loss_final or the finalize
 // kernel. With seed_intrapixel_or_none non-null (pointing at the intra-pixel
@@ -1075,11 +1257,26 @@ hipError_t launch_loss(dlx_plan* p, int f0, int nf, int chunk, const float* mode
     p->flux_blocks = nb;
     const SeedOut so{*seed_intrapixel_or_none, kstride(p), p->d_bs, p->Q, p->Nd, p->S, p->ldNo, p->ghNo(), p->gsNo(),
                      p->g_by_frame(), p->d_G, p->d_flux};
-    hipLaunchKernelGGL(loss_kernel<true>, dim3(nb), dim3(kLossThreads), 0, st, model, binned, data, flat, f0, f0 + nf,
-                       npix, kind, mu, inv_s2, r, gflat, chunk > 0 ? 1 : 0, blk, p->d_status, so);
+    if (!split_frames(nf, nb)) {
+      hipLaunchKernelGGL(loss_kernel<true>, dim3(nb), dim3(kLossThreads), 0, st, model, binned, data, flat, f0, f0 + nf,
+                         npix, kind, mu, inv_s2, r, gflat, chunk > 0 ? 1 : 0, blk, p->d_status, so);
+      return hipGetLastError();
+    }
+#define DLX_LOSS_FRAMES(QT)                                                                                        \
+  hipLaunchKernelGGL((loss_frames_kernel<true, QT>), dim3(nb), dim3(64 * std::min(nf, kFrameWaves)), 0, st, model,        \
+                     binned, data, flat, f0, f0 + nf, npix, kind, mu, inv_s2, r, gflat, chunk > 0 ? 1 : 0, blk,    \
+                     p->d_status, so)
+    switch ((long long)p->No * p->ldNo < (1LL << 31) ? p->Q : 0) {
+      case 1: DLX_LOSS_FRAMES(1); break;
+      case 2: DLX_LOSS_FRAMES(2); break;
+      case 3: DLX_LOSS_FRAMES(3); break;
+      case 4: DLX_LOSS_FRAMES(4); break;
+      default: DLX_LOSS_FRAMES(0); break;
+    }
+#undef DLX_LOSS_FRAMES
   } else {
-    hipLaunchKernelGGL(loss_kernel<false>, dim3(nb), dim3(kLossThreads), 0, st, model, binned, data, flat, f0,
-                       f0 + nf, npix, kind, mu, inv_s2, r, gflat, chunk > 0 ? 1 : 0, blk, p->d_status, SeedOut{});
+    launch_loss_terms(f0, nf, npix, model, binned, data, flat, kind, mu, inv_s2, r, gflat, chunk > 0 ? 1 : 0, blk,
+                      p->d_status, st);
   }
   return hipGetLastError();
 }
@@ -1144,8 +1341,8 @@ hipError_t launch_loss_plain(int nf, long long npix, const float* model, const f
                              const float* flat, int kind, double mu, double sigma, float* r, double* gflat,
                              double* blk, int* status, double* loss, hipStream_t st) {
   const int nb = loss_block_count(npix);
-  hipLaunchKernelGGL(loss_kernel<false>, dim3(nb), dim3(kLossThreads), 0, st, model, binned, data, flat, 0, nf, npix,
-                     kind, mu, 1.0 / (sigma * sigma), r, gflat, 0, blk, status, SeedOut{});
+  launch_loss_terms(0, nf, npix, model, binned, data, flat, kind, mu, 1.0 / (sigma * sigma), r, gflat, 0, blk, status,
+                    st);
   hipLaunchKernelGGL(final_sum_kernel, dim3(1), dim3(1024), 0, st, blk, nb, loss);
   return hipGetLastError();
 }
