@@ -1257,9 +1257,9 @@ constexpr double kTableBeta = 20.0;   // interpolation error about exp(-beta)
 
 // The table's pitch, taps and sizes for a problem, or false where one transform pair per star, frame and
 // wavelength is the cheaper form. A finer pitch (h16 up) needs fewer taps but more samples to transform;
-// the estimate weighs the folded products at their measured rate (85 TFLOP/s executed, after 15 us a launch; 120 on a table, which
-// leaves out the rows and columns no star reaches) against the FP64 matrix
-// instructions of the interpolation and its adjoint (64 cycles a SIMD each, times 2.3 and 2.2 to 2.6
+// the estimate weighs the folded products at their measured rate (85 TFLOP/s executed, after 15 us a
+// launch; 120 on a table, which leaves out the rows and columns no star reaches) against the FP64 matrix
+// instructions of the interpolation and its adjoint (64 cycles of a SIMD each, times 1.7 and 1.8 to 2.0
 // measured) and the passes over memory. (512 pupil, 768 focal samples, 32 wavelengths: 128 stars 2297 us at
 // h16 = 10, 2117 at 12, 2384 at 14; 24 stars 1038 at 9, 1088 at 12.)
 constexpr int kAdjointWgs = 2048;
@@ -1298,7 +1298,7 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
     const double adj = std::min(n / 32, own / 32 + 1) * std::min(std::ceil(n / cols), own / cols + 1) * waves * 2 *
                        quads * (std::ceil(((cols + K - 1) / h16 + 1) / waves) + 1);
     const double est = 4.0 * L * (n * Ni * Ni + n * n * Ni) / 120e6 + 60.0 + L * n * n * 8.0 / 3e6 +
-                       nfs * (2.3 * fwd + (table_adjoint_pair(h16, K) ? 2.2 : 2.6) * adj) * 64.0 / (1024 * 2400.0) +
+                       nfs * (1.7 * fwd + (table_adjoint_pair(h16, K) ? 1.8 : 2.0) * adj) * 64.0 / (1024 * 2400.0) +
                        nfs * No * No * 12.0 / 3e6 + 40.0;
     if (est >= least) continue;
     least = est;

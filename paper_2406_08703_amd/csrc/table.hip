@@ -11,6 +11,7 @@
 #include <cmath>
 
 #include "dlx_internal.h"
+#include "wave.h"
 
 namespace dlx {
 namespace {
@@ -174,18 +175,57 @@ __device__ __forceinline__ void stencil_weights(double* cf, const TableArgs& t) 
     cf[n] = ((n & 1) ? -1.0 : 1.0) / (double)n * window((double)n, t.W, t.beta);
 }
 
+// As products with the banded matrix of the stencil (FP64 matrix instructions, 16 x 16 samples per wave and
+// direction): the 2 W loads and products per sample of the plain sum took 174 us for 2112^2 samples and 64
+// taps, about 55 us here (18 us of matrix instructions).
 __global__ __launch_bounds__(256) void table_slope_kernel(const TableArgs t) {
-  __shared__ double cf[kMaxHalfTaps + 1];
-  stencil_weights(cf, t);
+  constexpr int kMid = 96;
+  __shared__ double s[2 * kMid];   // s[d + kMid]: weight of the sample d to the right of (or below) the result
+  const int H = t.W / 2;
+  if (threadIdx.x < 2 * kMid) {
+    const int d = (int)threadIdx.x - kMid, n = d < 0 ? -d : d;
+    const double v = n == 0 || n > H ? 0.0 : ((n & 1) ? -1.0 : 1.0) / (double)n * window((double)n, t.W, t.beta);
+    s[threadIdx.x] = d < 0 ? v : -v;
+  }
   __syncthreads();
-  const int lo = t.range[0], n = t.Nt - 2 * lo, hi = t.Nt - lo - 1;
-  const long long total = (long long)n * n;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
-    const int r = lo + (int)(i / n), c = lo + (int)(i % n);
-    double dx, dy;
-    stencil(cf, t.W / 2, r, c, lo, hi, [&](int y, int x) { return t.I[(long long)y * t.Nt + x]; }, dx, dy);
-    t.Ix[(long long)r * t.Nt + c] = (float)dx;
-    t.Iy[(long long)r * t.Nt + c] = (float)dy;
+  const int lane = threadIdx.x & 63, wave = wave_id(), n = lane & 15, g = lane >> 4;
+  const int lo = t.range[0], hi = t.Nt - lo - 1, side = (t.Nt - 2 * lo) / 32;
+  const long long ld = t.Nt;
+  for (int tile = blockIdx.x; tile < side * side; tile += gridDim.x) {
+    const int R = lo + 32 * (tile / side) + 16 * (wave >> 1), C = lo + 32 * (tile % side) + 16 * (wave & 1);
+    d4 dx = d4{0.0, 0.0, 0.0, 0.0}, dy = d4{0.0, 0.0, 0.0, 0.0};
+    // along x: rows of I times the band; a lane's two samples 8 p + 2 g and the next are one product's term each
+    const double* row = t.I + (R + n) * ld;
+    const bool inside = C - H >= lo && C + H + 47 <= hi;
+    for (int p0 = 0; 8 * p0 < 16 + 2 * H; p0 += 4) {   // (four loads in flight; the weights are zero past the band)
+      d2 v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int c = C - H + 8 * (p0 + i) + 2 * g;
+        if (inside)
+          __builtin_memcpy(&v[i], row + c, sizeof v[i]);
+        else
+          v[i] = d2{row[iclamp(c, lo, hi)], row[iclamp(c + 1, lo, hi)]};
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = 8 * (p0 + i) + 2 * g - H - n + kMid;
+        dx = mfma_f64(v[i][0], s[k], dx);
+        dx = mfma_f64(v[i][1], s[k + 1], dx);
+      }
+    }
+    for (int p0 = 0; 4 * p0 < 16 + 2 * H; p0 += 8) {   // along y: the band times columns of I
+      double v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = t.I[iclamp(R - H + 4 * (p0 + i) + g, lo, hi) * ld + C + n];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) dy = mfma_f64(s[4 * (p0 + i) + g - H - n + kMid], v[i], dy);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      t.Ix[(R + 4 * r + g) * ld + C + n] = (float)dx[r];
+      t.Iy[(R + 4 * r + g) * ld + C + n] = (float)dy[r];
+    }
   }
 }
 
@@ -215,7 +255,10 @@ __device__ __forceinline__ void far_weights(const TableArgs& t, const float* src
 // product with the column weights (K / 4 instructions), whose output feeds the products with the row
 // weights of the NY blocks below each other. Bound by the FP64 matrix rate; the next rows' samples are
 // loaded while the current ones' products run, and the workgroups of one part of the focal grid, whatever
-// their star, follow each other on one XCD, whose L2 then holds that part of the table. KP = K / 8.
+// their star, follow each other on one XCD, whose L2 then holds that part of the table. The weights of a
+// product with four row groups are read together, and the path of far stars is kept small enough that three
+// waves fit a SIMD. 128 stars of 768^2 samples, 28 taps: 260 us (373 us with a read and a wait before each
+// product and two waves, 150 us of matrix instructions). KP = K / 8.
 template <int KP, int NY>
 __global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, const float* sources, int fs0, int nstar,
                                                           int nbx) {
@@ -231,52 +274,51 @@ __global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, 
   d4 acc[NY];
 #pragma unroll
   for (int y = 0; y < NY; ++y) acc[y] = d4{0.0, 0.0, 0.0, 0.0};
-
-  auto add = [&](auto pair, int jx, int jy) {
-    const int cx = jx + t.h16 * xb + 2 * g, ry = jy + t.h16 * yb0 + n;
-    const int rbs = (t.h16 * (ny - 1) + K + 15) / 16;
-    d2 w[KP], v[KP], nx[KP];
+  // block y's product with the 16 table rows that start `rel` rows into its window
+  auto add_rows = [&](int y, int rel, const d4& d) {
+    if (y >= ny || rel <= -16 || rel >= K) return;
+    double wr[4];   // read together: a read before each product would be waited for each time
 #pragma unroll
-    for (int p = 0; p < KP; ++p) w[p] = *reinterpret_cast<const d2*>(&wx[n * KS + kPadL + 8 * p + 2 * g]);
-    // the window leaves the samples in use only where a block has columns past the focal grid
-    const bool inside = cx - 2 * g >= lo && cx - 2 * g + K - 1 <= hi;
-    auto load = [&](int rb, d2* o) {
-      const int row = iclamp(ry + 16 * rb, lo, hi);
+    for (int r = 0; r < 4; ++r) wr[r] = wy[n * KS + kPadL + rel + 4 * r + g];
 #pragma unroll
-      for (int p = 0; p < KP; ++p) o[p] = pair(row, inside ? cx + 8 * p : iclamp(cx + 8 * p, lo, hi - 1));
-    };
-    load(0, v);
-    for (int rb = 0; rb < rbs; ++rb) {
-      if (rb + 1 < rbs) load(rb + 1, nx);
-      d4 d = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int p = 0; p < KP; ++p) {
-        d = mfma_f64(v[p][0], w[p][0], d);
-        d = mfma_f64(v[p][1], w[p][1], d);
-      }
-#pragma unroll
-      for (int y = 0; y < NY; ++y) {
-        const int rel = 16 * rb - t.h16 * y;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (y < ny && rel + 4 * r > -4 && rel + 4 * r < K)   // the block's window reaches these four rows
-            acc[y] = mfma_f64(wy[n * KS + kPadL + rel + 4 * r + g], d[r], acc[y]);
-      }
-#pragma unroll
-      for (int p = 0; p < KP; ++p) v[p] = nx[p];
-    }
+    for (int r = 0; r < 4; ++r)
+      if (rel + 4 * r > -4 && rel + 4 * r < K)   // the block's window reaches these four rows
+        acc[y] = mfma_f64(wr[r], d[r], acc[y]);
   };
 
   if (!t.far[fs]) {
     load_weights(t, fs, wx);
     __syncthreads();
-    if (xb < t.nb)
-      add([&](int r, int c) {
-        d2 v;
-        __builtin_memcpy(&v, t.I + (long long)r * t.Nt + c, sizeof v);
-        return v;
-      }, t.base[2 * fs], t.base[2 * fs + 1]);
-  } else {
+    if (xb < t.nb) {
+      const int cx = t.base[2 * fs] + t.h16 * xb + 2 * g, ry = t.base[2 * fs + 1] + t.h16 * yb0 + n;
+      const int rbs = (t.h16 * (ny - 1) + K + 15) / 16;
+      d2 w[KP], v[KP], nx[KP];
+#pragma unroll
+      for (int p = 0; p < KP; ++p) w[p] = *reinterpret_cast<const d2*>(&wx[n * KS + kPadL + 8 * p + 2 * g]);
+      // the window leaves the samples in use only where a block has columns past the focal grid
+      const bool inside = cx - 2 * g >= lo && cx - 2 * g + K - 1 <= hi;
+      auto load = [&](int rb, d2* o) {
+        const double* row = t.I + (long long)iclamp(ry + 16 * rb, lo, hi) * t.Nt;
+#pragma unroll
+        for (int p = 0; p < KP; ++p)
+          __builtin_memcpy(&o[p], row + (inside ? cx + 8 * p : iclamp(cx + 8 * p, lo, hi - 1)), sizeof(d2));
+      };
+      load(0, v);
+      for (int rb = 0; rb < rbs; ++rb) {
+        if (rb + 1 < rbs) load(rb + 1, nx);
+        d4 d = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int p = 0; p < KP; ++p) {
+          d = mfma_f64(v[p][0], w[p][0], d);
+          d = mfma_f64(v[p][1], w[p][1], d);
+        }
+#pragma unroll
+        for (int y = 0; y < NY; ++y) add_rows(y, 16 * rb - t.h16 * y, d);
+#pragma unroll
+        for (int p = 0; p < KP; ++p) v[p] = nx[p];
+      }
+    }
+  } else {   // one wavelength after the other, kept simple: no star of a sampled pupil's own field comes here
     for (int l = 0; l < t.L; ++l) {
       int jx, jy;
       __syncthreads();
@@ -284,11 +326,22 @@ __global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, 
       __syncthreads();
       const float* e = t.E + l * t.e_by_wl;
       const double w = (double)t.wl[l].w;
-      if (xb < t.nb)
-        add([&](int r, int c) {
-          const float* q = e + (long long)r * t.Nt + c;
-          return d2{w * power(q[0], q[t.e_plane]), w * power(q[1], q[t.e_plane + 1])};
-        }, jx, jy);
+      if (xb >= t.nb) continue;
+      const int cx = jx + t.h16 * xb + 2 * g;
+#pragma unroll
+      for (int y = 0; y < NY; ++y)
+#pragma unroll 1
+        for (int rb = 0; 16 * rb < K; ++rb) {
+          const long long row = (long long)iclamp(jy + t.h16 * (yb0 + y) + n + 16 * rb, lo, hi) * t.Nt;
+          d4 d = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+          for (int p = 0; p < KP; ++p) {
+            const float* q = e + row + iclamp(cx + 8 * p, lo, hi - 1);
+            d = mfma_f64(w * power(q[0], q[t.e_plane]), wx[n * KS + kPadL + 8 * p + 2 * g], d);
+            d = mfma_f64(w * power(q[1], q[t.e_plane + 1]), wx[n * KS + kPadL + 8 * p + 2 * g + 1], d);
+          }
+          add_rows(y, 16 * rb, d);
+        }
     }
   }
   float* o = t.planes + (long long)star * t.No * t.ldg;
@@ -305,27 +358,60 @@ __global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, 
 }
 
 // Binning of the star images (Section 3): per star bs = sum K I over a detector pixel, FP64, and
-// binned = sum_s phi_s bs, model = flat binned. One pixel of one frame per thread.
-__global__ __launch_bounds__(256) void table_bin_kernel(const TableArgs t, int Qn, int Nd, int f0, const float* sources,
+// binned = sum_s phi_s bs, model = flat binned. One pixel of one frame per thread, with the loads of several
+// stars in flight (QT: oversampling, 0 any). Bound by the images it reads: 63 us for 64 frames of 2 stars
+// (768^2 samples, 3 x 3 per pixel; 138 us one star and one sample after the other).
+template <int QT>
+__global__ __launch_bounds__(256) void table_bin_kernel(const TableArgs t, int Qr, int Nd, int f0, const float* sources,
                                                         const float* intrapixel, long long kst, const float* flat,
                                                         float* bs, float* binned, float* model) {
+  constexpr int Q2 = QT > 0 ? QT * QT : 1, STARS = QT == 0 ? 1 : QT == 1 ? 8 : QT == 4 ? 1 : 2;
+  const int Q = QT > 0 ? QT : Qr;
   const long long npix = (long long)Nd * Nd;
   const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
   if (p >= npix) return;
   const int fl = blockIdx.y, f = f0 + fl;
   const int pr = (int)(p / Nd), pc = (int)(p - (long long)pr * Nd);
   const float* kp = intrapixel ? intrapixel + p * kst : nullptr;
+  float kw[Q2];
+  if constexpr (QT > 0) {
+#pragma unroll
+    for (int i = 0; i < Q2; ++i) kw[i] = kp ? kp[i] : 1.f;
+  }
+  const long long star = (long long)t.No * t.ldg;
+  const float* e = t.planes + (long long)fl * t.S * star + (long long)(Q * pr) * t.ldg + Q * pc;
   double total = 0.0;
-  for (int s = 0; s < t.S; ++s) {
-    const float* e = t.planes + ((long long)fl * t.S + s) * t.No * t.ldg + (long long)(Qn * pr) * t.ldg + Qn * pc;
-    double v = 0.0;
-    for (int a = 0; a < Qn; ++a)
-      for (int b = 0; b < Qn; ++b) {
-        const double x = e[(long long)a * t.ldg + b];
-        v = kp ? fma(x, (double)kp[a * Qn + b], v) : v + x;
+  for (int s0 = 0; s0 < t.S; s0 += STARS) {
+    double v[STARS];
+    if constexpr (QT > 0) {
+      float x[STARS][Q2];
+#pragma unroll
+      for (int k = 0; k < STARS; ++k) {
+        const float* es = e + (long long)min(s0 + k, t.S - 1) * star;   // (past the last star: read again, unused)
+#pragma unroll
+        for (int i = 0; i < Q2; ++i) x[k][i] = es[(long long)(i / QT) * t.ldg + i % QT];
       }
-    bs[((long long)fl * t.S + s) * npix + p] = (float)v;
-    total = fma((double)sources[((long long)f * t.S + s) * 3 + 2], v, total);
+#pragma unroll
+      for (int k = 0; k < STARS; ++k) {
+        v[k] = 0.0;
+#pragma unroll
+        for (int i = 0; i < Q2; ++i)
+          v[k] = intrapixel ? fma((double)x[k][i], (double)kw[i], v[k]) : v[k] + (double)x[k][i];
+      }
+    } else {
+      v[0] = 0.0;
+      for (int a = 0; a < Q; ++a)
+        for (int b = 0; b < Q; ++b) {
+          const double x = e[(long long)s0 * star + (long long)a * t.ldg + b];
+          v[0] = kp ? fma(x, (double)kp[a * Q + b], v[0]) : v[0] + x;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < STARS; ++k)
+      if (s0 + k < t.S) {
+        bs[((long long)fl * t.S + s0 + k) * npix + p] = (float)v[k];
+        total = fma((double)sources[((long long)f * t.S + s0 + k) * 3 + 2], v[k], total);
+      }
   }
   const float bv = (float)total;
   if (binned) binned[(long long)f * npix + p] = bv;
@@ -342,7 +428,7 @@ __global__ __launch_bounds__(256) void table_bin_kernel(const TableArgs t, int Q
 // groups of four focal rows or columns whose taps reach a tile are multiplied. (G holds whole blocks of 16
 // rows and columns, zero past the focal grid, so nothing is masked.) The FP64 matrix rate bounds it, with
 // two workgroups per CU at about half of it: G comes kAdjRows blocks at a time, one step ahead, and the
-// next star's weights during the current star. 128 stars of 768 focal samples onto 832: 520 us (1115 us
+// next star's weights during the current star. 128 stars of 768 focal samples onto 832: 480 us (1115 us
 // for 32 x 32 samples per wave, each forming its own V from G without a step ahead).
 constexpr int kAdjRows = 2;   // blocks of focal rows loaded at a time
 constexpr int kAdjLds = 150 << 10;
@@ -351,25 +437,6 @@ constexpr int kAdjLds = 150 << 10;
 int adjoint_blocks(int waves, int h16, int K) { return (16 * waves + K - 2) / h16 + 1; }
 size_t adjoint_lds(int waves, int h16, int K) {
   return sizeof(double) * (2 * 16 * wrow(K) + (size_t)adjoint_blocks(waves, h16, K) * 2 * 4 * 64);
-}
-
-// v moved by one DPP step (no source: 0), for the sums over a wave
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
-  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
-  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
-  return v + __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
-}
-
-// Sum over the 64 lanes, valid in lane 63.
-__device__ __forceinline__ double wave_total(double v) {
-  v = dpp_add<0x111>(v);   // row_shr:1
-  v = dpp_add<0x112>(v);   // row_shr:2
-  v = dpp_add<0x114>(v);   // row_shr:4
-  v = dpp_add<0x118>(v);   // row_shr:8
-  v = dpp_add<0x142>(v);   // row_bcast:15
-  return dpp_add<0x143>(v);   // row_bcast:31
 }
 
 template <int WAVES>
@@ -464,13 +531,19 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 2) void table_adjoint_kernel(co
 #pragma unroll
           for (int i = 0; i < kAdjRows; ++i) {
             const int rel = R0 - (jy + h16 * (yc + i));   // the tile's first row in the block's window
+            if (yc + i > yb1) continue;
+            const int r0 = min(max(rel, -16), K), r1 = min(max(rel + 16, -16), K);   // (unused past either end)
+            double w0[4], w1[4];   // read together: a read before each product would be waited for each time
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-              if (yc + i > yb1) continue;
+              w0[k] = wy[4 * k * KS + r0];
+              w1[k] = wy[4 * k * KS + r1];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
               const double a = (double)v[4 * i + k];
-              if (first_tap(k) <= rel + 15 && last_tap(k) >= rel) acc[0] = mfma_f64(a, wy[4 * k * KS + rel], acc[0]);
-              if (first_tap(k) <= rel + 31 && last_tap(k) >= rel + 16)
-                acc[1] = mfma_f64(a, wy[4 * k * KS + rel + 16], acc[1]);
+              if (first_tap(k) <= rel + 15 && last_tap(k) >= rel) acc[0] = mfma_f64(a, w0[k], acc[0]);
+              if (first_tap(k) <= rel + 31 && last_tap(k) >= rel + 16) acc[1] = mfma_f64(a, w1[k], acc[1]);
             }
           }
         }
@@ -764,14 +837,16 @@ hipError_t launch_table_image(const TableArgs& t, int n_reg, bool derivatives, h
   if (!derivatives)
     hipLaunchKernelGGL(table_image_kernel, dim3(blocks(n / 4, 256, 1u << 20)), dim3(256), 0, st, t);
   else
-    hipLaunchKernelGGL(table_slope_kernel, dim3(blocks(n, 256, 1u << 20)), dim3(256), 0, st, t);
+    hipLaunchKernelGGL(table_slope_kernel, dim3(blocks(n / 4, 256, 1u << 20)), dim3(256), 0, st, t);
   return hipGetLastError();
 }
 
 hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, int nf, hipStream_t st) {
   const int nbx = (t.nb + 3) / 4, nstar = nf * t.S;
-  // eight blocks of rows per wave (the fewest instructions) where that still fills the chip twice
-  const int ny = (long long)nbx * ((t.nb + 7) / 8) * nstar >= 1024 ? 8 : (long long)nbx * ((t.nb + 3) / 4) * nstar >= 512 ? 4 : 1;
+  // eight blocks of rows per wave (the fewest instructions) where that still gives a CU four workgroups, four
+  // where it gives one (12 stars of 384^2 samples: 20 us, 33 us with one block)
+  const long long wg8 = (long long)nbx * ((t.nb + 7) / 8) * nstar, wg4 = (long long)nbx * ((t.nb + 3) / 4) * nstar;
+  const int ny = wg8 >= 1024 ? 8 : wg4 >= 256 ? 4 : 1;
   const dim3 grid((unsigned)(nbx * ((t.nb + ny - 1) / ny) * nstar)), blk(256);
 #define DLX_SHIFT(KP)                                                                                              \
   case KP:                                                                                                         \
@@ -801,8 +876,18 @@ hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, 
 hipError_t launch_table_bin(const TableArgs& t, int Q, int Nd, int f0, int nf, const float* sources,
                             const float* intrapixel, long long kst, const float* flat, float* bs, float* binned,
                             float* model, hipStream_t st) {
-  hipLaunchKernelGGL(table_bin_kernel, dim3(blocks((long long)Nd * Nd, 256, 1u << 30), nf), dim3(256), 0, st, t, Q, Nd,
-                     f0, sources, intrapixel, kst, flat, bs, binned, model);
+  const dim3 grid(blocks((long long)Nd * Nd, 256, 1u << 30), nf), blk(256);
+#define DLX_TABLE_BIN(QT)                                                                                          \
+  hipLaunchKernelGGL(table_bin_kernel<QT>, grid, blk, 0, st, t, Q, Nd, f0, sources, intrapixel, kst, flat, bs, binned, \
+                     model)
+  switch (Q) {
+    case 1: DLX_TABLE_BIN(1); break;
+    case 2: DLX_TABLE_BIN(2); break;
+    case 3: DLX_TABLE_BIN(3); break;
+    case 4: DLX_TABLE_BIN(4); break;
+    default: DLX_TABLE_BIN(0); break;
+  }
+#undef DLX_TABLE_BIN
   return hipGetLastError();
 }
 

@@ -206,3 +206,25 @@ def test_table_reports_a_position_that_is_not_finite():
     assert good["status"] == 0
     from tests.test_gpu_parity import compare
     compare(good, reference("q4", "poisson"), q=4)
+
+
+@pytest.mark.parametrize("q,nd,pixel,n_sources,L", [(1, 150, 8.0, 3, 240), (1, 150, 8.0, 9, 90), (2, 61, 70.0, 5, 160),
+                                                    (5, 23, 150.0, 24, 36)])
+def test_table_bins_every_oversampling_and_star_count(q, nd, pixel, n_sources, L):
+    """Star counts below, at and past what the binning loads at once (8 and 2 for Q = 1 and 2; one for Q = 5)."""
+    from tests.test_gpu_dither import oracle_big, plan_for, run
+    from tests.test_gpu_parity import compare
+    print(f"table bins q={q} stars={n_sources}", flush=True)
+    w = make_dithered_workload(n_pupil=88, n_det=nd, oversample=q, margin=3, n_sources=n_sources, det_pixel_mas=pixel,
+                               wavelengths=tuple(np.linspace(545e-9, 645e-9, L)), dithers=((0, 0), (3, -2), (-3, 1)),
+                               flux=(1e6, 1e7))
+    big = oracle_big(w)
+    w = w.with_data(O.forward_dithered(big, w.coeffs_true, None, w.sources_true, w.flat_true, w.dithers, w.margin)[1])
+    p = w.eval_params()
+    ref = O.value_and_grad_dithered(big, p["coeffs"], None, p["sources"], p["flat"], w.data, w.dithers, w.margin,
+                                    "poisson", w.prior_mu, w.prior_sigma)
+    plan = plan_for(w)
+    n, got = transforms(plan, lambda: run(w, plan, True))
+    plan.close()
+    assert n == L
+    compare(got, ref, q=q, kind="poisson")
