@@ -1341,16 +1341,22 @@ dlx_status create_with_table(dlx_plan* p, const dlx_problem_desc& d, int flags) 
   const size_t most = std::min<size_t>(kDefaultChunkBudget / frame, 65535 / p->S);
   const int fc = (int)std::max<size_t>(1, std::min<size_t>(p->F, most));
   if (p->store_fields && fc < p->F) return DLX_ERR_UNSUPPORTED;
-  // Star groups of the adjoint: as few as give its workgroups about eight rounds of the chip, a multiple of
-  // the eight XCDs where one is near (the workgroups of a group share the seed weights of its stars, so a
-  // group that runs on one XCD reads them from its L2).
+  // Star groups of the adjoint, each of two stars or more (a workgroup's start and the sum of the groups'
+  // planes cost about half a star): as few as give its workgroups about eight rounds of the chip, and a
+  // multiple of the eight XCDs where one is near, as the workgroups of a group share the seed weights of its
+  // stars, which one XCD's L2 holds. (128 stars: 16 groups 498 us, 8 groups 584; 24 stars: 8 groups 166 us,
+  // 24 groups 183; 20 stars: 10 groups 199 us, 20 groups 208.)
   const int nwg = t.slots / t.waves, stars = fc * p->S;
-  t.per_group = std::max(1, stars / ceil_div(kAdjointWgs, nwg));
-  for (int per = t.per_group; 2 * per >= t.per_group && per > 0; --per)
-    if (ceil_div(stars, per) % 8 == 0) {
+  const int few = std::min(stars, std::max(2, stars / ceil_div(kAdjointWgs, nwg)));
+  t.per_group = few;
+  double off = 2.0;
+  for (int per = std::min(2, stars); per < 2 * few; ++per) {
+    const double ratio = per < few ? (double)few / per : (double)per / few;
+    if (ceil_div(stars, per) % 8 == 0 && ratio < off) {
+      off = ratio;
       t.per_group = per;
-      break;
     }
+  }
   t.groups = ceil_div(stars, t.per_group);
   // the table for stars anywhere in the pupil grid's own field: fields, seed weights, transform buffers and
   // matrices (a third of the free memory at most, else the other form)
