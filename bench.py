@@ -43,7 +43,7 @@ WORKLOADS = {
 }
 
 
-def measured_traffic(config, precision, stage, tile, fold=True):
+def measured_traffic(config, precision, stage, tile, fold=True, table=0):
     """HBM bytes per launch of `stage`'s kernel at `tile` (WM, WN) from the committed rocprofv3 summary.
 
     FETCH_SIZE and WRITE_SIZE (KiB per dispatch) are scaled by what the same
@@ -66,7 +66,8 @@ def measured_traffic(config, precision, stage, tile, fold=True):
     if fields.get("kernel_source_sha256") != hashlib.sha256(open(src, "rb").read()).hexdigest():
         return None
     kind = {"F1": 0, "F2": 1, "B3": 3, "B4": 4}[stage]
-    name = f"{kernel_name(fold)}<{kind},{tile[0]},{tile[1]},{0 if precision == 'fp32' else 1}>"
+    prec = "" if table else ",0" if precision == "fp32" else ",1"
+    name = f"{kernel_name(fold, table)}<{kind},{tile[0]},{tile[1]}{prec}>"
     if name not in stages:
         return None
     f, w = stages[name]
@@ -93,16 +94,18 @@ def step_stats(per):
     return {"median": round(statistics.median(per), 5), "min": round(min(per), 5), "max": round(max(per), 5)}
 
 
-def stage_bytes(P, stage):
+def stage_bytes(P, stage, samples=0):
     """Algorithmic HBM bytes per evaluation of the memory-bound stages of dlx_eval (each array
-    read or written once; FP32 unless noted)."""
+    read or written once; FP32 unless noted). `samples`: per side of a shared PSF table."""
     ni, no, nd, F, S, L = P.n_pupil, P.n_focal, P.n_det, P.n_frames, P.n_sources, P.n_wavelengths
     nz, nmap, npsf = P.n_zernike, P.n_map, P.n_psf
     return {
         # OPD (Z, A read), pupil field P0 per wavelength (planar complex), tilt vectors per PSF
-        "PREP": 4.0 * (nz + 1) * ni * ni + 8.0 * L * ni * ni + 16.0 * npsf * ni + 4.0 * nmap * ni,
-        # E read once; per-star binned images, binned and model written
-        "BIN": 8.0 * npsf * no * no + 4.0 * F * (S + 2) * nd * nd,
+        "PREP": 4.0 * (nz + 1) * ni * ni + 8.0 * L * ni * ni + (0 if samples else 16.0 * npsf * ni) + 4.0 * nmap * ni,
+        # E read once (a table's: then its FP64 image written and read, the star images written and read);
+        # per-star binned images, binned and model written
+        "BIN": (8.0 * L * samples ** 2 + 16.0 * samples ** 2 + 8.0 * F * S * no * no if samples else
+                8.0 * npsf * no * no) + 4.0 * F * (S + 2) * nd * nd,
         # model, binned, data, per-star binned read; r written; seed weights G written
         "LOSS": 4.0 * F * (4 + S) * nd * nd + 4.0 * F * no * no + 12.0 * nd * nd,
         # Zernike basis re-read for the projection, dL/dOPD (FP64) written and read
@@ -110,29 +113,31 @@ def stage_bytes(P, stage):
     }.get(stage)
 
 
-def kernel_name(fold):
-    return "fgemm_kernel" if fold else "cgemm_kernel"
+def kernel_name(fold, table=0):
+    return "fgemm_table_kernel" if table else "fgemm_kernel" if fold else "cgemm_kernel"
 
 
-def hbm_bytes(P, stage, table):
+def hbm_bytes(P, stage, table, samples=0):
     """stage_bytes of a timed stage; the fused evaluation bins and forms the loss in one launch
     (stage BIN, no LOSS stage), which then moves the bytes of both."""
-    b = stage_bytes(P, stage)
+    b = stage_bytes(P, stage, samples)
     if stage == "BIN" and "LOSS" not in table:
         b += stage_bytes(P, "LOSS")
     return b
 
 
-def gemm_roofline(P, gemm, tiles, precision, config, fold=True):
-    """Roofline entry of the dominant MFT stage from its HIP-event launch times."""
+def gemm_roofline(P, gemm, tiles, precision, config, fold=True, table=0):
+    """Roofline entry of the dominant MFT stage from its HIP-event launch times. `table`: samples per
+    side of a shared PSF table (its products are FP32 in both precisions)."""
+    split = precision != "fp32" and not table
     dom = max(gemm, key=lambda k: gemm[k]["ms_per_step"])
     dv = gemm[dom]
-    flops_per_launch = stage_flops(P, dom, fold) * dv["psfs"] / dv["launches"]
+    flops_per_launch = stage_flops(P, dom, fold, table) * dv["psfs"] / dv["launches"]
     achieved = flops_per_launch / (dv["avg_launch_ms"] * 1e-3) / 1e12
     tile = tiles[dom]
-    kname = (f"{kernel_name(fold)}<{dict(F1=0, F2=1, B3=3, B4=4)[dom]}, {tile[0] // 32}, {tile[1] // 32}, "
-             f"{0 if precision == 'fp32' else 1}> ({dom})")
-    if precision == "fp32":
+    kname = (f"{kernel_name(fold, table)}<{dict(F1=0, F2=1, B3=3, B4=4)[dom]}, {tile[0] // 32}, {tile[1] // 32}"
+             f"{'' if table else ', 1' if split else ', 0'}> ({dom})")
+    if not split:
         roofline = {"bound": "mfma", "kernel": kname, "achieved": round(achieved, 3),
                     "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / FP32_MFMA_PEAK_TFLOPS, 4),
                     "traffic": None, "flops_per_launch": flops_per_launch,
@@ -145,15 +150,16 @@ def gemm_roofline(P, gemm, tiles, precision, config, fold=True):
                     "traffic": None, "flops_per_launch": 3.0 * flops_per_launch,
                     "avg_launch_ms": round(dv["avg_launch_ms"], 5), "fp32_equivalent_tflops": round(achieved, 3),
                     "frac_of_fp32_mfma_peak": round(achieved / FP32_MFMA_PEAK_TFLOPS, 4)}
-    roofline["traffic"] = measured_traffic(config, precision, dom, (tile[0] // 32, tile[1] // 32), fold)
+    roofline["traffic"] = measured_traffic(config, precision, dom, (tile[0] // 32, tile[1] // 32), fold, table)
     return roofline
 
 
-def stage_flops(P, stage, fold=True):
+def stage_flops(P, stage, fold=True, table=0):
     """Real flops one PSF's product of `stage` executes on the matrix cores (a complex
     multiply-add is four real ones). Dense: the full complex product. Folded: four real
-    products over half the DFT rows and half the depth, h = ceil(N / 2)."""
-    ni, no = P.n_pupil, P.n_focal
+    products over half the DFT rows and half the depth, h = ceil(N / 2). On a PSF table (`table`
+    samples per side) one wavelength's product takes the place of every PSF's of that wavelength."""
+    ni, no = P.n_pupil, table or P.n_focal
     if not fold:
         return {"F1": 8.0 * no * ni * ni, "F2": 8.0 * no * no * ni,
                 "B3": 8.0 * ni * no * no, "B4": 8.0 * ni * ni * no}.get(stage)
@@ -162,9 +168,14 @@ def stage_flops(P, stage, fold=True):
             "B3": 8.0 * hi * no * ho, "B4": 8.0 * hi * ni * ho}.get(stage)
 
 
-def mft_executed_flops(P, fold=True):
-    """Flops one PSF's forward + adjoint MFT executes (the four stages)."""
-    return sum(stage_flops(P, k, fold) for k in ("F1", "F2", "B3", "B4"))
+def mft_executed_flops(P, fold=True, table=0):
+    """Flops of one forward + adjoint MFT (the four stages): of a PSF, or of a table's wavelength."""
+    return sum(stage_flops(P, k, fold, table) for k in ("F1", "F2", "B3", "B4"))
+
+
+def mft_runs(P, table=0):
+    """MFT pairs per evaluation: one per PSF, or one per wavelength on a table."""
+    return P.n_wavelengths if table else P.n_psf
 
 
 def frame_index(P):
@@ -347,11 +358,14 @@ def main():
     evals = n_psf * args.steps / t1
     F_mft = P.mft_flops()
     # algorithmic: the dense two-sided MFT count, forward + adjoint; executed: what the products run
-    # (the fused evaluation reuses E, so forward + adjoint only; the fold executes a quarter)
+    # (the fused evaluation reuses E, so forward + adjoint only; the fold executes a quarter;
     tf_alg = 2 * F_mft * n_psf / (ms_step * 1e-3) / 1e12
-    tf_exec = mft_executed_flops(P, fold) * n_psf / (ms_step * 1e-3) / 1e12
+    # with a shared PSF table the transforms run once per wavelength)
+    from paper_2406_08703_amd import dlx as C
+    samples = C.dlx_plan_table_samples(plan.plan)
+    tf_exec = mft_executed_flops(P, fold, samples) * mft_runs(P, samples) / (ms_step * 1e-3) / 1e12
     gemm = {k: v for k, v in table.items() if stage_flops(P, k)}
-    roofline = gemm_roofline(P, gemm, plan.tiles, args.precision, args.config, fold)
+    roofline = gemm_roofline(P, gemm, plan.tiles, args.precision, args.config, fold, samples)
     gemm_ms = sum(v["ms_per_step"] for v in gemm.values())
     all_ms = sum(v["ms_per_step"] for v in table.values())
 
@@ -368,7 +382,8 @@ def main():
                  "speedup_vs_fp32": round(ms_step / ms_b, 3),
                  "stage_ms_per_step": {k: round(v["ms_per_step"], 5) for k, v in bf["table"].items()},
                  "tiles": {k: f"{v[0]}x{v[1]}" for k, v in bf["plan"].tiles.items()},
-                 "roofline": gemm_roofline(P, gemm_b, bf["plan"].tiles, "bf16x3", args.config, fold),
+                 "roofline": gemm_roofline(P, gemm_b, bf["plan"].tiles, "bf16x3", args.config, fold,
+                                           C.dlx_plan_table_samples(bf["plan"].plan)),
                  "rel_err_vs_fp64": None}
 
     cpu, parity = None, None
@@ -491,7 +506,8 @@ def main():
                       "n_pupil": P.n_pupil, "n_focal": P.n_focal, "oversample": P.oversample,
                       "wavelengths": P.n_wavelengths, "sources": P.n_sources, "frames": P.n_frames,
                       "zernikes": P.n_zernike, "flat_pixels": P.n_det ** 2, "precision": args.precision},
-           "mft": "symmetric fold" if fold else "dense complex products",
+           "mft": ("symmetric fold" if fold else "dense complex products") +
+                  (f", one PSF table of {samples}^2 samples per wavelength" if samples else ""),
            "mft_tflops": {"algorithmic": round(tf_alg, 3), "executed": round(tf_exec, 3),
                           "algorithmic_over_fp32_mfma_peak": round(tf_alg / FP32_MFMA_PEAK_TFLOPS, 4),
                           "frac_fp32_mfma_peak_executed": round(tf_exec / FP32_MFMA_PEAK_TFLOPS, 4)},
@@ -500,9 +516,9 @@ def main():
            "tiles": {k: f"{v[0]}x{v[1]}" for k, v in plan.tiles.items()},
            "stage_ms_per_step": {k: round(v["ms_per_step"], 5) for k, v in table.items()},
            "gemm_share_of_step": round(gemm_ms / all_ms, 4) if all_ms else None,
-           "hbm_stages": {k: {"bytes_per_step": hbm_bytes(P, k, table),
-                              "GB/s": round(hbm_bytes(P, k, table) / (v["ms_per_step"] * 1e-3) / 1e9, 1),
-                              "frac_of_8TB/s": round(hbm_bytes(P, k, table) / (v["ms_per_step"] * 1e-3) / 1e9 /
+           "hbm_stages": {k: {"bytes_per_step": hbm_bytes(P, k, table, samples),
+                              "GB/s": round(hbm_bytes(P, k, table, samples) / (v["ms_per_step"] * 1e-3) / 1e9, 1),
+                              "frac_of_8TB/s": round(hbm_bytes(P, k, table, samples) / (v["ms_per_step"] * 1e-3) / 1e9 /
                                                      HBM_PEAK_GBS, 4)}
                           for k, v in table.items() if stage_bytes(P, k)},
            "roofline": roofline, "rel_err_vs_fp64": parity, "cpu_baseline": cpu, "bf16x3": split,
@@ -727,7 +743,8 @@ def bench_dither(args):
             C.dlx_plan_profile(plan.plan, False)
             gemm = {k: dict(ms_per_step=t / args.steps, launches=la, psfs=ps, avg_launch_ms=t / la)
                     for k, (t, la, ps) in st.items() if la and stage_flops(P, k)}
-            roof = gemm_roofline(P, gemm, plan.tiles, args.precision, "p0", not args.dense_mft)
+            roof = gemm_roofline(P, gemm, plan.tiles, args.precision, "p0", not args.dense_mft,
+                                 C.dlx_plan_table_samples(plan.plan))
             stages = {k: round(t / args.steps, 5) for k, (t, la, ps) in st.items() if la}
             del eb
         cap = CapturedEval(plan, c, None, s, fl, d, "poisson", w.prior_mu, w.prior_sigma)
@@ -739,11 +756,13 @@ def bench_dither(args):
         psfs = P.n_sources * P.n_wavelengths * (1 if dith else w.n_frames)
         no = P.n_focal if dith else P.oversample * w.n_det
         flops = 2.0 * 8.0 * no * P.n_pupil * (P.n_pupil + no) * psfs   # dense two-sided MFT count
-        hi_, ho_ = (P.n_pupil + 1) // 2, (no + 1) // 2
+        samples = C.dlx_plan_table_samples(plan.plan)
+        hi_, ne = (P.n_pupil + 1) // 2, samples or no
+        ho_, runs = (ne + 1) // 2, P.n_wavelengths if samples else psfs
         exec_flops = (flops if args.dense_mft else
-                      8.0 * (ho_ * P.n_pupil * hi_ + no * ho_ * hi_ + hi_ * no * ho_ + hi_ * P.n_pupil * ho_) * psfs)
+                      8.0 * (ho_ * P.n_pupil * hi_ + ne * ho_ * hi_ + hi_ * ne * ho_ + hi_ * P.n_pupil * ho_) * runs)
         results[mode] = dict(ms=wall * 1e3 / args.steps, per=per, psfs=psfs, flops=flops, exec_flops=exec_flops,
-                             loss=loss,
+                             loss=loss, samples=samples,
                              tiles=plan.tiles, roofline=roof, stages=stages)
         log(f"{mode}: {args.steps} replays in {wall:.4f} s ({psfs} PSFs of {no}x{no} per step)")
         cap = None
@@ -797,7 +816,8 @@ def bench_dither(args):
            "data": "synthetic",
            "config": {"workload": f"p0: {WORKLOADS['p0']}", "psf_per_step": r["psfs"], "frames": w.n_frames,
                       "precision": args.precision},
-           "mft": "dense complex products" if args.dense_mft else "symmetric fold",
+           "mft": ("dense complex products" if args.dense_mft else "symmetric fold") +
+                  (f", one PSF table of {r['samples']}^2 samples per wavelength" if r["samples"] else ""),
            "mft_tflops": {"algorithmic": round(r["flops"] / (ms * 1e-3) / 1e12, 3),
                           "executed": round(r["exec_flops"] / (ms * 1e-3) / 1e12, 3),
                           "algorithmic_over_fp32_mfma_peak": round(r["flops"] / (ms * 1e-3) / 1e12 /

@@ -234,6 +234,12 @@ int32_t dlx_plan_problems(const dlx_plan* plan);
  * k = F1, F2, B3, B4 (host int32_t[8]). */
 dlx_status dlx_plan_tiles(const dlx_plan* plan, int32_t* tiles);
 
+/* Samples per side of the shared PSF table that the plan's last evaluation used
+ * (see the note on the table above; its transforms run once per wavelength on
+ * that many focal samples), 0 for a plan without a table or with several
+ * problems. Waits for the plan's work; not for use during a capture. */
+dlx_status dlx_plan_table_samples(const dlx_plan* plan, int32_t* samples);
+
 /* Static pupil phase screen of one problem (Section 3, the optical layers: the
  * paper's system carries a fixed phase optic, the Toliman pupil's binary phase
  * plate, after the Zernike aperture). `screen` is a device array [Ni][Ni] of

@@ -1750,6 +1750,17 @@ dlx_status dlx_plan_tiles(const dlx_plan* p, int32_t* tiles) {
   return DLX_OK;
 }
 
+dlx_status dlx_plan_table_samples(const dlx_plan* p, int32_t* samples) {
+  if (!p || !samples) return DLX_ERR_INVALID_ARG;
+  *samples = 0;
+  if (!p->tab) return DLX_OK;
+  int range[2] = {0, 0};
+  if (hipDeviceSynchronize() != hipSuccess) return DLX_ERR_HIP;
+  if (hipMemcpy(range, p->ta.range, sizeof range, hipMemcpyDeviceToHost) != hipSuccess) return DLX_ERR_HIP;
+  *samples = p->ta.Nt - 2 * range[0];
+  return DLX_OK;
+}
+
 dlx_status dlx_plan_profile(dlx_plan* p, int32_t enable) {
   if (!p) return DLX_ERR_INVALID_ARG;
   if (p->multi()) {

@@ -38,7 +38,7 @@ DLX_FLAG_GROUPED = 32
 # Every symbol include/dlx.h declares.
 
 EXPORTS = ("dlx_validate", "dlx_plan_create", "dlx_plan_destroy", "dlx_plan_workspace_bytes", "dlx_plan_tiles",
-           "dlx_plan_sync",
+           "dlx_plan_table_samples", "dlx_plan_sync",
            "dlx_psf_forward", "dlx_loss_grad", "dlx_psf_backward", "dlx_eval", "dlx_graph_capture",
            "dlx_graph_launch", "dlx_plan_profile", "dlx_plan_stage_times", "dlx_status_string",
            "dlx_plan_offsets", "dlx_plan_problems", "dlx_plan_set_phase_screen", "dlx_loss_grad_noalloc")
@@ -109,6 +109,8 @@ def lib() -> ctypes.CDLL:
         L.dlx_plan_workspace_bytes.argtypes = [_vp]
         L.dlx_plan_tiles.restype = ctypes.c_int
         L.dlx_plan_tiles.argtypes = [_vp, _vp]
+        L.dlx_plan_table_samples.restype = ctypes.c_int
+        L.dlx_plan_table_samples.argtypes = [_vp, _vp]
         L.dlx_plan_sync.restype = ctypes.c_int
         L.dlx_plan_sync.argtypes = [_vp, _vp]
         L.dlx_psf_forward.restype = ctypes.c_int
@@ -214,6 +216,13 @@ def dlx_plan_tiles(plan: int) -> dict:
     t = (ctypes.c_int32 * 8)()
     _chk(lib().dlx_plan_tiles(_p(plan), ctypes.addressof(t)), "dlx_plan_tiles")
     return {k: (32 * t[2 * i], 32 * t[2 * i + 1]) for i, k in enumerate(("F1", "F2", "B3", "B4"))}
+
+
+def dlx_plan_table_samples(plan: int) -> int:
+    """Samples per side of the shared PSF table the last evaluation used (0: no table)."""
+    n = ctypes.c_int32()
+    _chk(lib().dlx_plan_table_samples(_p(plan), ctypes.addressof(n)), "dlx_plan_table_samples")
+    return n.value
 
 
 def dlx_plan_set_phase_screen(plan: int, problem: int, screen, stream: int = 0) -> None:
