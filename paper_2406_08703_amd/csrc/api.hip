@@ -1292,7 +1292,6 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
     const int waves = table_adjoint_waves(h16, K);
     if (!waves) continue;
     const double n = n_reg, own = std::min(n, No * h + W), cols = 16.0 * waves;   // own: samples a star reaches
-    const double nwg = (n / 32) * std::ceil(n / cols);
     const double fwd = (std::ceil((7 * h16 + K) / 16.0) * K / 4 + 8.0 * (K / 4 + 1)) / 8 * nb * nb;
     const double quads = (17.0 + W + 3 * h) / (h16 / 4.0);   // groups of four focal rows that reach 16 samples
     const double adj = std::min(n / 32, own / 32 + 1) * std::min(std::ceil(n / cols), own / cols + 1) * waves * 2 *
@@ -1314,7 +1313,9 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
     t.L = p->L;
     t.S = p->S;
     t.nfs = p->F * p->S;
-    t.slots = waves * (int)std::min(nwg, 4096.0);
+    // (stars all over an enlarged plane, as integer dithers are for, use the table about twice as far)
+    const int sized = p->dither ? std::min(Nt, round_up((int)std::ceil(2.0 * No * h + 2 * W + 10), 64)) : n_reg;
+    t.slots = waves * std::min((sized / 32) * ceil_div(sized, 16 * waves), 4096);
     t.waves = waves;
     t.tau = tau;
     t.c0 = 0.5 * (Nt - 1) - 0.5 * (No - 1) * h;
@@ -1322,7 +1323,7 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
     t.half_min = 0.5 * lmin / p->dx;
     t.dx = p->dx;
     *best = t;
-    *best_reg = n_reg;
+    *best_reg = sized;
   }
   return found;
 }
