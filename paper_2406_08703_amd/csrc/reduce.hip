@@ -837,16 +837,19 @@ __global__ __launch_bounds__(kSeedThreads) void seed_gather_kernel(
 //   v[a][b] = h sum_s sum_l w_l phi_s |E_{f,s,l}[Q p_r + a][Q p_c + b]|^2,
 // summed over the block's pixels into part[(f nblk + block) Q^2 + a Q + b].
 // With one kernel per pixel (gpix non-null) the pixel sum is dropped: the block runs every frame
-// of the chunk (grid.y = 1) and writes gpix[p][a][b], or adds to it for a chunk after the first.
+// of the chunk (grid.y = 1) and writes gpix[p][a][b], or adds to it for a chunk after the first. Few blocks
+// of long loops: bound by the latency of its loads, so those of several wavelengths are issued together
+// (one kernel per pixel, 6 frames of 8 wavelengths, 100^2 pixels of 2 x 2 samples: 25 us one wavelength at a time,
+// 21 us so, 12 us in blocks of one wave).
 template <int QT>
 __global__ __launch_bounds__(kSeedThreads) void kgrad_kernel(const float* E, long long plane, long long by_psf, int ld, int f0, int S, int L,
                              int Nd, const float* sources, const WlInfo* wl, const float* flat, const float* resid,
                              const int* win, int F_img, int Nd_img, int fh, int fs, double* part, double* gpix,
                              int nf_pix, int accumulate) {
-  constexpr int Q2 = QT * QT;
+  constexpr int Q2 = QT * QT, LB = QT <= 2 ? 8 : QT == 3 ? 4 : 2;
   __shared__ double sh[Q2][kSeedThreads / 64];
   const long long npix = (long long)Nd * Nd;
-  const long long p = (long long)blockIdx.x * kSeedThreads + threadIdx.x;
+  const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;   // (64 threads with gpix)
   double acc[Q2];
 #pragma unroll
   for (int k = 0; k < Q2; ++k) acc[k] = 0.0;
@@ -874,17 +877,27 @@ __global__ __launch_bounds__(kSeedThreads) void kgrad_kernel(const float* E, lon
       for (int k = 0; k < Q2; ++k) v[k] = 0.0;
       for (int s = 0; s < S; ++s) {
         const float phi = sources[((long long)f * S + s) * 3 + 2];
-        for (int l = 0; l < L; ++l) {
-          const float* e = E + (((long long)fl * S + s) * L + l) * by_psf + (long long)(QT * pr) * ld;
-          const float wphi = wl[l].w * phi;
+        for (int l0 = 0; l0 < L; l0 += LB) {   // LB wavelengths' loads in flight
+          float er[LB][Q2], ei[LB][Q2];
 #pragma unroll
-          for (int a = 0; a < QT; ++a)
+          for (int i = 0; i < LB; ++i) {   // (past the last wavelength: read again, unused)
+            const float* e = E + (((long long)fl * S + s) * L + min(l0 + i, L - 1)) * by_psf + (long long)(QT * pr) * ld;
 #pragma unroll
-            for (int b = 0; b < QT; ++b) {
-              const int c = fcol(QT * pc + b, fh, fs);
-              const float er = e[(long long)a * ld + c], ei = e[plane + (long long)a * ld + c];
-              v[a * QT + b] += (double)(wphi * (er * er + ei * ei));
+            for (int k = 0; k < Q2; ++k) {
+              const int c = fcol(QT * pc + k % QT, fh, fs);
+              er[i][k] = e[(long long)(k / QT) * ld + c];
+              ei[i][k] = e[plane + (long long)(k / QT) * ld + c];
             }
+          }
+#pragma unroll
+          for (int i = 0; i < LB; ++i) {
+            const float wphi = wl[min(l0 + i, L - 1)].w * phi;
+#pragma unroll
+            for (int k = 0; k < Q2; ++k) {
+              const float x = wphi * (er[i][k] * er[i][k] + ei[i][k] * ei[i][k]);
+              v[k] += l0 + i < L ? (double)x : 0.0;   // (a branch would let the loads sink into it)
+            }
+          }
         }
       }
 #pragma unroll
@@ -1202,7 +1215,10 @@ hipError_t launch_seed_gather(dlx_plan* p, const float* flat, const float* resid
 hipError_t launch_kgrad(dlx_plan* p, int f0, int nf, const float* sources, const float* flat, const float* resid,
                         double* gK, hipStream_t st) {
   const long long plane = (long long)p->chunk_psf * p->No * p->ldNo, by = (long long)p->No * p->ldNo;
-  const dim3 grid(p->seed_blocks, p->k_per_pixel ? 1 : nf), blk(kSeedThreads);
+  // no sums over pixels with one kernel per pixel: blocks of one wave, which spread over more CUs
+  const dim3 grid(p->k_per_pixel ? (unsigned)(((long long)p->Nd * p->Nd + 63) / 64) : p->seed_blocks,
+                  p->k_per_pixel ? 1 : nf);
+  const dim3 blk(p->k_per_pixel ? 64 : kSeedThreads);
   const int* win = p->dither ? p->d_win : nullptr;
   double* gpix = p->k_per_pixel ? gK : nullptr;
 #define DLX_KGRAD(QT)                                                                                          \

@@ -78,3 +78,34 @@ def test_fused_seed_of_several_frames_matches_the_separate_calls(q, nd, frames, 
     # flux: sums of at most nd^2 doubles whose magnitudes add up to no more than sum |flat r| max(bs)
     size = np.abs(p["flat"] * r.cpu().numpy()).sum() * (b.cpu().numpy().max() / p["sources"][..., 2].min())
     assert np.all(np.abs(ge[..., 2] - gs[..., 2]) <= 1e-13 * size)
+
+
+@pytest.mark.parametrize("q,nd,L,frames,per_pixel", [(1, 13, 9, 2, True), (2, 11, 11, 3, True), (2, 11, 9, 2, False),
+                                                     (3, 9, 5, 2, True), (4, 8, 3, 2, False), (4, 8, 5, 2, True)])
+def test_intrapixel_gradient_past_the_wavelengths_loaded_at_once(q, nd, L, frames, per_pixel):
+    """Wavelength counts that leave a remainder of the 8, 8, 4 and 2 that kgrad_kernel loads together for
+    Q = 1 .. 4, and pixels past the last whole wave; held, as the other intra-pixel tests are, to 1e-5 of the
+    gradient's own scale sum |F r| B / Q^2 (per pixel with one kernel per pixel)."""
+    import oracle as O
+    from paper_2406_08703_amd import PsfPlan, evaluate
+    from tests.gpu_helpers import dev, geometry
+    from tests.helpers import oracle_problem
+    print(f"intra-pixel gradient q={q} L={L} per_pixel={per_pixel}", flush=True)
+    w = make_workload("c3", n_pupil=24, n_focal=q * nd, oversample=q, n_wavelengths=L, n_frames=frames, noll=(2, 3, 4))
+    rng = np.random.default_rng(L)
+    k = 1.0 + 0.05 * rng.normal(size=(nd, nd, q, q) if per_pixel else (q, q))
+    import dataclasses
+    w = dataclasses.replace(w, intrapixel=k.astype(np.float32))
+    prob = oracle_problem(w)
+    p = w.eval_params()
+    data = rng.poisson(50.0, (frames, nd, nd)).astype(np.float64)
+    ref = O.value_and_grad(prob, p["coeffs"], None, p["sources"], p["flat"], data, "chi2", w.prior_mu, w.prior_sigma)
+    want = O.intrapixel_grad(prob, p["coeffs"], None, p["sources"], p["flat"], ref["r"])
+    plan = PsfPlan(geometry(w), dev(w.transmission), dev(w.zbasis), None, dev(w.intrapixel), pixel_kernel=per_pixel)
+    got = evaluate(plan, dev(p["coeffs"]), None, dev(p["sources"]), dev(p["flat"]), dev(data), "chi2", w.prior_mu,
+                   w.prior_sigma, intrapixel_grad=True).grad_intrapixel.cpu().numpy()
+    assert plan.sync() == 0
+    plan.close()
+    size = np.abs(np.asarray(p["flat"], np.float64)[None] * ref["r"]) * ref["binned"]
+    scale = size.sum(0).max() if per_pixel else size.sum()
+    assert np.max(np.abs(got - want)) / (scale / (q * q)) < 1e-5
