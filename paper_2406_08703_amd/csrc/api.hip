@@ -1260,8 +1260,9 @@ constexpr double kTableBeta = 20.0;   // interpolation error about exp(-beta)
 // the estimate weighs the folded products at their measured rate (85 TFLOP/s executed, after 15 us a
 // launch; 120 on a table, which leaves out the rows and columns no star reaches) against the FP64 matrix
 // instructions of the interpolation and its adjoint (64 cycles of a SIMD each, times 1.7 and 1.8 to 2.0
-// measured) and the passes over memory. (512 pupil, 768 focal samples, 32 wavelengths: 128 stars 2297 us at
-// h16 = 10, 2117 at 12, 2384 at 14; 24 stars 1038 at 9, 1088 at 12.)
+// measured), the passes over memory and 70 us for the table's seven further launches (388 focal samples, 6
+// stars, 2 wavelengths, where the estimates are near: 255 us on a table, 240 without). (512 pupil, 768 focal
+// samples, 32 wavelengths: 128 stars 1803 us at h16 = 10, 1686 at 12, 1805 at 13; 24 stars 933 at 9, 994 at 12.)
 constexpr int kAdjointWgs = 2048;
 
 bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
@@ -1273,6 +1274,10 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
   const double Ni = p->Ni, No = p->No, L = p->L, nfs = (double)p->F * p->S;
   const double lmin = *std::min_element(p->lam.begin(), p->lam.end());
   const double lmax = *std::max_element(p->lam.begin(), p->lam.end());
+  // A focal grid wider than the pupil grid's own field (one period of the sampled tilts) can hold stars whose
+  // tilts each wavelength reduces by itself, which cost a table far more than their own transforms (52 pupil
+  // and 620 focal samples, 192 stars all over them: 44 ms on a table, 6.1 ms without).
+  if (No * p->du > lmin / p->dx) return false;
   const double direct = 4.0 * p->n_psf * (No * Ni * Ni + No * No * Ni) / 85e6 + 60.0 + p->n_psf * No * No * 8.0 / 4.5e6;
   double least = 0.85 * direct;
   bool found = false;
@@ -1298,7 +1303,7 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
                        quads * (std::ceil(((cols + K - 1) / h16 + 1) / waves) + 1);
     const double est = 4.0 * L * (n * Ni * Ni + n * n * Ni) / 120e6 + 60.0 + L * n * n * 8.0 / 3e6 +
                        nfs * (1.7 * fwd + (table_adjoint_pair(h16, K) ? 1.8 : 2.0) * adj) * 64.0 / (1024 * 2400.0) +
-                       nfs * No * No * 12.0 / 3e6 + 40.0;
+                       nfs * No * No * 12.0 / 3e6 + 70.0;
     if (est >= least) continue;
     least = est;
     found = true;

@@ -208,7 +208,7 @@ def test_table_reports_a_position_that_is_not_finite():
     compare(good, reference("q4", "poisson"), q=4)
 
 
-@pytest.mark.parametrize("q,nd,pixel,n_sources,L", [(1, 150, 8.0, 3, 240), (1, 150, 8.0, 9, 90), (2, 61, 70.0, 5, 160),
+@pytest.mark.parametrize("q,nd,pixel,n_sources,L", [(1, 150, 8.0, 3, 240), (1, 150, 8.0, 9, 90), (2, 61, 70.0, 13, 90),
                                                     (5, 23, 150.0, 24, 36)])
 def test_table_bins_every_oversampling_and_star_count(q, nd, pixel, n_sources, L):
     """Star counts below, at and past what the binning loads at once (8 and 2 for Q = 1 and 2; one for Q = 5)."""
@@ -228,3 +228,18 @@ def test_table_bins_every_oversampling_and_star_count(q, nd, pixel, n_sources, L
     plan.close()
     assert n == L
     compare(got, ref, q=q, kind="poisson")
+
+
+def test_focal_grids_wider_than_the_pupil_field_keep_their_own_transforms():
+    """100 detector pixels of half a resolution element on a pupil of 40 samples: stars on the detector may lie
+    beyond the sampled tilts' period, so every star, frame and wavelength is transformed; on 101 samples the
+    same problem takes the table."""
+    from tests.gpu_helpers import make_plan, run_eval
+    print("table and the pupil field", flush=True)
+    for n_pupil in (40, 101):
+        w = make_workload("c3", n_pupil=n_pupil, n_focal=300, n_wavelengths=24, n_frames=16, noll=(2, 3, 4))
+        w = w.with_data(np.ones((w.problem.n_frames, w.problem.n_det, w.problem.n_det)))
+        plan = make_plan(w)
+        n, got = transforms(plan, lambda: run_eval(w, plan=plan))
+        plan.close()
+        assert n == (w.problem.n_psf if n_pupil == 40 else len(w.problem.wavelengths))
