@@ -766,10 +766,48 @@ __global__ void window_kernel(const float* Bbig, int Nb, const int* win, int Nd,
 // windows gathers, for enlarged pixel q, h[q] = sum over the frames whose window
 // holds q (p = q - win_f) of flat[p] r_f[p], in frame order; then
 //   G[Q q_r + a][Q q_c + b] = K[a][b] h[q]
-// and the flux partials sum_q h[q] bs_s[q] (one enlarged frame).
-// A wave runs 256 pixels, four per lane, and adds up its own flux partials, at flux[s nblk + wave of the
-// grid] (20 stars over 1064^2 pixels: 52 us; 65 us with a block's sum and its two barriers per star).
-__global__ __launch_bounds__(kSeedThreads) void seed_gather_kernel(
+// and the flux partials sum_q h[q] bs_s[q] of this block (one enlarged frame),
+// at flux[s nblk + block].
+__global__ void seed_gather_kernel(const float* resid, const float* flat, const float* intrapixel, const float* bs,
+                                   const int* win, int F, int Nd, int Nb, int Q, int S, int ldg, int fh, int fs,
+                                   float* G, double* flux) {
+  __shared__ double sh[kSeedThreads / 64];
+  const long long nb2 = (long long)Nb * Nb, npix = (long long)Nd * Nd;
+  const long long q = (long long)blockIdx.x * kSeedThreads + threadIdx.x;
+  float h = 0.f;
+  if (q < nb2) {
+    const int qr = (int)(q / Nb), qc = (int)(q - (long long)qr * Nb);
+    for (int f = 0; f < F; ++f) {
+      const int pr = qr - win[2 * f], pc = qc - win[2 * f + 1];
+      if (pr >= 0 && pr < Nd && pc >= 0 && pc < Nd) {
+        const long long p = (long long)pr * Nd + pc;
+        h += flat[p] * resid[(long long)f * npix + p];
+      }
+    }
+    float* g = G + (long long)(Q * qr) * ldg;
+    for (int a = 0; a < Q; ++a)
+      for (int b = 0; b < Q; ++b)
+        g[(long long)a * ldg + fcol(Q * qc + b, fh, fs)] = intrapixel ? h * intrapixel[a * Q + b] : h;
+  }
+  for (int s = 0; s < S; ++s) {
+    double v = q < nb2 ? (double)h * (double)bs[(long long)s * nb2 + q] : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (int w = 0; w < kSeedThreads / 64; ++w) t += sh[w];
+      flux[(long long)s * gridDim.x + blockIdx.x] = t;
+    }
+    __syncthreads();
+  }
+}
+
+// seed_gather_kernel for many stars: a wave runs 256 pixels, four per lane, and adds up its own flux
+// partials, at flux[s nblk + wave of the grid] (20 stars over 1064^2 pixels: 52 us; 65 us with a block's sum
+// and its two barriers per star).
+__global__ __launch_bounds__(kSeedThreads) void seed_gather_stars_kernel(
     const float* resid, const float* flat, const float* intrapixel, const float* bs, const int* win, int F, int Nd,
     int Nb, int Q, int S, int ldg, int fh, int fs, float* G, int nblk, double* flux) {
   const long long nb2 = (long long)Nb * Nb, npix = (long long)Nd * Nd;
@@ -1202,10 +1240,17 @@ hipError_t launch_window(dlx_plan* p, const float* flat, float* binned, float* m
 hipError_t launch_seed_gather(dlx_plan* p, const float* flat, const float* resid, const float* intrapixel,
                               hipStream_t st) {
   p->flux_blocks = p->seed_blocks;
-  static_assert(kSeedThreads == 256, "a wave of seed_gather_kernel covers one seed block");
-  hipLaunchKernelGGL(seed_gather_kernel, dim3((p->seed_blocks + 3) / 4), dim3(kSeedThreads), 0, st, resid, flat,
-                     intrapixel, p->d_bs, p->d_win, p->F_img, p->Nd_img, p->Nd, p->Q, p->S, p->ldNo, p->ghNo(),
-                     p->gsNo(), p->d_G, p->seed_blocks, p->d_flux);
+  static_assert(kSeedThreads == 256, "a wave of seed_gather_stars_kernel covers one seed block");
+  // from 16 stars the block's sums, with two barriers per star, outweigh four pixels in turn (20 stars over
+  // 1064^2 pixels 52 us against 65; 4 stars over 200^2 pixels of 17 frames 6 us slower)
+  if (p->S >= 16)
+    hipLaunchKernelGGL(seed_gather_stars_kernel, dim3((p->seed_blocks + 3) / 4), dim3(kSeedThreads), 0, st, resid, flat,
+                       intrapixel, p->d_bs, p->d_win, p->F_img, p->Nd_img, p->Nd, p->Q, p->S, p->ldNo, p->ghNo(),
+                       p->gsNo(), p->d_G, p->seed_blocks, p->d_flux);
+  else
+    hipLaunchKernelGGL(seed_gather_kernel, dim3(p->seed_blocks), dim3(kSeedThreads), 0, st, resid, flat, intrapixel,
+                       p->d_bs, p->d_win, p->F_img, p->Nd_img, p->Nd, p->Q, p->S, p->ldNo, p->ghNo(), p->gsNo(), p->d_G,
+                       p->d_flux);
   return hipGetLastError();
 }
 
