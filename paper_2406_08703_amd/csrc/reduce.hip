@@ -1284,9 +1284,11 @@ hipError_t launch_kgrad(dlx_plan* p, int f0, int nf, const float* sources, const
 int loss_block_count(long long npix) { return (int)((npix + kLossThreads - 1) / kLossThreads); }
 
 // Whether the frames are shared out over the waves of a block: where one wave per 64 pixels gives a SIMD
-// fewer than four waves. (With 1024 blocks or more one wave runs its frames faster: 16 frames of 512^2 pixels
-// 25 us against 26 to 35, 5 of 1024^2 31 against 45, 4 of 1024^2 with the seed 55 against 58.)
-bool split_frames(int nf, int nb) { return nf > 1 && nb < 1024; }
+// fewer than four waves and there are six frames or more (6 frames of 100^2 pixels with the seed 18 us in
+// turn, 13 shared; 3 frames of 85^2 without it 1 us faster in turn). (With 1024 blocks or more one wave runs
+// its frames faster: 16 frames of 512^2 pixels 25 us against 26 to 35, 5 of 1024^2 31 against 45, 4 of 1024^2
+// with the seed 55 against 58.)
+bool split_frames(int nf, int nb) { return nf >= 6 && nb < 1024; }
 
 // The loss terms alone: one frame, or several shared out over the waves of a block.
 void launch_loss_terms(int f0, int nf, long long npix, const float* model, const float* binned, const float* data,
