@@ -1253,84 +1253,45 @@ struct TableInner {
 // and give the same images bit for bit.
 bool table_allowed(const dlx_problem_desc& d) { return d.n_frames > 1 || d.frame_dithers || d.n_map > 0; }
 
-constexpr double kTableBeta = 20.0;   // interpolation error about exp(-beta)
-
-// The table's pitch, taps and sizes for a problem, or false where one transform pair per star, frame and
-// wavelength is the cheaper form. A finer pitch (h16 up) needs fewer taps but more samples to transform;
-// the estimate weighs the folded products at their measured rate (85 TFLOP/s executed, after 15 us a
-// launch; 120 on a table, which leaves out the rows and columns no star reaches) against the FP64 matrix
-// instructions of the interpolation and its adjoint (64 cycles of a SIMD each, times 1.7 and 1.8 to 2.0
-// measured), the passes over memory and 70 us for the table's seven further launches (388 focal samples, 6
-// stars, 2 wavelengths, where the estimates are near: 255 us on a table, 240 without). (512 pupil, 768 focal
-// samples, 32 wavelengths: 128 stars 1803 us at h16 = 10, 1686 at 12, 1805 at 13; 24 stars 933 at 9, 994 at 12.)
 constexpr int kAdjointWgs = 2048;
 
 bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
-  // The table's products are FP32 in both arithmetics (they are a small part of the evaluation). A split
-  // plan of few wavelengths keeps its own products: its error in the faintest pixels, 2e-5 to 6e-5 of the
-  // residual (2e-6 to 1e-5 where 16 or more wavelengths average it), would make the two forms of one
-  // problem differ by as much.
-  if (p->prec == DLX_BF16X3 && p->L < 16) return false;
-  const double Ni = p->Ni, No = p->No, L = p->L, nfs = (double)p->F * p->S;
-  const double lmin = *std::min_element(p->lam.begin(), p->lam.end());
-  const double lmax = *std::max_element(p->lam.begin(), p->lam.end());
-  // A focal grid wider than the pupil grid's own field (one period of the sampled tilts) can hold stars whose
-  // tilts each wavelength reduces by itself, which cost a table far more than their own transforms (52 pupil
-  // and 620 focal samples, 192 stars all over them: 44 ms on a table, 6.1 ms without).
-  if (No * p->du > lmin / p->dx) return false;
-  const double direct = 4.0 * p->n_psf * (No * Ni * Ni + No * No * Ni) / 85e6 + 60.0 + p->n_psf * No * No * 8.0 / 4.5e6;
-  double least = 0.85 * direct;
-  bool found = false;
-  const int nb = ceil_div(p->No, 16);
-  for (int h16 = 1; h16 <= 40; ++h16) {
-    const double h = h16 / 16.0, tau = p->du / h, sigma = lmin / (2.0 * p->D) / tau;
-    if (!(sigma >= 1.2)) continue;
-    if (sigma > 4.0 && found) break;
-    const int W = (int)std::ceil(2.0 * kTableBeta / (3.14159265358979 * (1.0 - 1.0 / sigma)));
-    if (W > 72) continue;
-    const int K = round_up((int)std::floor(15.0 * h) + W + 1, 8);
-    // samples in use for stars within the middle of the detector, with the taps and the stencil around them
-    const int n_reg = round_up((int)std::ceil(No * h * (nfs > 1 ? 1.25 : 1.02) + 2 * W + 10), 64);
-    const double half = 0.5 * (No - 1) * h + 0.5 * lmax / p->dx / tau + W + 6;
-    if (half > 16000.0) continue;
-    const int Nt = std::max(n_reg, round_up((int)std::ceil(2.0 * half), 64));
-    const int waves = table_adjoint_waves(h16, K);
-    if (!waves) continue;
-    const double n = n_reg, own = std::min(n, No * h + W), cols = 16.0 * waves;   // own: samples a star reaches
-    const double fwd = (std::ceil((7 * h16 + K) / 16.0) * K / 4 + 8.0 * (K / 4 + 1)) / 8 * nb * nb;
-    const double quads = (17.0 + W + 3 * h) / (h16 / 4.0);   // groups of four focal rows that reach 16 samples
-    const double adj = std::min(n / 32, own / 32 + 1) * std::min(std::ceil(n / cols), own / cols + 1) * waves * 2 *
-                       quads * (std::ceil(((cols + K - 1) / h16 + 1) / waves) + 1);
-    const double est = 4.0 * L * (n * Ni * Ni + n * n * Ni) / 120e6 + 60.0 + L * n * n * 8.0 / 3e6 +
-                       nfs * (1.7 * fwd + (table_adjoint_pair(h16, K) ? 1.8 : 2.0) * adj) * 64.0 / (1024 * 2400.0) +
-                       nfs * No * No * 12.0 / 3e6 + 70.0;
-    if (est >= least) continue;
-    least = est;
-    found = true;
-    TableArgs t = {};
-    t.Nt = Nt;
-    t.No = p->No;
-    t.ldg = p->ldNo;
-    t.nb = nb;
-    t.h16 = h16;
-    t.W = W;
-    t.K = K;
-    t.L = p->L;
-    t.S = p->S;
-    t.nfs = p->F * p->S;
-    // (stars all over an enlarged plane, as integer dithers are for, use the table about twice as far)
-    const int sized = p->dither ? std::min(Nt, round_up((int)std::ceil(2.0 * No * h + 2 * W + 10), 64)) : n_reg;
-    t.slots = waves * std::min((sized / 32) * ceil_div(sized, 16 * waves), 4096);
-    t.waves = waves;
-    t.tau = tau;
-    t.c0 = 0.5 * (Nt - 1) - 0.5 * (No - 1) * h;
-    t.beta = kTableBeta;
-    t.half_min = 0.5 * lmin / p->dx;
-    t.dx = p->dx;
-    *best = t;
-    *best_reg = sized;
-  }
-  return found;
+  TableProblem q;
+  q.Ni = p->Ni;
+  q.No = p->No;
+  q.L = p->L;
+  q.S = p->S;
+  q.F = p->F;
+  q.bf16x3 = p->prec == DLX_BF16X3;
+  q.dither = p->dither;
+  q.D = p->D;
+  q.dx = p->dx;
+  q.du = p->du;
+  q.lmin = *std::min_element(p->lam.begin(), p->lam.end());
+  q.lmax = *std::max_element(p->lam.begin(), p->lam.end());
+  TableShape s;
+  if (!choose_table_shape(q, &s)) return false;
+  TableArgs t = {};
+  t.Nt = s.Nt;
+  t.No = p->No;
+  t.ldg = p->ldNo;
+  t.nb = ceil_div(p->No, 16);
+  t.h16 = s.h16;
+  t.W = s.W;
+  t.K = s.K;
+  t.L = p->L;
+  t.S = p->S;
+  t.nfs = p->F * p->S;
+  t.slots = s.slots;
+  t.waves = s.waves;
+  t.tau = s.tau;
+  t.c0 = 0.5 * (s.Nt - 1) - 0.5 * (p->No - 1) * (s.h16 / 16.0);
+  t.beta = kTableBeta;
+  t.half_min = 0.5 * q.lmin / p->dx;
+  t.dx = p->dx;
+  *best = t;
+  *best_reg = s.n_reg;
+  return true;
 }
 
 // A plan on a PSF table: the images' arrays here, the optics in the table's own one-star plan.

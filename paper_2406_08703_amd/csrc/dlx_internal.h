@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "dlx.h"
+#include "table_choice.h"
 
 namespace dlx {
 
@@ -268,8 +269,6 @@ hipError_t launch_table_bin(const TableArgs& t, int Q, int Nd, int f0, int nf, c
 hipError_t launch_table_adjoint(const TableArgs& t, const float* sources, int f0, int nf, bool first,
                                 hipStream_t st);
 hipError_t launch_table_seed(const TableArgs& t, int n_reg, hipStream_t st);
-int table_adjoint_waves(int h16, int K);
-bool table_adjoint_pair(int h16, int K);
 size_t table_weight_count(int K);   // weights of one star
 hipError_t launch_table_kgrad(const TableArgs& t, int Q, int Nd, int f0, int nf, const float* sources,
                               const float* flat, const float* resid, const int* win, int F_img, int Nd_img,

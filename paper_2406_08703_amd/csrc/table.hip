@@ -37,10 +37,6 @@ __device__ __forceinline__ int xcd_order(int w, int n) {
 
 __device__ __forceinline__ int floor_div(int a, int b) { return (a >= 0 ? a : a - b + 1) / b; }
 
-// Row length of a star's weights: K, and zeros on both sides.
-constexpr int kPadL = 16;
-__host__ __device__ constexpr int wrow(int K) { return K + kPadL + 18; }
-
 // The window of the interpolation kernel at distance t (table samples), zero from W / 2 on.
 __device__ __forceinline__ double window(double t, int W, double beta) {
   const double z = 2.0 * t / (double)W;
@@ -157,6 +153,7 @@ __global__ __launch_bounds__(256) void table_image_kernel(const TableArgs t) {
 // (phi'(n) = (-1)^n / n times the window: the interpolation kernel's derivative at whole distances).
 // Samples outside the range in use count as the edge's: only nodes no star's samples touch see them.
 constexpr int kMaxHalfTaps = 48;
+static_assert(kTableMaxW <= 2 * kMaxHalfTaps, "a stencil holds half the taps of any window");
 
 template <class F>
 __device__ __forceinline__ void stencil(const double* cf, int nh, int r, int c, int lo, int hi, F at, double& dx,
@@ -179,7 +176,8 @@ __device__ __forceinline__ void stencil_weights(double* cf, const TableArgs& t) 
 // direction): the 2 W loads and products per sample of the plain sum took 174 us for 2112^2 samples and 64
 // taps, about 55 us here (18 us of matrix instructions).
 __global__ __launch_bounds__(256) void table_slope_kernel(const TableArgs t) {
-  constexpr int kMid = 96;
+  constexpr int kMid = 96;   // a band's place, 16 and up to 31 more columns around half the taps
+  static_assert(kTableMaxW / 2 + 47 < kMid, "");
   __shared__ double s[2 * kMid];   // s[d + kMid]: weight of the sample d to the right of (or below) the result
   const int H = t.W / 2;
   if (threadIdx.x < 2 * kMid) {
@@ -431,13 +429,6 @@ __global__ __launch_bounds__(256) void table_bin_kernel(const TableArgs t, int Q
 // next star's weights during the current star. 128 stars of 768 focal samples onto 832: 480 us (1115 us
 // for 32 x 32 samples per wave, each forming its own V from G without a step ahead).
 constexpr int kAdjRows = 2;   // blocks of focal rows loaded at a time
-constexpr int kAdjLds = 150 << 10;
-
-// blocks of focal columns that reach a workgroup's 16 `waves` table columns (V holds 4 KB for each)
-int adjoint_blocks(int waves, int h16, int K) { return (16 * waves + K - 2) / h16 + 1; }
-size_t adjoint_lds(int waves, int h16, int K) {
-  return sizeof(double) * (2 * 16 * wrow(K) + (size_t)adjoint_blocks(waves, h16, K) * 2 * 4 * 64);
-}
 
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES, WAVES / 2) void table_adjoint_kernel(const TableArgs t, const float* sources, int f0, int nf,
@@ -453,6 +444,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 2) void table_adjoint_kernel(co
   const double* wy = wx + 16 * KS;
   const int lo = t.range[0], hi = t.Nt - lo - 1;
   constexpr int CW = 16 * WAVES, TH = 64 * WAVES, kPairs = 2048 / TH;
+  static_assert(16 * wrow(kTableMaxK) <= kPairs * TH, "the threads stage the weights of any window");
   const int nrt = (t.Nt - 2 * lo) / 32, ncg = (t.Nt - 2 * lo + CW - 1) / CW;
   const int nwg = t.slots / WAVES, lin = xcd_order(blockIdx.x, gridDim.x);
   const int group = lin / nwg, wg = lin - group * nwg;
@@ -870,6 +862,7 @@ hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, 
     default: return hipErrorInvalidValue;
   }
 #undef DLX_SHIFT
+  static_assert(kTableMinK == 8 * 2 && kTableMaxK == 8 * 10, "every window that can be chosen is compiled");
   return hipGetLastError();
 }
 
@@ -912,18 +905,6 @@ hipError_t launch_table_adjoint(const TableArgs& t, const float* sources, int f0
 }
 
 size_t table_weight_count(int K) { return 2 * 16 * (size_t)wrow(K); }
-
-// Waves of an adjoint workgroup (16 table columns each): 8, or 4 where the focal blocks that reach 128
-// columns do not fit the LDS; 0 where neither does. (Four where eight fit as well is slower, 703 us against
-// 665 for 128 stars at h16 = 12: the first product, shared by the waves, covers K columns more than they own.)
-int table_adjoint_waves(int h16, int K) {
-  for (int waves : {8, 4})
-    if (adjoint_lds(waves, h16, K) <= kAdjLds) return waves;
-  return 0;
-}
-
-// whether two workgroups of eight waves fit a CU
-bool table_adjoint_pair(int h16, int K) { return adjoint_lds(8, h16, K) <= 80 << 10; }
 
 // The table's seed weights, once every frame is in the groups' planes.
 hipError_t launch_table_seed(const TableArgs& t, int n_reg, hipStream_t st) {
