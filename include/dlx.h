@@ -160,13 +160,16 @@ enum {
  * frames, integer dithers or a bicubic map has enough stars and frames for it
  * to pay, the plan transforms the on-axis pupil once per wavelength onto a
  * table finer than the image's own bandwidth, interpolates every star's image
- * from the band's sum there (FP64, error about 1e-9 of the local intensity),
+ * from the band's sum there in FP64 (next to a sample too bright for that, from
+ * the wavelengths' fields: |dI| <= 2 eta sqrt(I I_max) + eta^2 I_max everywhere,
+ * eta < 3e-7, as one transform per star leaves, and never negative),
  * and sends the gradient back the same way: same results up to rounding, for
  * any star position. Its products are FP32 in both arithmetics. Such a plan
  * holds the table for stars anywhere in the pupil grid's own field (a third of
  * the free device memory at most); a plan with a workspace limit, with
  * DLX_FLAG_DENSE_MFT or DLX_FLAG_GROUPED keeps one transform per star, frame
- * and wavelength, and so does a DLX_BF16X3 plan of fewer than 16 wavelengths. */
+ * and wavelength, and so does a plan of one wavelength (whose nulls no band
+ * fills) and a DLX_BF16X3 plan of fewer than 16. */
 
 /* DLX_FLAG_PIXEL_KERNEL gives every detector pixel its own intra-pixel kernel
  * (Section 6: intra-pixel sensitivity, recoverable at this sampling): every

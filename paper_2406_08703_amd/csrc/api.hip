@@ -115,6 +115,8 @@ void layout_images(dlx_plan* p, Pool& pool) {
   t.base = pool.take<int>(2 * (size_t)t.nfs);
   t.far = pool.take<int>(t.nfs);
   t.range = pool.take<int>(2);
+  t.dark_n = pool.take<int>(p->n_chunks);
+  t.dark = pool.take<int>(fc * p->S * t.nb * t.nb);
   t.planes = pool.take<float>(fc * p->S * No * ldNo);
   t.Hpart = pool.take<double>(t.groups * nt2);
   t.H = pool.take<float>((1 + (size_t)p->L) * nt2);
@@ -1289,6 +1291,12 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
   t.beta = kTableBeta;
   t.half_min = 0.5 * q.lmin / p->dx;
   t.dx = p->dx;
+  double peak = 0.0;
+  for (int l = 0; l < p->L; ++l) {
+    const double a = p->Ni * p->dx * p->du / p->lam[l];
+    peak += std::fabs(p->wts[l]) * a * a;
+  }
+  t.root_peak = std::sqrt(peak);
   *best = t;
   *best_reg = s.n_reg;
   return true;
@@ -1332,7 +1340,7 @@ dlx_status create_with_table(dlx_plan* p, const dlx_problem_desc& d, int flags) 
 
   p->ta = t;
   p->frames_per_chunk = fc;
-  p->n_chunks = ceil_div(p->F, fc);
+  p->n_chunks = p->ta.n_chunks = ceil_div(p->F, fc);
   p->chunk_psf = fc * p->S * p->L;
   p->n_reg = n_reg;
   p->loss_blocks = loss_block_count((long long)p->Nd_img * p->Nd_img);
@@ -1572,7 +1580,7 @@ dlx_status table_images(dlx_plan* p, int f0, int nf, const float* sources, const
                         float* binned, float* model, hipStream_t st) {
   Stage sg(p, st, DLX_STAGE_BIN, (long long)nf * p->S * p->L);
   if (f0 == 0) DLX_HIP(launch_table_image(p->ta, p->n_reg, false, st));
-  DLX_HIP(launch_table_shift(p->ta, sources, f0, nf, st));
+  DLX_HIP(launch_table_shift(p->ta, sources, f0, nf, f0 / p->frames_per_chunk, st));
   const long long kst = p->k_per_pixel ? (long long)p->Q * p->Q : 0;
   const bool big = p->dither && binned;   // bin the enlarged plane once, then cut every frame's window
   DLX_HIP(launch_table_bin(p->ta, p->Q, p->Nd, f0, nf, sources, intrapixel, kst, big ? nullptr : flat, p->d_bs,

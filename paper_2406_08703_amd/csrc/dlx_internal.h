@@ -121,7 +121,11 @@ struct GemmArgs {
 // wavelength instead of one per star, frame and wavelength) and each star's samples are interpolated from
 // it in FP64 by a windowed sinc of W taps,
 //   phi(t) = sinc(t) exp(beta (sqrt(1 - (2 t / W)^2) - 1)),  |t| < W / 2,
-// whose error (about exp(-beta), beta = 20) lies two orders below the FP32 transforms' own. The adjoint
+// whose error (about exp(-beta), beta = 20) lies two orders below the FP32 transforms' own. What those leave
+// at the table's samples is another matter: the error of a bright sample, 1e-7 of it, is not band-limited, so
+// up to 1e-9 of it (1e-10 a few samples further) reaches every sample interpolated across it, more than a
+// null or a dark zone next to it may hold. Blocks with so dark a sample are interpolated from the L fields
+// instead and squared (table_field_kernel), which leaves what a transform per star leaves. The adjoint
 // is the transpose: the seed weights of every frame are spread onto the table with the same weights and
 // summed over the stars, and one adjoint transform per wavelength follows.
 // The table pitch is chosen so that 16 focal samples advance by a whole number h16 of table samples: the
@@ -149,6 +153,10 @@ struct TableArgs {
   int* base;               // first table sample of block 0 [nfs][2]
   int* far;                // [nfs] 1: a tilt beyond half_min
   int* range;              // {lo, any far star}
+  double root_peak;        // the image's largest possible sample, sum_l |w_l| (Ni dx du / lambda_l)^2: its root
+  int n_chunks;
+  int* dark_n;             // [n_chunks] blocks of the chunk's images that are interpolated from the fields
+  int* dark;               // and their numbers (star nb + block row) nb + block column
   float* planes;           // star images on the focal grid [chunk frames * S][No][ldg]
   const float* G;          // seed weights [chunk frames][ldg][ldg], zero past the focal grid
   double* Hpart;           // [groups][Nt][Nt]
@@ -262,7 +270,7 @@ hipError_t launch_loss_plain(int nf, long long npix, const float* model, const f
 hipError_t launch_gemm(int kind, int prec, TileShape ts, const GemmArgs& a, int n_wg, hipStream_t st);
 hipError_t launch_table_weights(const TableArgs& t, const float* sources, hipStream_t st);
 hipError_t launch_table_image(const TableArgs& t, int n_reg, bool derivatives, hipStream_t st);
-hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, int nf, hipStream_t st);
+hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, int nf, int chunk, hipStream_t st);
 hipError_t launch_table_bin(const TableArgs& t, int Q, int Nd, int f0, int nf, const float* sources,
                             const float* intrapixel, long long kst, const float* flat, float* bs, float* binned,
                             float* model, hipStream_t st);

@@ -107,6 +107,7 @@ __global__ __launch_bounds__(256) void table_weights_kernel(const TableArgs t, c
       t.range[0] = lo > 0.0 ? (int)lo : 0;
       t.range[1] = sf[0] | sf[1] | sf[2] | sf[3];
     }
+    for (int i = threadIdx.x; i < t.n_chunks; i += 256) t.dark_n[i] = 0;
     return;
   }
   const int i = blockIdx.x - 1, fs = i >> 1, axis = i & 1;
@@ -234,6 +235,21 @@ __device__ __forceinline__ void load_weights(const TableArgs& t, int fs, double*
   for (int e = threadIdx.x; e < n2; e += 256) reinterpret_cast<d2*>(w)[e] = src[e];
 }
 
+// A block of interpolated samples is dark, and interpolated from the fields instead, when one of them lies below
+// a bound set by the largest sample of its window, `most`: kDarkPeak of it, as at most 3e-10 of a core reaches the
+// samples around it (512^2 pupils, 1 to 32 wavelengths); in the wings, whose rounding errors, 2.5e-10 sqrt(most x
+// peak) as interpolated and 1.5e-9 sqrt(sample x peak) from a transform per star, are larger for their light,
+// kDarkNull sqrt(most x peak), and nowhere more than kDarkWing of it. Hard-edged pupils' broadband images have no
+// such block, or a few in a hundred; those of soft pupils and of a few close wavelengths have many.
+constexpr float kDarkPeak = 4e-6f, kDarkNull = 2.5e-7f, kDarkWing = 5e-4f;
+
+// high 32 bits of a sample: in the order of the samples where they are not negative
+__device__ __forceinline__ int high_word(double v) { return (int)(__builtin_bit_cast(unsigned long long, v) >> 32); }
+
+__device__ __forceinline__ void add_dark(const TableArgs& t, int chunk, int star, int yb, int xb) {
+  if ((threadIdx.x & 63) == 0) t.dark[atomicAdd(t.dark_n + chunk, 1)] = (star * t.nb + yb) * t.nb + xb;
+}
+
 // the same for one wavelength of a star whose tilt is reduced per wavelength
 __device__ __forceinline__ void far_weights(const TableArgs& t, const float* src, int l, double* wx, double* wy,
                                             int& jx, int& jy) {
@@ -258,8 +274,7 @@ __device__ __forceinline__ void far_weights(const TableArgs& t, const float* src
 // waves fit a SIMD. 128 stars of 768^2 samples, 28 taps: 260 us (373 us with a read and a wait before each
 // product and two waves, 150 us of matrix instructions). KP = K / 8.
 template <int KP, int NY>
-__global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, const float* sources, int fs0, int nstar,
-                                                          int nbx) {
+__global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, int fs0, int nstar, int nbx, int chunk) {
   constexpr int K = 8 * KP, KS = wrow(K);
   __shared__ __attribute__((aligned(16))) double sh[2 * 16 * KS];
   double *wx = sh, *wy = sh + 16 * KS;
@@ -272,9 +287,13 @@ __global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, 
   d4 acc[NY];
 #pragma unroll
   for (int y = 0; y < NY; ++y) acc[y] = d4{0.0, 0.0, 0.0, 0.0};
+  int top[NY];   // this lane's largest sample in each block's window (high word)
+#pragma unroll
+  for (int y = 0; y < NY; ++y) top[y] = 0;
   // block y's product with the 16 table rows that start `rel` rows into its window
-  auto add_rows = [&](int y, int rel, const d4& d) {
+  auto add_rows = [&](int y, int rel, const d4& d, int m) {
     if (y >= ny || rel <= -16 || rel >= K) return;
+    top[y] = max(top[y], m);
     double wr[4];   // read together: a read before each product would be waited for each time
 #pragma unroll
     for (int r = 0; r < 4; ++r) wr[r] = wy[n * KS + kPadL + rel + 4 * r + g];
@@ -305,53 +324,134 @@ __global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, 
       for (int rb = 0; rb < rbs; ++rb) {
         if (rb + 1 < rbs) load(rb + 1, nx);
         d4 d = d4{0.0, 0.0, 0.0, 0.0};
+        int m = 0;
 #pragma unroll
         for (int p = 0; p < KP; ++p) {
           d = mfma_f64(v[p][0], w[p][0], d);
           d = mfma_f64(v[p][1], w[p][1], d);
+          m = max(m, max(high_word(v[p][0]), high_word(v[p][1])));
         }
 #pragma unroll
-        for (int y = 0; y < NY; ++y) add_rows(y, 16 * rb - t.h16 * y, d);
+        for (int y = 0; y < NY; ++y) add_rows(y, 16 * rb - t.h16 * y, d, m);
 #pragma unroll
         for (int p = 0; p < KP; ++p) v[p] = nx[p];
       }
     }
-  } else {   // one wavelength after the other, kept simple: no star of a sampled pupil's own field comes here
-    for (int l = 0; l < t.L; ++l) {
-      int jx, jy;
-      __syncthreads();
-      far_weights(t, sources + fs * 3, l, wx, wy, jx, jy);
-      __syncthreads();
-      const float* e = t.E + l * t.e_by_wl;
-      const double w = (double)t.wl[l].w;
-      if (xb >= t.nb) continue;
-      const int cx = jx + t.h16 * xb + 2 * g;
-#pragma unroll
-      for (int y = 0; y < NY; ++y)
-#pragma unroll 1
-        for (int rb = 0; 16 * rb < K; ++rb) {
-          const long long row = (long long)iclamp(jy + t.h16 * (yb0 + y) + n + 16 * rb, lo, hi) * t.Nt;
-          d4 d = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-          for (int p = 0; p < KP; ++p) {
-            const float* q = e + row + iclamp(cx + 8 * p, lo, hi - 1);
-            d = mfma_f64(w * power(q[0], q[t.e_plane]), wx[n * KS + kPadL + 8 * p + 2 * g], d);
-            d = mfma_f64(w * power(q[1], q[t.e_plane + 1]), wx[n * KS + kPadL + 8 * p + 2 * g + 1], d);
-          }
-          add_rows(y, 16 * rb, d);
-        }
-    }
+  } else {   // every wavelength has its own window
+    for (int y = 0; y < ny && xb < t.nb; ++y) add_dark(t, chunk, star, yb0 + y, xb);
+    return;
   }
+  if (xb >= t.nb) return;
   float* o = t.planes + (long long)star * t.No * t.ldg;
   const int x = 16 * xb + n;
-  if (x < t.No) {
+  const float root_peak = (float)t.root_peak;
 #pragma unroll
-    for (int y = 0; y < NY; ++y)
+  for (int y = 0; y < NY; ++y) {
+    if (y >= ny) continue;
+    const float most = (float)__builtin_bit_cast(double, (unsigned long long)wave_max(top[y]) << 32);
+    const double least = fmaxf(kDarkPeak * most, fminf(kDarkNull * __fsqrt_rn(most) * root_peak, kDarkWing * most));
+    bool dark = false;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int yy = 16 * (yb0 + y) + 4 * r + g;
-        if (y < ny && yy < t.No) o[(long long)yy * t.ldg + x] = (float)acc[y][r];
+    for (int r = 0; r < 4; ++r) {
+      const int yy = 16 * (yb0 + y) + 4 * r + g;
+      if (x < t.No && yy < t.No) {
+        o[(long long)yy * t.ldg + x] = (float)acc[y][r];
+        dark |= acc[y][r] < least;
       }
+    }
+    if (__any(dark)) add_dark(t, chunk, star, yb0 + y, xb);
+  }
+}
+
+// The dark blocks' samples, and all of far stars: sum_l w_l |sum_j phi_j E_l[j]|^2, the fields interpolated with
+// the same weights (they have half the image's bandwidth), a far star's with those of its tilt at each wavelength.
+// A workgroup per block, its waves share out the wavelengths. Two chains of products per wavelength where
+// the image has one for all: bound by the latency of the loads for a few blocks, by the FP64 matrix rate for many.
+template <int KP>
+__global__ __launch_bounds__(256, 2) void table_field_kernel(const TableArgs t, const float* sources, int fs0, int chunk) {
+  constexpr int K = 8 * KP, KS = wrow(K);
+  __shared__ __attribute__((aligned(16))) double wy[16 * KS];
+  __shared__ double part[4][4][64];
+  const int lane = threadIdx.x & 63, wave = wave_id(), n = lane & 15, g = lane >> 4;
+  const int lo = t.range[0], hi = t.Nt - lo - 1, count = t.dark_n[chunk];
+  for (int i = blockIdx.x; i < count; i += gridDim.x) {
+    const int item = t.dark[i], xb = item % t.nb, yb = item / t.nb % t.nb, star = item / (t.nb * t.nb), fs = fs0 + star;
+    const bool far = t.far[fs];
+    d2 wx[KP];   // column weights of this lane's samples 8 p + 2 g and the next
+    double fy = 0.0;
+    if (!far) {
+      const double* src = t.wt + (long long)fs * 2 * 16 * KS;
+      for (int e = threadIdx.x; e < 8 * KS; e += 256)
+        reinterpret_cast<d2*>(wy)[e] = reinterpret_cast<const d2*>(src + 16 * KS)[e];
+#pragma unroll
+      for (int p = 0; p < KP; ++p) wx[p] = *reinterpret_cast<const d2*>(src + n * KS + kPadL + 8 * p + 2 * g);
+    }
+    __syncthreads();
+    d4 tot = d4{0.0, 0.0, 0.0, 0.0};
+    for (int l = wave; l < t.L; l += 4) {
+      int jx = t.base[2 * fs], jy = t.base[2 * fs + 1];
+      if (far) {   // each weight is needed by one lane, so none goes through LDS
+        const double fx = star_origin(t, reduced(t, sources[fs * 3], l), jx) + (double)(n * t.h16) / 16.0;
+        fy = star_origin(t, reduced(t, sources[fs * 3 + 1], l), jy) + (double)(n * t.h16) / 16.0;
+#pragma unroll
+        for (int p = 0; p < KP; ++p)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) wx[p][k] = kernel_weight(fx - (double)(8 * p + 2 * g + k), t.W, t.beta);
+      }
+      const float* e = t.E + l * t.e_by_wl;
+      const int cx = jx + t.h16 * xb + 2 * g, ry = jy + t.h16 * yb + n;
+      d4 fr = d4{0.0, 0.0, 0.0, 0.0}, fi = d4{0.0, 0.0, 0.0, 0.0};
+      constexpr bool kAhead = KP <= 6;   // (longer windows leave no registers for the next rows)
+      float2 er[KP], ei[KP], nr[kAhead ? KP : 1], ni[kAhead ? KP : 1];
+      auto load = [&](int rb, float2* re, float2* im) {
+        const float* row = e + (long long)iclamp(ry + 16 * rb, lo, hi) * t.Nt;
+#pragma unroll
+        for (int p = 0; p < KP; ++p) {
+          const int c = iclamp(cx + 8 * p, lo, hi - 1);
+          __builtin_memcpy(&re[p], row + c, sizeof re[p]);
+          __builtin_memcpy(&im[p], row + c + t.e_plane, sizeof im[p]);
+        }
+      };
+      if constexpr (kAhead) load(0, er, ei);
+      for (int rb = 0; 16 * rb < K; ++rb) {
+        if constexpr (!kAhead) load(rb, er, ei);
+        if constexpr (kAhead)
+          if (16 * rb + 16 < K) load(rb + 1, nr, ni);   // while the current rows' products run
+        d4 dr = d4{0.0, 0.0, 0.0, 0.0}, di = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int p = 0; p < KP; ++p) {
+          dr = mfma_f64((double)er[p].x, wx[p][0], dr);
+          di = mfma_f64((double)ei[p].x, wx[p][0], di);
+          dr = mfma_f64((double)er[p].y, wx[p][1], dr);
+          di = mfma_f64((double)ei[p].y, wx[p][1], di);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (16 * rb + 4 * r < K) {
+            const int q = 16 * rb + 4 * r + g;
+            const double w = far ? kernel_weight(fy - (double)q, t.W, t.beta) : wy[n * KS + kPadL + q];
+            fr = mfma_f64(w, dr[r], fr);
+            fi = mfma_f64(w, di[r], fi);
+          }
+        if constexpr (kAhead) {
+#pragma unroll
+          for (int p = 0; p < KP; ++p) {
+            er[p] = nr[p];
+            ei[p] = ni[p];
+          }
+        }
+      }
+      const double w = (double)t.wl[l].w;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) tot[r] = fma(w, fma(fr[r], fr[r], fi[r] * fi[r]), tot[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wave][r][lane] = tot[r];
+    __syncthreads();   // and the weights are done with
+    const int x = 16 * xb + n, y = 16 * yb + 4 * wave + g;   // this wave adds up and writes output register `wave`
+    double v = 0.0;
+    for (int k = 0; k < 4; ++k) v += part[k][wave][lane];
+    if (x < t.No && y < t.No) t.planes[(long long)star * t.No * t.ldg + (long long)y * t.ldg + x] = (float)v;
   }
 }
 
@@ -833,21 +933,25 @@ hipError_t launch_table_image(const TableArgs& t, int n_reg, bool derivatives, h
   return hipGetLastError();
 }
 
-hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, int nf, hipStream_t st) {
+// Star images of frames [f0, f0 + nf), the chunk's; then its dark blocks (a kernel that leaves at once where
+// there are none).
+hipError_t launch_table_shift(const TableArgs& t, const float* sources, int f0, int nf, int chunk, hipStream_t st) {
   const int nbx = (t.nb + 3) / 4, nstar = nf * t.S;
   // eight blocks of rows per wave (the fewest instructions) where that still gives a CU four workgroups, four
   // where it gives one (12 stars of 384^2 samples: 20 us, 33 us with one block)
   const long long wg8 = (long long)nbx * ((t.nb + 7) / 8) * nstar, wg4 = (long long)nbx * ((t.nb + 3) / 4) * nstar;
   const int ny = wg8 >= 1024 ? 8 : wg4 >= 256 ? 4 : 1;
   const dim3 grid((unsigned)(nbx * ((t.nb + ny - 1) / ny) * nstar)), blk(256);
+  const dim3 fgrid((unsigned)std::min<long long>((long long)t.nb * t.nb * nstar, 512));   // as many as the chip holds
 #define DLX_SHIFT(KP)                                                                                              \
   case KP:                                                                                                         \
     if (ny == 8)                                                                                                   \
-      hipLaunchKernelGGL((table_shift_kernel<KP, 8>), grid, blk, 0, st, t, sources, f0 * t.S, nstar, nbx);        \
+      hipLaunchKernelGGL((table_shift_kernel<KP, 8>), grid, blk, 0, st, t, f0 * t.S, nstar, nbx, chunk);          \
     else if (ny == 4)                                                                                              \
-      hipLaunchKernelGGL((table_shift_kernel<KP, 4>), grid, blk, 0, st, t, sources, f0 * t.S, nstar, nbx);        \
+      hipLaunchKernelGGL((table_shift_kernel<KP, 4>), grid, blk, 0, st, t, f0 * t.S, nstar, nbx, chunk);          \
     else                                                                                                           \
-      hipLaunchKernelGGL((table_shift_kernel<KP, 1>), grid, blk, 0, st, t, sources, f0 * t.S, nstar, nbx);        \
+      hipLaunchKernelGGL((table_shift_kernel<KP, 1>), grid, blk, 0, st, t, f0 * t.S, nstar, nbx, chunk);          \
+    hipLaunchKernelGGL(table_field_kernel<KP>, fgrid, blk, 0, st, t, sources, f0 * t.S, chunk);                   \
     break
   switch (t.K / 8) {
     DLX_SHIFT(2);

@@ -28,6 +28,9 @@ bool choose_table_shape(const TableProblem& p, TableShape* best) {
   // residual (2e-6 to 1e-5 where 16 or more wavelengths average it), would make the two forms of one
   // problem differ by as much.
   if (p.bf16x3 && p.L < 16) return false;
+  // A band fills the nulls of its wavelengths; one wavelength keeps them, and nearly every block of its image
+  // has a sample that would have to be interpolated from the field (5 times the products, see TableArgs).
+  if (p.L < 2 || !(p.lmax > p.lmin)) return false;
   const double Ni = p.Ni, No = p.No, L = p.L, nfs = (double)p.F * p.S;
   const double lmin = p.lmin, lmax = p.lmax, n_psf = nfs * L;
   // A focal grid wider than the pupil grid's own field (one period of the sampled tilts) can hold stars whose

@@ -24,4 +24,17 @@ __device__ __forceinline__ double wave_total(double v) {
   return dpp_add<0x143>(v);   // row_bcast:31
 }
 
+// Largest of the 64 lanes' values (all active, none negative), the same in every lane.
+__device__ __forceinline__ int wave_max(int v) {
+#define DLX_MAX_STEP(CTRL) v = max(v, __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true))
+  DLX_MAX_STEP(0x111);   // row_shr:1
+  DLX_MAX_STEP(0x112);   // row_shr:2
+  DLX_MAX_STEP(0x114);   // row_shr:4
+  DLX_MAX_STEP(0x118);   // row_shr:8
+  DLX_MAX_STEP(0x142);   // row_bcast:15
+  DLX_MAX_STEP(0x143);   // row_bcast:31
+#undef DLX_MAX_STEP
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
 }  // namespace dlx
