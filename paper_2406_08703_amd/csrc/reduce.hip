@@ -1283,12 +1283,16 @@ hipError_t launch_kgrad(dlx_plan* p, int f0, int nf, const float* sources, const
 
 int loss_block_count(long long npix) { return (int)((npix + kLossThreads - 1) / kLossThreads); }
 
-// Whether the frames are shared out over the waves of a block: where one wave per 64 pixels gives a SIMD
-// fewer than four waves and there are six frames or more (6 frames of 100^2 pixels with the seed 18 us in
-// turn, 13 shared; 3 frames of 85^2 without it 1 us faster in turn). (With 1024 blocks or more one wave runs
-// its frames faster: 16 frames of 512^2 pixels 25 us against 26 to 35, 5 of 1024^2 31 against 45, 4 of 1024^2
-// with the seed 55 against 58.)
-bool split_frames(int nf, int nb) { return nf >= 6 && nb < 1024; }
+// Whether the frames are shared out over the waves of a block, min(nf, 16) of them: the same for the loss alone
+// and with the seed weights, so that both add the flat-field gradient up in the same order. A CU holds 16 such
+// waves, one block of 16 frames: up to 256 blocks from six frames on, up to 512 (two rounds) from eight on; past
+// that one wave per 64 pixels that runs the frames in turn hides its own loads. (us shared / in turn, the loss
+// alone and then with the seed weights. 100^2 pixels: 4 frames 5.4 / 5.0 and 10.6 / 13.7, 6 frames 6.2 / 6.0 and
+// 12.2 / 18.1, 16 frames 7.9 / 11.4 and 13.5 / 41.8; 256^2: 6 frames 6.6 / 6.4 and 12.3 / 18.6, 64 frames 28 / 39
+// and 52 / 176; 362^2: 6 frames 10.4 / 8.4 and 15.4 / 20.7, 8 frames 9.2 / 9.9 and 15.9 / 26.1, 10 frames 12.0 / 11.3 and
+// 25.0 / 31.8, 64 frames 50 / 52 and 104 / 204; 430^2: 16 frames 25 / 21 and 48 / 58; 500^2: 6 frames 13.7 / 11.9 and
+// 34 / 26, 16 frames 32 / 25 and 65 / 67; 1024^2: 5 frames 45 / 31, 4 frames with the seed weights 58 / 55.)
+bool split_frames(int nf, int nb) { return nb <= 512 && nf >= (nb <= 256 ? 6 : 8); }
 
 // The loss terms alone: one frame, or several shared out over the waves of a block.
 void launch_loss_terms(int f0, int nf, long long npix, const float* model, const float* binned, const float* data,
