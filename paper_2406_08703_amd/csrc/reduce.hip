@@ -1241,9 +1241,11 @@ hipError_t launch_seed_gather(dlx_plan* p, const float* flat, const float* resid
                               hipStream_t st) {
   p->flux_blocks = p->seed_blocks;
   static_assert(kSeedThreads == 256, "a wave of seed_gather_stars_kernel covers one seed block");
-  // from 16 stars the block's sums, with two barriers per star, outweigh four pixels in turn (20 stars over
-  // 1064^2 pixels 52 us against 65; 4 stars over 200^2 pixels of 17 frames 6 us slower)
-  if (p->S >= 16)
+  // Four pixels per lane and no block sums cost a quarter of the waves: from two waves per SIMD of them on
+  // (2048 blocks of 256 pixels), four with one star. (us, four pixels / one. 400^2 pixels: 1 star 8.3 / 5.0, 20
+  // stars 29 / 18; 700^2, 1914 blocks: 2 stars 9.5 / 7.3, 16 stars 26 / 27; 800^2, 2500 blocks: 1 star 9.4 / 8.3, 2
+  // stars 10.3 / 10.0, 4 stars 12.8 / 13.3, 20 stars 33 / 39; 1064^2, 4422 blocks: 1 star 11.3 / 12.4, 20 stars 53 / 69.)
+  if ((long long)p->seed_blocks * std::min(p->S, 2) >= 4096)
     hipLaunchKernelGGL(seed_gather_stars_kernel, dim3((p->seed_blocks + 3) / 4), dim3(kSeedThreads), 0, st, resid, flat,
                        intrapixel, p->d_bs, p->d_win, p->F_img, p->Nd_img, p->Nd, p->Q, p->S, p->ldNo, p->ghNo(),
                        p->gsNo(), p->d_G, p->seed_blocks, p->d_flux);
