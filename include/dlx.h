@@ -165,8 +165,9 @@ enum {
  * eta < 3e-7, as one transform per star leaves, and never negative),
  * and sends the gradient back the same way: same results up to rounding, for
  * any star position. Its products are FP32 in both arithmetics. Such a plan
- * holds the table for stars anywhere in the pupil grid's own field (a third of
- * the free device memory at most); a plan with a workspace limit, with
+ * holds the table for stars anywhere in the pupil grid's own field, in 16 GiB at
+ * most; where the device has not that much left, the plan takes the other form
+ * (dlx_plan_table_samples says 0). A plan with a workspace limit, with
  * DLX_FLAG_DENSE_MFT or DLX_FLAG_GROUPED keeps one transform per star, frame
  * and wavelength, and so does a plan of one wavelength (whose nulls no band
  * fills) and a DLX_BF16X3 plan of fewer than 16. */

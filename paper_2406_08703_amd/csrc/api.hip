@@ -48,7 +48,6 @@ using namespace dlx;
 
 namespace {
 
-constexpr size_t kDefaultChunkBudget = size_t(8) << 30;  // bytes of per-chunk intermediates
 constexpr int kTargetWG = 1024;
 constexpr int kMaxKgradQ = 4;   // the intra-pixel gradient kernel is compiled for Q <= 4
 // A frame's seed weights larger than this (bytes) are applied in a separate
@@ -1255,15 +1254,15 @@ struct TableInner {
 // and give the same images bit for bit.
 bool table_allowed(const dlx_problem_desc& d) { return d.n_frames > 1 || d.frame_dithers || d.n_map > 0; }
 
-constexpr int kAdjointWgs = 2048;
-
-bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
+// The table of a problem (chunk: its frames per chunk), or false where the other form is the cheaper one.
+bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg, int* chunk) {
   TableProblem q;
   q.Ni = p->Ni;
   q.No = p->No;
   q.L = p->L;
   q.S = p->S;
   q.F = p->F;
+  q.Nd = p->Nd;
   q.bf16x3 = p->prec == DLX_BF16X3;
   q.dither = p->dither;
   q.D = p->D;
@@ -1286,6 +1285,8 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
   t.nfs = p->F * p->S;
   t.slots = s.slots;
   t.waves = s.waves;
+  t.groups = s.groups;
+  t.per_group = s.per_group;
   t.tau = s.tau;
   t.c0 = 0.5 * (s.Nt - 1) - 0.5 * (p->No - 1) * (s.h16 / 16.0);
   t.beta = kTableBeta;
@@ -1299,6 +1300,7 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
   t.root_peak = std::sqrt(peak);
   *best = t;
   *best_reg = s.n_reg;
+  *chunk = s.chunk;
   return true;
 }
 
@@ -1306,38 +1308,9 @@ bool choose_table(const dlx_plan* p, TableArgs* best, int* best_reg) {
 // DLX_ERR_UNSUPPORTED (with nothing kept) where the problem takes the other form.
 dlx_status create_with_table(dlx_plan* p, const dlx_problem_desc& d, int flags) {
   TableArgs t;
-  int n_reg = 0;
-  if (!choose_table(p, &t, &n_reg)) return DLX_ERR_UNSUPPORTED;
-  size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return DLX_ERR_HIP;
-  const size_t nt2 = (size_t)t.Nt * t.Nt, frame = sizeof(float) * p->S * p->No * (size_t)p->ldNo + per_frame_bytes(p);
-  // one grid layer per star of a chunk: at most 65535
-  if (p->S > 65535) return DLX_ERR_UNSUPPORTED;
-  const size_t most = std::min<size_t>(kDefaultChunkBudget / frame, 65535 / p->S);
-  const int fc = (int)std::max<size_t>(1, std::min<size_t>(p->F, most));
+  int n_reg = 0, fc = 0;
+  if (!choose_table(p, &t, &n_reg, &fc)) return DLX_ERR_UNSUPPORTED;
   if (p->store_fields && fc < p->F) return DLX_ERR_UNSUPPORTED;
-  // Star groups of the adjoint, each of two stars or more (a workgroup's start and the sum of the groups'
-  // planes cost about half a star): as few as give its workgroups about eight rounds of the chip, and a
-  // multiple of the eight XCDs where one is near, as the workgroups of a group share the seed weights of its
-  // stars, which one XCD's L2 holds. (128 stars: 16 groups 498 us, 8 groups 584; 24 stars: 8 groups 166 us,
-  // 24 groups 183; 20 stars: 10 groups 199 us, 20 groups 208.)
-  const int nwg = t.slots / t.waves, stars = fc * p->S;
-  const int few = std::min(stars, std::max(2, stars / ceil_div(kAdjointWgs, nwg)));
-  t.per_group = few;
-  double off = 2.0;
-  for (int per = std::min(2, stars); per < 2 * few; ++per) {
-    const double ratio = per < few ? (double)few / per : (double)per / few;
-    if (ceil_div(stars, per) % 8 == 0 && ratio < off) {
-      off = ratio;
-      t.per_group = per;
-    }
-  }
-  t.groups = ceil_div(stars, t.per_group);
-  // the table for stars anywhere in the pupil grid's own field: fields, seed weights, transform buffers and
-  // matrices (a third of the free memory at most, else the other form)
-  const size_t optics = sizeof(float) * (size_t)p->L * (2 * nt2 + nt2 + 8 * (size_t)t.Nt * p->ldNi);
-  if (optics + 8 * (3 + t.groups) * nt2 + fc * frame > free_b / 3) return DLX_ERR_UNSUPPORTED;
-
   p->ta = t;
   p->frames_per_chunk = fc;
   p->n_chunks = p->ta.n_chunks = ceil_div(p->F, fc);

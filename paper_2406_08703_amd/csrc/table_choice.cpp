@@ -9,6 +9,40 @@ namespace {
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 int round_up(int a, int b) { return ceil_div(a, b) * b; }
 
+constexpr int kAdjointWgs = 2048;
+
+// Frames per chunk, star groups and device memory of a table whose sizes are set.
+void size_arrays(const TableProblem& p, TableShape* s) {
+  const size_t ldNo = round_up(p.No, 16), ldNi = round_up(p.Ni, 16), No = p.No, S = p.S, L = p.L, Nt = s->Nt;
+  const size_t nd2 = (size_t)p.Nd * p.Nd, nt2 = Nt * Nt, nfs = (size_t)p.F * S;
+  const size_t frame = sizeof(float) * (S * No * ldNo + No * ldNo + S * nd2);
+  // one grid layer per star of a chunk: at most 65535
+  s->chunk = (int)std::max<size_t>(1, std::min<size_t>({(size_t)p.F, kDefaultChunkBudget / frame, 65535 / S}));
+  // Star groups of the adjoint, each of two stars or more (a workgroup's start and the sum of the groups'
+  // planes cost about half a star): as few as give its workgroups about eight rounds of the chip, and a
+  // multiple of the eight XCDs where one is near, as the workgroups of a group share the seed weights of its
+  // stars, which one XCD's L2 holds. (128 stars: 16 groups 498 us, 8 groups 584; 24 stars: 8 groups 166 us,
+  // 24 groups 183; 20 stars: 10 groups 199 us, 20 groups 208.)
+  const int nwg = s->slots / s->waves, stars = s->chunk * p.S;
+  const int few = std::min(stars, std::max(2, stars / ceil_div(kAdjointWgs, nwg)));
+  s->per_group = few;
+  double off = 2.0;
+  for (int per = std::min(2, stars); per < 2 * few; ++per) {
+    const double ratio = per < few ? (double)few / per : (double)per / few;
+    if (ceil_div(stars, per) % 8 == 0 && ratio < off) {
+      off = ratio;
+      s->per_group = per;
+    }
+  }
+  s->groups = ceil_div(stars, s->per_group);
+  // fields, transform buffers, matrices and pupils of every wavelength; seed weights with a plane of each
+  // wavelength's own, the groups' planes, the image and its derivatives; the stars' weights and position sums
+  const size_t optics = sizeof(float) * 2 * L * (nt2 + 4 * Nt * ldNi + p.Ni * ldNi);
+  const size_t table = (4 * (1 + L) + 8 * (size_t)s->groups + 16) * nt2;
+  const size_t stars_bytes = nfs * (16 * (size_t)s->slots + 8 * 32 * (size_t)wrow(s->K));
+  s->bytes = optics + table + stars_bytes + s->chunk * frame;
+}
+
 // whether two adjoint workgroups of eight waves fit a CU
 bool adjoint_pair(int h16, int K) { return adjoint_lds(8, h16, K) <= 80 << 10; }
 
@@ -28,6 +62,7 @@ bool choose_table_shape(const TableProblem& p, TableShape* best) {
   // residual (2e-6 to 1e-5 where 16 or more wavelengths average it), would make the two forms of one
   // problem differ by as much.
   if (p.bf16x3 && p.L < 16) return false;
+  if (p.S > 65535) return false;
   // A band fills the nulls of its wavelengths; one wavelength keeps them, and nearly every block of its image
   // has a sample that would have to be interpolated from the field (5 times the products, see TableArgs).
   if (p.L < 2 || !(p.lmax > p.lmin)) return false;
@@ -65,18 +100,22 @@ bool choose_table_shape(const TableProblem& p, TableShape* best) {
                        nfs * (1.7 * fwd + (adjoint_pair(h16, K) ? 1.8 : 2.0) * adj) * 64.0 / (1024 * 2400.0) +
                        nfs * No * No * 12.0 / 3e6 + 70.0;
     if (est >= least) continue;
-    least = est;
-    found = true;
     // (stars all over an enlarged plane, as integer dithers are for, use the table about twice as far)
     const int sized = p.dither ? std::min(Nt, round_up((int)std::ceil(2.0 * No * h + 2 * W + 10), 64)) : n_reg;
-    best->Nt = Nt;
-    best->n_reg = sized;
-    best->h16 = h16;
-    best->W = W;
-    best->K = K;
-    best->waves = waves;
-    best->slots = waves * std::min((sized / 32) * ceil_div(sized, 16 * waves), 4096);
-    best->tau = tau;
+    TableShape s = {};
+    s.Nt = Nt;
+    s.n_reg = sized;
+    s.h16 = h16;
+    s.W = W;
+    s.K = K;
+    s.waves = waves;
+    s.slots = waves * std::min((sized / 32) * ceil_div(sized, 16 * waves), 4096);
+    s.tau = tau;
+    size_arrays(p, &s);
+    if (s.bytes > kTableMaxBytes) continue;
+    *best = s;
+    least = est;
+    found = true;
   }
   return found;
 }

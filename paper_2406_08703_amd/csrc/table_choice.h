@@ -34,8 +34,17 @@ constexpr int table_adjoint_waves(int h16, int K) {
   return adjoint_lds(8, h16, K) <= kAdjLds ? 8 : adjoint_lds(4, h16, K) <= kAdjLds ? 4 : 0;
 }
 
+constexpr size_t kDefaultChunkBudget = size_t(8) << 30;   // bytes of per-chunk intermediates
+
+// The most device memory a table takes, in all (8.9 GiB for 1024 pupil and 2048 focal samples of 16 wavelengths, 7.9
+// for 512, 768, 32 and 128 stars; of 400 problems drawn over 32 to 800 pupil samples and 2 to 40 wavelengths one or two
+// need more). A
+// constant, so that the form a problem takes does not hang on what else the device holds at the time.
+constexpr size_t kTableMaxBytes = size_t(16) << 30;
+
 struct TableProblem {
   int Ni, No, L, S, F;   // pupil and focal samples per side, wavelengths, stars per frame, frames propagated
+  int Nd;                // detector pixels per side
   bool bf16x3, dither;
   double D, dx, du;      // pupil diameter and pitch (metres), focal pitch (radians)
   double lmin, lmax;     // metres
@@ -46,6 +55,9 @@ struct TableShape {
   int n_reg;    // those in use for stars within the detector
   int h16, W, K, waves, slots;   // see TableArgs
   double tau;   // pitch, radians
+  int chunk;    // frames per chunk
+  int groups, per_group;   // star groups of the adjoint
+  size_t bytes;            // device memory, to within a few per cent
 };
 
 // False where one transform pair per star, frame and wavelength is the cheaper form.

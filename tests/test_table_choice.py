@@ -35,7 +35,7 @@ def choose(tmp_path_factory):
         assert r.returncode == 0, r.stderr
         lines = r.stdout.splitlines()
         assert len(lines) == len(problems)
-        names = ("h16", "W", "K", "waves", "Nt", "n_reg", "slots", "lds", "pairs")
+        names = ("h16", "W", "K", "waves", "Nt", "n_reg", "slots", "lds", "pairs", "chunk", "groups", "per_group", "bytes")
         return [dict(zip(names, map(int, l.split()[1:]))) if l[0] == "1" else None for l in lines]
     return run
 
@@ -43,7 +43,7 @@ def choose(tmp_path_factory):
 def problem(n_pupil, n_focal, L, stars, frames, pixel=0.5, q=1, band=(500e-9, 600e-9), bf16x3=0, dither=0):
     """`pixel`: a detector pixel in units of (band centre) / D; q focal samples across it."""
     lo, hi = band if L > 1 else (band[0], band[0])
-    return (n_pupil, n_focal, L, stars, frames, bf16x3, dither, D, pixel * 0.5 * (lo + hi) / D / q, lo, hi)
+    return (n_pupil, n_focal, L, stars, frames, n_focal // q, bf16x3, dither, D, pixel * 0.5 * (lo + hi) / D / q, lo, hi)
 
 
 def check(p, s):
@@ -51,6 +51,8 @@ def check(p, s):
     assert s["pairs"] <= 2048 and s["W"] <= 72 and s["W"] + 15 * s["h16"] // 16 < s["K"], (p, s)
     assert s["waves"] in (4, 8) and s["lds"] <= 150 * 1024, (p, s)
     assert s["Nt"] % 64 == 0 and s["n_reg"] % 64 == 0 and s["n_reg"] <= s["Nt"] <= 32064, (p, s)
+    assert 1 <= s["chunk"] <= p[4] and s["chunk"] * p[3] <= 65535 and s["bytes"] <= 16 << 30, (p, s)
+    assert (s["groups"] - 1) * s["per_group"] < s["chunk"] * p[3] <= s["groups"] * s["per_group"], (p, s)
     assert s["slots"] > 0 and s["slots"] % s["waves"] == 0, (p, s)
 
 
@@ -88,3 +90,17 @@ def test_nyquist_pixels_without_oversampling(choose, args):
     p = problem(*args)
     s = choose([p])[0]
     assert s is None or check(p, s) is None
+
+
+def test_a_table_that_needs_too_much_memory_is_not_chosen(choose):
+    """1500^2 pupils and 40 wavelengths over an octave: the table would take 73 GiB; with few wavelengths
+    and a smaller field the same detector has one. A million stars need too much for their weights."""
+    big = problem(1500, 1024, 40, 1, 64, band=(450e-9, 900e-9))
+    small = problem(600, 512, 8, 1, 64)
+    many = problem(128, 128, 24, 2, 500000)
+    few = problem(128, 128, 24, 2, 5000)
+    got = choose([big, small, many, few])
+    assert got[0] is None and got[2] is None
+    for s in (got[1], got[3]):
+        assert s is not None and s["bytes"] <= 16 << 30
+    assert got[3]["bytes"] > 10000 * 16 * got[3]["slots"]   # the stars' own arrays are counted
