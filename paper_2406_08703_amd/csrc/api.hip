@@ -12,6 +12,7 @@
 #include <new>
 #include <utility>
 
+#include "alloc.h"
 #include "dlx_internal.h"
 
 namespace dlx {
@@ -982,8 +983,8 @@ hipError_t group_small_upload(dlx_plan* p) {
                  bytes(t_z.size(), sizeof(GroupBlock)) + bytes(t_fin.size(), sizeof(GroupBlock));
   for (int c = 0; c < 5; ++c) total += bytes(t_bl[c].size(), sizeof(GroupBlock));
   char* base = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&base), total);
-  if (e != hipSuccess) return e;
+  if (!device_alloc(reinterpret_cast<void**>(&base), total)) return hipErrorOutOfMemory;
+  hipError_t e = hipSuccess;
   g.dmem_small = base;
   size_t off = 0;
   auto put = [&](const void* src, size_t nbytes) -> char* {
@@ -1049,7 +1050,7 @@ dlx_status group_build(dlx_plan* p, bool tune) {
   auto bytes = [](size_t c, size_t sz) { return (c * sz + 255) & ~size_t(255); };
   for (int s = 0; s < 4; ++s) total += bytes(n, sizeof(GemmArgs)) + bytes(g->cap_wg[s], sizeof(int2));
   total += bytes(total_src, sizeof(float));
-  if (hipMalloc(&g->dmem, total) != hipSuccess) {
+  if (!device_alloc(&g->dmem, total)) {
     group_free(g);
     p->group = nullptr;
     return DLX_ERR_OOM;
@@ -1322,7 +1323,7 @@ dlx_status create_with_table(dlx_plan* p, const dlx_problem_desc& d, int flags) 
   layout(p, sizing);
   p->pool_bytes = sizing.off + 256;
   dlx_status s = DLX_ERR_UNSUPPORTED;
-  if (hipMalloc(&p->pool, p->pool_bytes) == hipSuccess) {
+  if (device_alloc(&p->pool, p->pool_bytes)) {
     Pool pool{reinterpret_cast<char*>(p->pool), 0};
     layout(p, pool);
     const int lo_reg = (t.Nt - n_reg) / 2;
@@ -1495,7 +1496,7 @@ dlx_status create_one(const dlx_problem_desc& d, dlx_precision precision, int32_
     delete p;
     return DLX_ERR_OOM;
   }
-  if (hipMalloc(&p->pool, p->pool_bytes) != hipSuccess) {
+  if (!device_alloc(&p->pool, p->pool_bytes)) {
     delete p;
     return DLX_ERR_OOM;
   }
