@@ -51,10 +51,13 @@ bool adjoint_pair(int h16, int K) { return adjoint_lds(8, h16, K) <= 80 << 10; }
 // The table's pitch, taps and sizes for a problem, or false where one transform pair per star, frame and
 // wavelength is the cheaper form. A finer pitch (h16 up) needs fewer taps but more samples to transform;
 // the estimate weighs the folded products at their measured rate (85 TFLOP/s executed, after 15 us a
-// launch; 120 on a table, which leaves out the rows and columns no star reaches) against the FP64 matrix
+// launch, 121 in split precision; 120 on a table, which leaves out the rows and columns no star reaches) against the FP64 matrix
 // instructions of the interpolation and its adjoint (64 cycles of a SIMD each, times 1.7 and 1.8 to 2.0
 // measured), the passes over memory and 70 us for the table's seven further launches (388 focal samples, 6
-// stars, 2 wavelengths, where the estimates are near: 255 us on a table, 240 without). (512 pupil, 768 focal
+// stars, 2 wavelengths, where the estimates are near: 255 us on a table, 240 without). Of 157 FP32 problems whose
+// estimates lie 0.4 to 0.85 apart the slowest took 0.96 of the per-star time on a table, of 125 split ones 1.01;
+// 14 further split ones, taken in while the estimate had FP32's rate for them, took up to 1.28 of it (960 pupil, 320 focal
+// samples, 38 wavelengths, 3 frames: 2134 us on a table, 1673 without). (512 pupil, 768 focal
 // samples, 32 wavelengths: 128 stars 1803 us at h16 = 10, 1686 at 12, 1805 at 13; 24 stars 933 at 9, 994 at 12.)
 bool choose_table_shape(const TableProblem& p, TableShape* best) {
   // The table's products are FP32 in both arithmetics (they are a small part of the evaluation). A split
@@ -72,7 +75,8 @@ bool choose_table_shape(const TableProblem& p, TableShape* best) {
   // tilts each wavelength reduces by itself, which cost a table far more than their own transforms (52 pupil
   // and 620 focal samples, 192 stars all over them: 44 ms on a table, 6.1 ms without).
   if (No * p.du > lmin / p.dx) return false;
-  const double direct = 4.0 * n_psf * (No * Ni * Ni + No * No * Ni) / 85e6 + 60.0 + n_psf * No * No * 8.0 / 4.5e6;
+  const double rate = p.bf16x3 ? 121e6 : 85e6, launches = p.bf16x3 ? 150.0 : 60.0;
+  const double direct = 4.0 * n_psf * (No * Ni * Ni + No * No * Ni) / rate + launches + n_psf * No * No * 8.0 / 4.5e6;
   double least = 0.85 * direct;
   bool found = false;
   const int nb = ceil_div(p.No, 16);

@@ -104,3 +104,22 @@ def test_a_table_that_needs_too_much_memory_is_not_chosen(choose):
     for s in (got[1], got[3]):
         assert s is not None and s["bytes"] <= 16 << 30
     assert got[3]["bytes"] > 10000 * 16 * got[3]["slots"]   # the stars' own arrays are counted
+
+
+@pytest.mark.parametrize("args,hi", [((640, 256, 40, 1, 4), 700e-9), ((512, 384, 24, 1, 4), 700e-9),
+                                     ((960, 320, 38, 1, 3), 725e-9), ((576, 432, 32, 1, 3), 570e-9),
+                                     ((896, 256, 33, 1, 3), 565e-9), ((822, 538, 16, 1, 3), 630e-9)])
+def test_split_precision_is_weighed_at_its_own_speed(choose, args, hi):
+    """Few frames of large pupils: a table beats FP32 transforms per star, and costs 9 to 28% more than split ones."""
+    fp32, split = choose([problem(*args, band=(500e-9, hi), bf16x3=b) for b in (0, 1)])
+    assert fp32 is not None and split is None
+
+
+def test_split_precision_keeps_the_table_where_it_pays(choose):
+    """24 stars of 512 pupil and 768 focal samples and 32 wavelengths (10 times faster), and small plans of many frames,
+    whose launches cost as much in split precision (half the time and less)."""
+    joint = problem(512, 768, 32, 2, 12, q=3, band=(500e-9, 700e-9), bf16x3=1)
+    small = [problem(96, 320, 26, 1, 24, q=2, band=(500e-9, 650e-9), bf16x3=1),
+             problem(352, 32, 33, 2, 24, pixel=0.25, band=(500e-9, 730e-9), bf16x3=1),
+             problem(320, 144, 39, 2, 4, pixel=0.25, q=3, band=(500e-9, 670e-9), bf16x3=1)]
+    assert all(s is not None for s in choose([joint, *small]))
