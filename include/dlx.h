@@ -168,9 +168,11 @@ enum {
  * holds the table for stars anywhere in the pupil grid's own field, in 16 GiB at
  * most; where the device has not that much left, the plan takes the other form
  * (dlx_plan_table_samples says 0). A plan with a workspace limit, with
- * DLX_FLAG_DENSE_MFT or DLX_FLAG_GROUPED keeps one transform per star, frame
- * and wavelength, and so does a plan of one wavelength (whose nulls no band
- * fills) and a DLX_BF16X3 plan of fewer than 16. */
+ * DLX_FLAG_DENSE_MFT, or whose problems DLX_FLAG_GROUPED runs together (one frame
+ * each, no map, no integer dithers) keeps one transform per star, frame and
+ * wavelength, and so does a plan of one wavelength (whose nulls no band fills)
+ * and a DLX_BF16X3 plan of fewer than 16; where that flag does not apply it
+ * changes nothing here either. */
 
 /* DLX_FLAG_PIXEL_KERNEL gives every detector pixel its own intra-pixel kernel
  * (Section 6: intra-pixel sensitivity, recoverable at this sampling): every
