@@ -114,7 +114,9 @@ void layout_images(dlx_plan* p, Pool& pool) {
   t.wt = pool.take<double>((size_t)t.nfs * table_weight_count(t.K));
   t.base = pool.take<int>(2 * (size_t)t.nfs);
   t.far = pool.take<int>(t.nfs);
-  t.range = pool.take<int>(2);
+  t.range = pool.take<int>(3);
+  t.need = pool.take<unsigned char>((1 + (size_t)p->L) * (t.Nt / 32) * (t.Nt / 32));
+  t.need_rows = pool.take<unsigned char>((1 + (size_t)p->L) * (t.Nt / 32));
   t.dark_n = pool.take<int>(p->n_chunks);
   t.dark = pool.take<int>(fc * p->S * t.nb * t.nb);
   t.planes = pool.take<float>(fc * p->S * No * ldNo);
@@ -194,6 +196,8 @@ GemmArgs base_args(const dlx_plan* p, int f0, int nframes) {
   a.wl = p->d_wl;
   a.xcoord = p->d_x;
   a.range = p->range;
+  a.need = p->need;
+  a.need_rows = p->need_rows;
   return a;
 }
 
@@ -1245,6 +1249,7 @@ T* at(T* base, long long off) {
 // What a PSF table's own plan takes from the outer one.
 struct TableInner {
   const int* range;
+  const unsigned char *need, *need_rows;
   int lo_reg;
   float* H;
   double du;   // the focal grid's pitch: the field's factor dx du / lambda is that grid's, not the table's
@@ -1317,6 +1322,7 @@ dlx_status create_with_table(dlx_plan* p, const dlx_problem_desc& d, int flags) 
   p->n_chunks = p->ta.n_chunks = ceil_div(p->F, fc);
   p->chunk_psf = fc * p->S * p->L;
   p->n_reg = n_reg;
+  p->ta.lo_sparse = (t.Nt - n_reg) / 2 - n_reg / 8;
   p->loss_blocks = loss_block_count((long long)p->Nd_img * p->Nd_img);
   p->seed_blocks = seed_block_count((long long)p->Nd * p->Nd);
   Pool sizing{nullptr, 0};
@@ -1327,7 +1333,7 @@ dlx_status create_with_table(dlx_plan* p, const dlx_problem_desc& d, int flags) 
     Pool pool{reinterpret_cast<char*>(p->pool), 0};
     layout(p, pool);
     const int lo_reg = (t.Nt - n_reg) / 2;
-    const int range[2] = {lo_reg, 0};
+    const int range[3] = {lo_reg, 0, 0};
     const float unit[3] = {0.f, 0.f, 1.f};
     hipError_t e = hipMemset(p->pool, 0, p->pool_bytes);
     if (e == hipSuccess) e = hipMemcpy(p->ta.range, range, sizeof range, hipMemcpyHostToDevice);
@@ -1340,7 +1346,7 @@ dlx_status create_with_table(dlx_plan* p, const dlx_problem_desc& d, int flags) 
     td.n_sources = td.n_frames = 1;
     td.focal_pixel_rad = t.tau;
     td.frame_dithers = nullptr;
-    const TableInner inner{p->ta.range, lo_reg, p->ta.H, p->du};
+    const TableInner inner{p->ta.range, p->ta.need, p->ta.need_rows, lo_reg, p->ta.H, p->du};
     s = e != hipSuccess ? DLX_ERR_HIP
                         : create_one(td, DLX_FP32, flags & DLX_FLAG_NO_AUTOTUNE, 0, false, &inner, &p->tab);
     if (s == DLX_ERR_OOM) s = DLX_ERR_UNSUPPORTED;
@@ -1401,6 +1407,8 @@ dlx_status create_one(const dlx_problem_desc& d, dlx_precision precision, int32_
   p->n_psf = p->F * p->S * p->L;
   if (inner) {
     p->range = inner->range;
+    p->need = inner->need;
+    p->need_rows = inner->need_rows;
     p->lo_reg = inner->lo_reg;
   }
 

@@ -108,8 +108,11 @@ struct GemmArgs {
   // packed sources (the launch passes the base; `sources` above is unused there)
   long long src_off;
   // PSF table (see TableArgs): range[0] is the first table row and column in use (the last is
-  // mirror-symmetric), range[1] is nonzero when every wavelength has its own seed weights
+  // mirror-symmetric), range[1] is nonzero when every wavelength has its own seed weights, range[2] when
+  // only the tiles marked in `need` (and the rows in `need_rows`) are in use
   const int* range;
+  const unsigned char* need;
+  const unsigned char* need_rows;
   long long seedw_by_wl;
 };
 
@@ -152,7 +155,14 @@ struct TableArgs {
   double* wt;              // weights [nfs][2][16][K and padding] (x, y)
   int* base;               // first table sample of block 0 [nfs][2]
   int* far;                // [nfs] 1: a tilt beyond half_min
-  int* range;              // {lo, any far star}
+  int* range;              // {lo, any far star, only marked tiles are in use}
+  // With stars so far out that the table in use would be a quarter wider than the launches are sized for (first row
+  // below lo_sparse) its blocks of 32 x 32 samples are used sparsely: need[p][Nt / 32][Nt / 32] marks those that a star's window reaches (kReach),
+  // and those whose samples it takes to form the derivatives there (kNeed), p = 0 for every wavelength, 1 + l for
+  // wavelength l of stars reduced by its own period; need_rows[p][Nt / 32] likewise for rows with such a block.
+  int lo_sparse;
+  unsigned char* need;
+  unsigned char* need_rows;
   double root_peak;        // the image's largest possible sample, sum_l |w_l| (Ni dx du / lambda_l)^2: its root
   int n_chunks;
   int* dark_n;             // [n_chunks] blocks of the chunk's images that are interpolated from the fields
@@ -163,6 +173,8 @@ struct TableArgs {
   float* H;                // table seed weights [1 + L][Nt][Nt]
   double* pos;             // [nfs][slots][2]
 };
+
+constexpr unsigned char kNeed = 1, kReach = 2;
 
 // Tile shape of one GEMM launch: 4 waves (2 x 2), each WM x WN blocks of 16 x 16.
 struct TileShape {
@@ -393,7 +405,9 @@ struct dlx_plan {
   dlx::TableArgs ta = {};
   int n_reg = 0;                 // table samples per side in use when the stars lie within the detector
   const int* range = nullptr;    // a table's own plan: the outer plan's range
-  int lo_reg = 0;                // and the first row in use for n_reg
+  const unsigned char* need = nullptr;       // and its marks
+  const unsigned char* need_rows = nullptr;
+  int lo_reg = 0;                // the first row in use for n_reg
   // stored columns of the seed weights: natural order with a table, else the fold's
   int ghNo() const { return tab ? No : hNo(); }
   int gsNo() const { return tab ? 0 : sNo(); }

@@ -593,8 +593,18 @@ struct TileRange {
 // 3.7e-7 of the flat-field gradient's norm; 9e-8 and 9e-7 in one running sum, 6.6e-8 and 6.7e-7 with one
 // transform per frame. F2 takes 939 us with the partial sums, whose registers leave two workgroups per CU,
 // 865 us without.)
-template <int KIND, int WM, int WN, int PREC, bool TAB = false>
-__device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const float* src, const TileRange tr) {
+// LIST (B3 of a table whose blocks are used sparsely): the k-stages start at klist[0 .. n_list), all whole.
+// The two forms of that stage share the kernel's LDS buffers, `lds`.
+template <int KIND, int WM, int WN, int PREC>
+constexpr int fold_lds_elements() {
+  constexpr int CH = PREC == 0 ? 4 : 8, ND = PREC == 0 ? 2 : 4, NX = PREC == 0 ? 4 : 8, BM = 32 * WM, BN = 32 * WN;
+  constexpr bool DA = KIND != KIND_F2;
+  return (PREC == 0 ? 2 : 1) * 4 * CH * (ND * (DA ? BM : BN) + NX * (DA ? BN : BM));
+}
+
+template <int KIND, int WM, int WN, int PREC, bool TAB = false, bool LIST = false>
+__device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const float* src, const TileRange tr,
+                                           float* lds = nullptr, const unsigned short* klist = nullptr, int n_list = 0) {
   constexpr bool DA = KIND != KIND_F2;   // DFT operand on the A side (rows i), data on the B side
   constexpr int BM = 32 * WM, BN = 32 * WN;
   constexpr int BK = PREC == 0 ? 16 : 32;
@@ -611,7 +621,10 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
   // FP32 runs a two-buffer pipeline (below); BF16X3 one LDS buffer
   constexpr bool PIPE = PREC == 0;
   constexpr int BUF_EL = D_EL + X_EL;
-  __shared__ __attribute__((aligned(16))) el_t smem[(PIPE ? 2 : 1) * BUF_EL];
+  static_assert((PIPE ? 2 : 1) * BUF_EL == fold_lds_elements<KIND, WM, WN, PREC>(), "");
+  constexpr bool SHARED_LDS = TAB && KIND == KIND_B3;
+  __shared__ __attribute__((aligned(16))) el_t own_lds[SHARED_LDS ? 4 : (PIPE ? 2 : 1) * BUF_EL];
+  el_t* const smem = SHARED_LDS ? reinterpret_cast<el_t*>(lds) : own_lds;
   constexpr int kPosSlots = KIND == KIND_B4 ? 32 : 1;
   __shared__ double spos[kPosSlots][4][2];   // B4: per-PSF, per-wave position partials
 
@@ -668,7 +681,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
     k_lo = tr.k0 + ks * kc;
     k_hi = min(K, k_lo + kc);
   }
-  const int nk = k_hi > k_lo ? (k_hi - k_lo + BK - 1) / BK : 0;
+  const int nk = LIST ? n_list : k_hi > k_lo ? (k_hi - k_lo + BK - 1) / BK : 0;
 
   // Items run wavelength-major: item it is the chunk's PSF (it % nfs) L + it / nfs, so consecutive
   // items (and the contiguous workgroup ranges of one XCD) share a wavelength's DFT matrix (and, for
@@ -707,6 +720,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
   u4 xn[X_U][2 * V], xm[X_U][2 * V];   // re, im at the natural chunk and at the mirror chunk
   u4 w0[X_U][V], w1[X_U][V];           // F1: ty re, im at k; B3: G at k and at the mirror
   int gx_k[X_U];
+  unsigned char on_n[LIST ? X_U : 1], on_m[LIST ? X_U : 1];   // marks of the table blocks at the two chunks
 
   auto load_tile = [&](int k0) {
 #pragma unroll
@@ -823,6 +837,17 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
           w0[r][v] = hg ? g0 : one;
           w1[r][v] = hg ? g1 : one;
         }
+        if constexpr (LIST) {
+          const int side = nX / 32, i = gj >> 5, j = gkc >> 5, jm = side - 1 - j;
+          const unsigned char* p = a.need + (long long)i * side;
+          on_n[r] = p[j];
+          on_m[r] = p[jm];
+          if (a.range[1]) {
+            p += (long long)(1 + item) * side * side;   // (one star: the item is the wavelength)
+            on_n[r] |= p[j];
+            on_m[r] |= p[jm];
+          }
+        }
       }
     }
   };
@@ -910,6 +935,11 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
             xi = g * xi;
             yr = gm * yr;
             yi = gm * yi;
+            if constexpr (LIST) {   // a block that no star reaches holds neither fields nor weights
+              const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
+              if (!(on_n[r] & kReach)) xr = xi = zero;
+              if (!(on_m[r] & kReach)) yr = yi = zero;
+            }
           }
           // K tail and the unpaired middle term (assigned after the products: padding is not read)
           const int kb = gx_k[r] + 4 * v;
@@ -1001,7 +1031,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
   // pipelined stream state: the tile count, the PSF the loader points at, the full k-stages
   int ts = 0, lpsf = p_begin;
   const int k_full = a.kodd ? min(k_hi, K - 1) : k_hi;
-  const int nfull = max(0, (k_full - k_lo) / BK);   // k-stages [0, nfull) hold full tiles
+  const int nfull = LIST ? nk : max(0, (k_full - k_lo) / BK);   // k-stages [0, nfull) hold full tiles
   for (int it = p_begin; it < p_end; ++it) {
     const int lb = (it % nfs) * a.L + it / nfs;
     const int gb = a.psf0 + lb;
@@ -1177,12 +1207,13 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
         }
         mma(smem + (kt & 1) * BUF_EL);
       } else {
-        load_tile_c(k_lo);
+        auto at = [&](int t) { return LIST ? (int)klist[min(t, nk - 1)] : k_lo + t * BK; };
+        load_tile_c(at(0));
         if (nfull > 0)
           store_tile(smem, std::false_type{});
         else
           store_tile(smem, std::true_type{});
-        load_tile_c(k_lo + BK);
+        load_tile_c(at(1));
         __syncthreads();
         f4 tot[PARTS ? WM : 1][PARTS ? WN : 1][4];
         if constexpr (PARTS) {
@@ -1212,7 +1243,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
         for (; kt + 1 < nfull; ++kt) {   // the next tile is full: one basic block per stage
           mma(smem + (kt & 1) * BUF_EL);
           store_tile(smem + ((kt + 1) & 1) * BUF_EL, std::false_type{});
-          load_tile_c(k_lo + (kt + 2) * BK);
+          load_tile_c(at(kt + 2));
           pipe_schedule();
           __syncthreads();
           if constexpr (PARTS)
@@ -1222,7 +1253,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
           mma(smem + (kt & 1) * BUF_EL);
           if (kt + 1 < nk) {
             store_tile(smem + ((kt + 1) & 1) * BUF_EL, std::true_type{});
-            load_tile_c(k_lo + (kt + 2) * BK);
+            load_tile_c(at(kt + 2));
           }
           __syncthreads();
         }
@@ -1474,13 +1505,45 @@ __global__ __launch_bounds__(256, PREC == 0 ? 2 : 1) void fgemm_kernel(const Gem
                                  TileRange{0, 0, a.tiles_m, a.tiles_n, 0});
 }
 
+// Whether any block of the table's rows [i0, i0 + ni) and folded columns [j0, j0 + nj) (blocks of 32 samples; with
+// every column its mirror) carries `mark` at wavelength wl; nj 0: whether any block of the rows does.
+__device__ __forceinline__ bool marked(const GemmArgs& a, int side, int wl, int i0, int ni, int j0, int nj, bool mirror_rows,
+                                       unsigned char mark) {
+  const int lane = threadIdx.x & 63, n = nj > 0 ? ni * nj * 2 : 2 * ni;   // at most 4 x 4 x 2
+  bool on = false;
+  if (lane < n) {
+    const int m = lane & 1, e = lane >> 1;
+    int i = i0 + (nj > 0 ? e / nj : e);
+    if (i < side) {
+      long long o;
+      const unsigned char* p;
+      if (nj > 0) {
+        const int j = j0 + e % nj, jj = m ? side - 1 - j : j;
+        o = (long long)i * side + jj;
+        p = a.need;
+        on = j < side && (p[o] & mark) != 0;
+        if (a.range[1] && j < side) on |= (p[(long long)(1 + wl) * side * side + o] & mark) != 0;
+      } else {
+        if (m && mirror_rows) i = side - 1 - i;
+        p = a.need_rows;
+        on = (p[i] & mark) != 0;
+        if (a.range[1]) on |= (p[(1 + wl) * side + i] & mark) != 0;
+      }
+    }
+  }
+  return __any(on);
+}
+
 // A folded stage on the PSF table: only rows and columns [lo, Nt - lo) are in use, lo = a.range[0] (a
 // multiple of 32) being set on the device by the stars' positions. The tiles in use are enumerated
-// compactly; the grid is sized for stars within the detector and each workgroup strides over the rest.
+// compactly; the grid is sized for stars within the detector and each workgroup strides over the rest. With
+// stars outside that (a.range[2]) only the marked blocks are in use: tiles of F1 and F2 without one are left out, B3
+// contracts over the columns that are reached in its rows, and fills U^T with zeros where none is (B4 reads all).
 template <int KIND, int WM, int WN>
 __global__ __launch_bounds__(256, 2) void fgemm_table_kernel(const GemmArgs a) {
   constexpr int BM = 32 * WM, BN = 32 * WN;
   const int lo = a.range[0];
+  const bool sparse = a.range[2] != 0;
   TileRange tr{0, 0, a.tiles_m, a.tiles_n, 0};
   if constexpr (KIND == KIND_F1) {   // rows: the folded half of the table
     tr.tm0 = lo / BM;
@@ -1498,8 +1561,66 @@ __global__ __launch_bounds__(256, 2) void fgemm_table_kernel(const GemmArgs a) {
     tr.k0 = lo;
   }
   const int total = tr.tiles_m * tr.tiles_n * a.n_items;
+  __shared__ __attribute__((aligned(16))) float lds[KIND == KIND_B3 ? fold_lds_elements<KIND, WM, WN, 0>() : 4];
   for (int w = blockIdx.x; w < total; w += gridDim.x) {
-    fgemm_body<KIND, WM, WN, 0, true>(a, xcd_remap(w, total), a.sources, tr);
+    const int lin = xcd_remap(w, total);
+    if (sparse && KIND != KIND_B4) {
+      // (one star: the item is the wavelength; tiles as fgemm_body numbers them)
+      const int tiles = tr.tiles_m * tr.tiles_n, wl = lin / tiles, tile = lin - wl * tiles;
+      const int tm = tr.tm0 + (KIND == KIND_B3 ? tile % tr.tiles_m : tile / tr.tiles_n);
+      const int tn = tr.tn0 + (KIND == KIND_B3 ? tile / tr.tiles_m : tile % tr.tiles_n);
+      if constexpr (KIND == KIND_F1) {
+        if (!marked(a, a.M / 16, wl, WM * tm, WM, 0, 0, true, kNeed)) continue;
+      } else if constexpr (KIND == KIND_F2) {
+        if (!marked(a, a.M / 32, wl, WM * tm, WM, WN * tn, WN, false, kNeed)) continue;
+      } else if constexpr (KIND == KIND_B3) {
+        const int side = a.N / 32, lane = threadIdx.x & 63;
+        if (!marked(a, side, wl, WN * tn, WN, 0, 0, false, kReach)) {
+          float* ob = static_cast<float*>(a.out) + (long long)wl * a.out_by_psf;
+          for (int e = threadIdx.x; e < BM * BN; e += 256) {
+            const int i = BM * tm + e / BN, j = BN * tn + e % BN;
+            if (i >= a.M || j >= a.N) continue;
+            const long long c = j < a.out_h ? j : j + a.out_s, o = (long long)i * a.ldo + c;
+            const long long om = (long long)(a.mirror_n - 1 - i) * a.ldo + c;
+            ob[o] = ob[a.out_plane + o] = ob[om] = ob[a.out_plane + om] = 0.f;
+          }
+          continue;
+        }
+        __shared__ unsigned short klist[1024];   // a table has at most 32064 samples: 501 blocks of two k-stages
+        __shared__ int klen;
+        if (threadIdx.x < 64) {
+          int n = 0;
+          for (int b = lo / 32; b < side / 2; b += 64) {
+            const int j = b + lane;
+            unsigned char v = 0;
+            for (int k = 0; k < WN && j < side / 2; ++k) {
+              const int i = WN * tn + k;
+              if (i >= side) continue;
+              const long long o = (long long)i * side + j, om = (long long)i * side + side - 1 - j;
+              v |= a.need[o] | a.need[om];
+              if (a.range[1]) {
+                const unsigned char* p = a.need + (long long)(1 + wl) * side * side;
+                v |= p[o] | p[om];
+              }
+            }
+            const bool on = (v & kReach) != 0;
+            const unsigned long long m = __ballot(on);
+            if (on) {
+              const int q = 2 * (n + __popcll(m & ((1ull << lane) - 1)));
+              klist[q] = (unsigned short)(32 * j);
+              klist[q + 1] = (unsigned short)(32 * j + 16);
+            }
+            n += __popcll(m);
+          }
+          if (lane == 0) klen = 2 * n;
+        }
+        __syncthreads();
+        fgemm_body<KIND, WM, WN, 0, true, true>(a, lin, a.sources, tr, lds, klist, klen);
+        __syncthreads();
+        continue;
+      }
+    }
+    fgemm_body<KIND, WM, WN, 0, true>(a, lin, a.sources, tr, lds);
     __syncthreads();   // the next tile reuses the LDS buffers
   }
 }

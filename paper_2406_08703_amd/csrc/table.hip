@@ -71,11 +71,72 @@ __device__ __forceinline__ double reduced(const TableArgs& t, double pos, int l)
 // any b, 0 <= q < K, with zeros around them, so that a shifted window reads zeros where it leaves the K
 // samples.
 // Block 0 sets range[0], the first table row in use: the largest offset of a star, half the focal grid,
-// and W samples on either side (half for the interpolation, half for the derivative's stencil).
+// and W samples on either side (half for the interpolation, half for the derivative's stencil); and where that
+// is far out, or a star's tilts are reduced, marks the blocks in use.
+
+// The blocks of 32 x 32 samples that the stars' windows reach, and around them those whose samples go into
+// the derivatives there: the band of the derivative's products covers 47 samples more than half its taps. Stars
+// that need no more than the rows and columns from lo_sparse on share one square; the others have their own.
+__device__ __forceinline__ void mark_blocks(const TableArgs& t, const float* sources, int lo, bool far) {
+  const int side = t.Nt / 32, first = lo / 32, last = side - 1 - first, planes = far ? 1 + t.L : 1;
+  for (long long i = threadIdx.x; i < (long long)planes * side * side / 4; i += 256) reinterpret_cast<int*>(t.need)[i] = 0;
+  for (int i = threadIdx.x; i < planes * side; i += 256) t.need_rows[i] = 0;
+  const int lane = threadIdx.x & 63, wave = wave_id(), span = t.h16 * (t.nb - 1) + t.K - 1;
+  const double half = 0.5 * t.Nt - 0.5 * (double)(t.No - 1) * t.h16 / 16.0 - t.W - 4.0;   // see range[0]
+  const double inner = (half - max(t.lo_sparse, 0)) * t.tau;
+  auto outlying = [&](int fs) {   // (a position that is not finite has the axis' window)
+    return t.far[fs] || fabs((double)sources[fs * 3]) > inner || fabs((double)sources[fs * 3 + 1]) > inner;
+  };
+  __shared__ double sm[4];
+  double m = 0.0;
+  for (int fs = threadIdx.x; fs < t.nfs; fs += 256)
+    if (!outlying(fs)) m = fmax(m, fmax(fabs((double)sources[fs * 3]), fabs((double)sources[fs * 3 + 1])));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+  if (lane == 0) sm[wave] = m;
+  __syncthreads();
+  const int c0 = max((int)(half - fmax(fmax(sm[0], sm[1]), fmax(sm[2], sm[3])) / t.tau), 0);
+  for (int pass = 0; pass < 2; ++pass) {
+    const unsigned char v = pass ? kNeed | kReach : kNeed;
+    const int pad = pass ? 0 : t.W / 2 + 64;
+    __syncthreads();   // the stores of one pass before the next
+    const int b0 = max(floor_div(c0 - pad, 32), first), b1 = side - 1 - b0, nb = b1 - b0 + 1;
+    for (int e = threadIdx.x; e < nb * nb; e += 256) t.need[(long long)(b0 + e / nb) * side + b0 + e % nb] = v;
+    for (int e = threadIdx.x; e < nb; e += 256) t.need_rows[b0 + e] = v;
+    for (int fs = wave; fs < t.nfs; fs += 4) {
+      if (!outlying(fs)) continue;
+      const int wls = t.far[fs] ? t.L : 1;
+      for (int l = 0; l < wls; ++l) {
+        double x = sources[fs * 3], y = sources[fs * 3 + 1];
+        int plane = 0, jx, jy;
+        if (t.far[fs]) {
+          x = reduced(t, x, l);
+          y = reduced(t, y, l);
+          plane = 1 + l;
+        }
+        star_origin(t, x, jx);
+        star_origin(t, y, jy);
+        const int x0 = max(floor_div(jx - pad, 32), first), x1 = min(floor_div(jx + span + pad, 32), last);
+        const int y0 = max(floor_div(jy - pad, 32), first), y1 = min(floor_div(jy + span + pad, 32), last);
+        const int nx = x1 - x0 + 1, ny = y1 - y0 + 1;
+        if (nx <= 0 || ny <= 0) continue;
+        unsigned char* need = t.need + (long long)plane * side * side;
+        for (int e = lane; e < nx * ny; e += 64) need[(long long)(y0 + e / nx) * side + x0 + e % nx] = v;
+        for (int e = lane; e < ny; e += 64) t.need_rows[plane * side + y0 + e] = v;
+      }
+    }
+  }
+}
+
+// whether the block of 32 x 32 samples at block row i and column j carries `mark` for every wavelength
+__device__ __forceinline__ bool block_marked(const TableArgs& t, int i, int j, unsigned char mark) {
+  return (t.need[(long long)i * (t.Nt / 32) + j] & mark) != 0;
+}
+
 __global__ __launch_bounds__(256) void table_weights_kernel(const TableArgs t, const float* sources) {
   if (blockIdx.x == 0) {
     __shared__ double sm[4];
-    __shared__ int sf[4];
+    __shared__ int sf[4], s_lo;
     double m = 0.0;
     int any = 0;
     for (int fs = threadIdx.x; fs < t.nfs; fs += 256) {
@@ -104,9 +165,14 @@ __global__ __launch_bounds__(256) void table_weights_kernel(const TableArgs t, c
       m = fmax(fmax(sm[0], sm[1]), fmax(sm[2], sm[3]));
       const double half = 0.5 * (double)(t.No - 1) * t.h16 / 16.0 + m / t.tau + t.W + 4.0;
       const double lo = floor((0.5 * t.Nt - half) / 32.0) * 32.0;
-      t.range[0] = lo > 0.0 ? (int)lo : 0;
-      t.range[1] = sf[0] | sf[1] | sf[2] | sf[3];
+      s_lo = lo > 0.0 ? (int)lo : 0;
+      sf[0] |= sf[1] | sf[2] | sf[3];
+      t.range[0] = s_lo;
+      t.range[1] = sf[0];
+      t.range[2] = sf[0] || s_lo < t.lo_sparse;
     }
+    __syncthreads();
+    if (sf[0] || s_lo < t.lo_sparse) mark_blocks(t, sources, s_lo, sf[0] != 0);
     for (int i = threadIdx.x; i < t.n_chunks; i += 256) t.dark_n[i] = 0;
     return;
   }
@@ -131,9 +197,11 @@ __device__ __forceinline__ double power(float er, float ei) {
 // field of the table is read once.
 __global__ __launch_bounds__(256) void table_image_kernel(const TableArgs t) {
   const int lo = t.range[0], n = t.Nt - 2 * lo, nq = n / 4;
+  const bool sparse = t.range[2] != 0;
   const long long total = (long long)n * nq;
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
     const int r = (int)(i / nq), c = (int)(i - (long long)r * nq);
+    if (sparse && !block_marked(t, (lo + r) >> 5, (lo + 4 * c) >> 5, kNeed)) continue;
     const long long o = (long long)(lo + r) * t.Nt + lo + 4 * c;
     const float* e = t.E + o;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -153,44 +221,54 @@ __global__ __launch_bounds__(256) void table_image_kernel(const TableArgs t) {
 // Derivatives of the table image at its own samples, Ix[j] = sum_n phi'(n) I[j - n] and likewise along y
 // (phi'(n) = (-1)^n / n times the window: the interpolation kernel's derivative at whole distances).
 // Samples outside the range in use count as the edge's: only nodes no star's samples touch see them.
-constexpr int kMaxHalfTaps = 48;
-static_assert(kTableMaxW <= 2 * kMaxHalfTaps, "a stencil holds half the taps of any window");
+constexpr int kMid = 96;   // a band's place, 16 and up to 31 more columns around half the taps
+static_assert(kTableMaxW / 2 + 47 < kMid, "");
 
-template <class F>
-__device__ __forceinline__ void stencil(const double* cf, int nh, int r, int c, int lo, int hi, F at, double& dx,
-                                        double& dy) {
-  dx = dy = 0.0;
-  for (int n = 1; n <= nh; ++n) {
-    const int cm = iclamp(c - n, lo, hi), cp = iclamp(c + n, lo, hi);
-    const int rm = iclamp(r - n, lo, hi), rp = iclamp(r + n, lo, hi);
-    dx = fma(cf[n], at(r, cm) - at(r, cp), dx);
-    dy = fma(cf[n], at(rm, c) - at(rp, c), dy);
+// s[d + kMid]: weight of the sample d to the right of (or below) the result
+__device__ __forceinline__ void band_weights(double* s, const TableArgs& t) {
+  if (threadIdx.x < 2 * kMid) {
+    const int d = (int)threadIdx.x - kMid, n = d < 0 ? -d : d;
+    const double v = n == 0 || n > t.W / 2 ? 0.0 : ((n & 1) ? -1.0 : 1.0) / (double)n * window((double)n, t.W, t.beta);
+    s[threadIdx.x] = d < 0 ? v : -v;
   }
 }
 
-__device__ __forceinline__ void stencil_weights(double* cf, const TableArgs& t) {
-  for (int n = threadIdx.x + 1; n <= t.W / 2; n += blockDim.x)
-    cf[n] = ((n & 1) ? -1.0 : 1.0) / (double)n * window((double)n, t.W, t.beta);
+// The 16 x 16 derivatives at (R, C) of the samples at(row, column), by one wave.
+template <class F>
+__device__ __forceinline__ void slopes16(const double* s, int H, int R, int C, int lo, int hi, F at, d4& dx, d4& dy) {
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  dx = dy = d4{0.0, 0.0, 0.0, 0.0};
+  for (int p0 = 0; 4 * p0 < 16 + 2 * H; p0 += 4) {   // (the weights are zero past the band)
+    double v[4], u[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int o = 4 * (p0 + i) + g - H;
+      v[i] = at(R + n, iclamp(C + o, lo, hi));
+      u[i] = at(iclamp(R + o, lo, hi), C + n);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const double w = s[4 * (p0 + i) + g - H - n + kMid];
+      dx = mfma_f64(v[i], w, dx);
+      dy = mfma_f64(w, u[i], dy);
+    }
+  }
 }
 
 // As products with the banded matrix of the stencil (FP64 matrix instructions, 16 x 16 samples per wave and
 // direction): the 2 W loads and products per sample of the plain sum took 174 us for 2112^2 samples and 64
 // taps, about 55 us here (18 us of matrix instructions).
 __global__ __launch_bounds__(256) void table_slope_kernel(const TableArgs t) {
-  constexpr int kMid = 96;   // a band's place, 16 and up to 31 more columns around half the taps
-  static_assert(kTableMaxW / 2 + 47 < kMid, "");
-  __shared__ double s[2 * kMid];   // s[d + kMid]: weight of the sample d to the right of (or below) the result
+  __shared__ double s[2 * kMid];
   const int H = t.W / 2;
-  if (threadIdx.x < 2 * kMid) {
-    const int d = (int)threadIdx.x - kMid, n = d < 0 ? -d : d;
-    const double v = n == 0 || n > H ? 0.0 : ((n & 1) ? -1.0 : 1.0) / (double)n * window((double)n, t.W, t.beta);
-    s[threadIdx.x] = d < 0 ? v : -v;
-  }
+  band_weights(s, t);
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = wave_id(), n = lane & 15, g = lane >> 4;
   const int lo = t.range[0], hi = t.Nt - lo - 1, side = (t.Nt - 2 * lo) / 32;
+  const bool sparse = t.range[2] != 0;
   const long long ld = t.Nt;
   for (int tile = blockIdx.x; tile < side * side; tile += gridDim.x) {
+    if (sparse && !block_marked(t, lo / 32 + tile / side, lo / 32 + tile % side, kReach)) continue;
     const int R = lo + 32 * (tile / side) + 16 * (wave >> 1), C = lo + 32 * (tile % side) + 16 * (wave & 1);
     d4 dx = d4{0.0, 0.0, 0.0, 0.0}, dy = d4{0.0, 0.0, 0.0, 0.0};
     // along x: rows of I times the band; a lane's two samples 8 p + 2 g and the next are one product's term each
@@ -250,12 +328,12 @@ __device__ __forceinline__ void add_dark(const TableArgs& t, int chunk, int star
   if ((threadIdx.x & 63) == 0) t.dark[atomicAdd(t.dark_n + chunk, 1)] = (star * t.nb + yb) * t.nb + xb;
 }
 
-// the same for one wavelength of a star whose tilt is reduced per wavelength
+// The weights of one wavelength of a star whose tilt is reduced by its period, by one wave into its own LDS.
 __device__ __forceinline__ void far_weights(const TableArgs& t, const float* src, int l, double* wx, double* wy,
                                             int& jx, int& jy) {
   const int KS = wrow(t.K);
   const double fx = star_origin(t, reduced(t, src[0], l), jx), fy = star_origin(t, reduced(t, src[1], l), jy);
-  for (int e = threadIdx.x; e < 16 * KS; e += 256) {
+  for (int e = threadIdx.x & 63; e < 16 * KS; e += 64) {
     const int a = e / KS, q = e - a * KS - kPadL;
     const bool in = q >= 0 && q < t.K;
     const double s = (double)(a * t.h16) / 16.0 - (double)q;
@@ -569,10 +647,18 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 2) void table_adjoint_kernel(co
     for (int i = 0; i < kPairs; ++i)
       if ((int)threadIdx.x + TH * i < n2) nw[i] = src[threadIdx.x + TH * i];
   };
+  const bool sparse = t.range[2] != 0;
+  bool again = false;
   for (int tile = wg; tile < nrt * ncg; tile += nwg) {
     const int R0 = lo + 32 * (tile % nrt), C0 = lo + CW * (tile / nrt);
     const int c = C0 + 16 * wave;   // this wave's columns
-    const bool live = c <= hi;
+    bool live = c <= hi;
+    if (sparse) {   // (what no star reaches is neither computed nor read)
+      bool any = false;
+      for (int k = 0; k < CW; k += 32) any |= C0 + k <= hi && block_marked(t, R0 >> 5, (C0 + k) >> 5, kReach);
+      if (!any) continue;
+      live = live && block_marked(t, R0 >> 5, c >> 5, kReach);
+    }
     const long long t0 = (long long)R0 * t.Nt + (live ? c : lo);   // the tile, and this lane's place in it
     const unsigned o0 = (unsigned)(g * t.Nt + n);
     d4 H[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
@@ -672,25 +758,27 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 2) void table_adjoint_kernel(co
         }
       }
       double px = 0.0, py = 0.0;
+      if (live) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const double d = phi * D[i][r];
-          H[i][r] += d;
-          px = fma(d, (double)gx[4 * i + r], px);
-          py = fma(d, (double)gy[4 * i + r], py);
-        }
+          for (int r = 0; r < 4; ++r) {
+            const double d = phi * D[i][r];
+            H[i][r] += d;
+            px = fma(d, (double)gx[4 * i + r], px);
+            py = fma(d, (double)gy[4 * i + r], py);
+          }
+      }
       px = wave_total(px);
       py = wave_total(py);
       if (lane == 63) {
         double* o = t.pos + ((long long)fs * t.slots + slot) * 2;
-        const bool again = tile != wg;
         o[0] = (again ? o[0] : 0.0) - px / t.tau;
         o[1] = (again ? o[1] : 0.0) - py / t.tau;
       }
       fs = after;
     }
+    again = true;
     if (live) {
       double* h = t.Hpart + group * (long long)t.Nt * t.Nt + t0;
 #pragma unroll
@@ -704,74 +792,80 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 2) void table_adjoint_kernel(co
   }
 }
 
-// The same for stars whose tilt is reduced per wavelength, one wavelength after the other, each into that
-// wavelength's own plane of H (table_seed_kernel adds the common one). A wave owns 32 x 32 samples; no star
-// of a sampled pupil's own field comes here, so it is kept simple.
+// The same for stars whose tilt is reduced per wavelength, each into that wavelength's own plane of H
+// (table_seed_kernel adds the common one). The blocks of 32 x 32 samples that one of these stars reaches at a
+// wavelength are shared out over all waves; a wave forms the derivatives of its block from the field, once, and
+// the seed weights of every such star there. (One such star among
+// 24, 32 wavelengths of 768 focal samples: 3.7 ms; 33 ms one wavelength and one star after the other over the whole table.)
 __global__ __launch_bounds__(256) void table_far_kernel(const TableArgs t, const float* sources, int f0, int nf,
                                                         int first) {
   extern __shared__ double sh[];
-  __shared__ double cf[kMaxHalfTaps + 1];
+  __shared__ double s[2 * kMid];
   if (!t.range[1]) return;
-  const int KS = wrow(t.K);
-  double *wx = sh, *wy = sh + 16 * KS;
-  const int lane = threadIdx.x & 63, wave = wave_id(), n = lane & 15, g = lane >> 4;
-  const int lo = t.range[0], hi = t.Nt - lo - 1;
-  const int nt = (t.Nt - 2 * lo) / 32, ntile = nt * nt;
-  const int slot = blockIdx.x * 4 + wave;
-  stencil_weights(cf, t);
-  for (int l = 0; l < t.L; ++l) {
-    for (int t0 = blockIdx.x * 4; t0 < ntile; t0 += gridDim.x * 4) {
-      const bool live = t0 + wave < ntile;
-      const int tile = live ? t0 + wave : 0;
-      const int R0 = lo + 32 * (tile / nt), C0 = lo + 32 * (tile % nt);
+  const int KS = wrow(t.K), lane = threadIdx.x & 63, wave = wave_id(), n = lane & 15, g = lane >> 4;
+  double *wx = sh + wave * 2 * 16 * KS, *wy = wx + 16 * KS;
+  const int lo = t.range[0], hi = t.Nt - lo - 1, side = t.Nt / 32;
+  const int slot = blockIdx.x * 4 + wave, waves = gridDim.x * 4;
+  band_weights(s, t);
+  __syncthreads();
+  const long long blocks = (long long)t.L * side * side;
+  const unsigned char* need = t.need + (long long)side * side;
+  for (long long b0 = slot; b0 < blocks; b0 += 64LL * waves) {   // 64 blocks' marks at a time
+    const long long b = b0 + (long long)lane * waves;
+    unsigned long long on = __ballot(b < blocks && (need[b < blocks ? b : 0] & kReach) != 0);
+    while (on) {
+      const int bit = __builtin_ctzll(on);
+      on &= on - 1;
+      const long long block = b0 + (long long)bit * waves;
+      const int l = (int)(block / (side * side)), at = (int)(block - (long long)l * side * side);
+      const int R0 = 32 * (at / side), C0 = 32 * (at % side);
       d4 H[2][2], gx[2][2], gy[2][2];
-      __syncthreads();   // the stencil's weights
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           H[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int row = R0 + 16 * i + 4 * r + g, col = C0 + 16 * j + n;
-            const float* e = t.E + l * t.e_by_wl;
-            const double w = (double)t.wl[l].w;
-            double dx, dy;
-            stencil(cf, t.W / 2, row, col, lo, hi, [&](int y, int x) {
-              const long long q = (long long)y * t.Nt + x;
-              return w * power(e[q], e[q + t.e_plane]);
-            }, dx, dy);
-            gx[i][j][r] = dx;
-            gy[i][j][r] = dy;
-          }
+          const float* e = t.E + l * t.e_by_wl;
+          const double w = (double)t.wl[l].w;
+          slopes16(s, t.W / 2, R0 + 16 * i, C0 + 16 * j, lo, hi, [&](int y, int x) {
+            const long long q = (long long)y * t.Nt + x;
+            return w * power(e[q], e[q + t.e_plane]);
+          }, gx[i][j], gy[i][j]);
         }
       for (int fs = f0 * t.S; fs < (f0 + nf) * t.S; ++fs) {
         if (!t.far[fs]) continue;
         int jx, jy;
-        __syncthreads();
+        star_origin(t, reduced(t, sources[fs * 3], l), jx);
+        star_origin(t, reduced(t, sources[fs * 3 + 1], l), jy);
+        const int xb0 = max(0, floor_div(C0 - t.K - jx, t.h16) + 1), xb1 = min(t.nb - 1, floor_div(C0 + 31 - jx, t.h16));
+        const int yb0 = max(0, floor_div(R0 - t.K - jy, t.h16) + 1), yb1 = min(t.nb - 1, floor_div(R0 + 31 - jy, t.h16));
+        if (xb0 > xb1 || yb0 > yb1) continue;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the previous star's weights are done with
+        __builtin_amdgcn_wave_barrier();
         far_weights(t, sources + fs * 3, l, wx, wy, jx, jy);
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         const float* G = t.G + (long long)(fs / t.S - f0) * t.ldg * t.ldg;
         d4 D[2][2];
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j) D[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-        const int xb1 = min(t.nb - 1, floor_div(C0 + 31 - jx, t.h16));
-        const int yb1 = min(t.nb - 1, floor_div(R0 + 31 - jy, t.h16));
-        const int yb0 = max(0, floor_div(R0 - t.K - jy, t.h16) + 1);
-        for (int xb = max(0, floor_div(C0 - t.K - jx, t.h16) + 1); live && xb <= xb1; ++xb) {
+        for (int xb = xb0; xb <= xb1; ++xb) {
           const int x = 16 * xb + n;
           const float* gc = G + (x < t.No ? x : t.No - 1);
           d4 V[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+          float nv[4];
+          auto fetch = [&](int yb) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) nv[k] = gc[(long long)min(16 * yb + 4 * k + g, t.No - 1) * t.ldg];
+          };
+          fetch(yb0);
           for (int yb = yb0; yb <= yb1; ++yb) {
             double v[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const int y = 16 * yb + 4 * k + g;
-              const float q = gc[(long long)(y < t.No ? y : t.No - 1) * t.ldg];
-              v[k] = x < t.No && y < t.No ? (double)q : 0.0;
-            }
+            for (int k = 0; k < 4; ++k) v[k] = x < t.No && 16 * yb + 4 * k + g < t.No ? (double)nv[k] : 0.0;
+            if (yb < yb1) fetch(yb + 1);   // one step ahead
             const int rel = R0 - (jy + t.h16 * yb);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -814,23 +908,21 @@ __global__ __launch_bounds__(256) void table_far_kernel(const TableArgs t, const
           px += __shfl_xor(px, o, 64);
           py += __shfl_xor(py, o, 64);
         }
-        if (lane < 2 && live) {   // the lanes that zeroed these partials
+        if (lane < 2) {   // the lanes that zeroed these partials
           double* o = t.pos + ((long long)fs * t.slots + slot) * 2 + lane;
           *o -= (lane ? py : px) / t.tau;
         }
       }
-      if (live) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const long long o = (long long)(R0 + 16 * i + 4 * r + g) * t.Nt + C0 + 16 * j + n;
-              float* h = t.H + (1 + l) * (long long)t.Nt * t.Nt;
-              h[o] = (float)((first ? 0.0 : (double)h[o]) + H[i][j][r]);
-            }
-      }
+          for (int r = 0; r < 4; ++r) {
+            const long long o = (long long)(R0 + 16 * i + 4 * r + g) * t.Nt + C0 + 16 * j + n;
+            float* h = t.H + (1 + l) * (long long)t.Nt * t.Nt;
+            h[o] = (float)((first ? 0.0 : (double)h[o]) + H[i][j][r]);
+          }
     }
   }
 }
@@ -839,14 +931,47 @@ __global__ __launch_bounds__(256) void table_far_kernel(const TableArgs t, const
 // wavelength's own plane
 __global__ __launch_bounds__(256) void table_seed_kernel(const TableArgs t) {
   const int lo = t.range[0], n = t.Nt - 2 * lo;
-  const long long total = (long long)n * n, plane = (long long)t.Nt * t.Nt;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
-    const long long o = (long long)(lo + i / n) * t.Nt + lo + i % n;
+  const long long plane = (long long)t.Nt * t.Nt;
+  auto sum = [&](long long o) {
     double v = 0.0;
     for (int k = 0; k < t.groups; ++k) v += t.Hpart[k * plane + o];
-    t.H[o] = (float)v;
-    if (t.range[1])
-      for (int l = 0; l < t.L; ++l) t.H[(1 + l) * plane + o] = (float)((double)t.H[(1 + l) * plane + o] + v);
+    return v;
+  };
+  if (!t.range[2]) {
+    const long long total = (long long)n * n;
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+      const long long o = (long long)(lo + i / n) * t.Nt + lo + i % n;
+      t.H[o] = (float)sum(o);
+    }
+    return;
+  }
+  // only the blocks that a star reaches, at every wavelength (a wavelength's plane starts from its own stars'
+  // weights, where it has any) or at some
+  const int side = t.Nt / 32, used = n / 32, lane = threadIdx.x & 63;
+  for (int b = blockIdx.x; b < used * used; b += gridDim.x) {
+    const int bi = lo / 32 + b / used, bj = lo / 32 + b % used;
+    const bool here = block_marked(t, bi, bj, kReach);
+    for (int l0 = 0; l0 < (t.range[1] ? t.L : 1); l0 += 64) {
+      unsigned long long own = 0, all = 1;
+      if (t.range[1]) {
+        const int l = l0 + lane;
+        const unsigned char* m = t.need + ((long long)(1 + (l < t.L ? l : 0)) * side + bi) * side + bj;
+        own = __ballot(l < t.L && (*m & kReach) != 0);
+        all = here ? __ballot(l < t.L) : own;
+      }
+      if (!here && !own) continue;
+      for (int e = threadIdx.x; e < 1024; e += 256) {
+        const long long o = (long long)(32 * bi + e / 32) * t.Nt + 32 * bj + e % 32;
+        const double v = here ? sum(o) : 0.0;
+        if (here && l0 == 0) t.H[o] = (float)v;
+        if (!t.range[1]) continue;
+        for (unsigned long long w = all; w; w &= w - 1) {
+          const int bit = __builtin_ctzll(w);
+          float* h = t.H + (1 + l0 + bit) * plane + o;
+          *h = (float)((own >> bit & 1 ? (double)*h : 0.0) + v);
+        }
+      }
+    }
   }
 }
 
@@ -992,7 +1117,7 @@ hipError_t launch_table_bin(const TableArgs& t, int Q, int Nd, int f0, int nf, c
 // far stars onto the wavelengths' planes (which leaves at once when there are none).
 hipError_t launch_table_adjoint(const TableArgs& t, const float* sources, int f0, int nf, bool first,
                                 hipStream_t st) {
-  const size_t lds = adjoint_lds(t.waves, t.h16, t.K), far_lds = 2 * 16 * wrow(t.K) * sizeof(double);
+  const size_t lds = adjoint_lds(t.waves, t.h16, t.K), far_lds = 4 * 2 * 16 * wrow(t.K) * sizeof(double);
 #define DLX_ADJOINT(WAVES)                                                                                           \
   case WAVES:                                                                                                        \
     hipLaunchKernelGGL(table_adjoint_kernel<WAVES>, dim3(t.slots / WAVES * t.groups), dim3(64 * WAVES), lds, st, t, \

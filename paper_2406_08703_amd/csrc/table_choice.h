@@ -12,7 +12,7 @@ constexpr double kTableBeta = 20.0;   // interpolation error about exp(-beta)
 // Table samples that a block of 16 focal samples may touch, K (a multiple of 8): the interpolation is compiled
 // for kTableMinK to kTableMaxK, and the adjoint stages the weights of one star for no more.
 constexpr int kTableMinK = 16, kTableMaxK = 80;
-constexpr int kTableMaxW = 72;   // taps: the derivative's band and the far stars' stencil hold half of them
+constexpr int kTableMaxW = 72;   // taps: the derivative's band holds half of them on either side
 
 // Row length of a star's weights: K, and zeros on both sides.
 constexpr int kPadL = 16;
