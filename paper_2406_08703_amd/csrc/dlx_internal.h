@@ -401,7 +401,6 @@ struct dlx_plan {
   // shared PSF table: its one-star plan (fields, adjoint, dL/dOPD), which also holds the optics of the
   // evaluation, and the table's own arrays
   dlx_plan* tab = nullptr;
-  void* tab_pool = nullptr;
   dlx::TableArgs ta = {};
   int n_reg = 0;                 // table samples per side in use when the stars lie within the detector
   const int* range = nullptr;    // a table's own plan: the outer plan's range
