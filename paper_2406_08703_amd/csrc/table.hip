@@ -422,22 +422,38 @@ __global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, 
   if (xb >= t.nb) return;
   float* o = t.planes + (long long)star * t.No * t.ldg;
   const int x = 16 * xb + n;
-  const float root_peak = (float)t.root_peak;
+  if (x < t.No) {
+#pragma unroll
+    for (int y = 0; y < NY; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int yy = 16 * (yb0 + y) + 4 * r + g;
+        if (y < ny && yy < t.No) o[(long long)yy * t.ldg + x] = (float)acc[y][r];
+      }
+  }
+  // any block dark by the largest sample of all their windows? Only then block by block, by its own
+  auto least = [&](int high) {
+    const float most = (float)__builtin_bit_cast(double, (unsigned long long)wave_max(high) << 32);
+    return (double)fmaxf(kDarkPeak * most, fminf(kDarkNull * __fsqrt_rn(most) * (float)t.root_peak, kDarkWing * most));
+  };
+  auto below = [&](int y, double bound) {
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) any |= acc[y][r] < bound && 16 * (yb0 + y) + 4 * r + g < t.No;
+    return any && x < t.No;
+  };
+  int most = top[0];
+#pragma unroll
+  for (int y = 1; y < NY; ++y) most = max(most, top[y]);
+  const double bound = least(most);
+  bool some = false;
+#pragma unroll
+  for (int y = 0; y < NY; ++y) some |= below(y, bound);
+  if (!__any(some)) return;
 #pragma unroll
   for (int y = 0; y < NY; ++y) {
-    if (y >= ny) continue;
-    const float most = (float)__builtin_bit_cast(double, (unsigned long long)wave_max(top[y]) << 32);
-    const double least = fmaxf(kDarkPeak * most, fminf(kDarkNull * __fsqrt_rn(most) * root_peak, kDarkWing * most));
-    bool dark = false;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int yy = 16 * (yb0 + y) + 4 * r + g;
-      if (x < t.No && yy < t.No) {
-        o[(long long)yy * t.ldg + x] = (float)acc[y][r];
-        dark |= acc[y][r] < least;
-      }
-    }
-    if (__any(dark)) add_dark(t, chunk, star, yb0 + y, xb);
+    const bool dark = below(y, least(top[y]));
+    if (y < ny && __any(dark)) add_dark(t, chunk, star, yb0 + y, xb);
   }
 }
 
