@@ -47,12 +47,13 @@ def measured_traffic(config, precision, stage, tile, fold=True, table=0):
     """HBM bytes per launch of `stage`'s kernel at `tile` (WM, WN) from the committed rocprofv3 summary.
 
     FETCH_SIZE and WRITE_SIZE (KiB per dispatch) are scaled by what the same
-    counters read for a plain copy kernel of known size. Returns None when no
-    summary exists, when it lacks this kernel, or when the GEMM source
+    counters read for a plain copy kernel of known size. The products on a shared
+    PSF table have a summary of their own (FP32 in both arithmetics). Returns None
+    when no summary exists, when it lacks this kernel, or when the GEMM source
     changed since it was taken.
     """
     import hashlib
-    path = os.path.join(ROOT, "profiles", f"traffic_{config}_{precision}.txt")
+    path = os.path.join(ROOT, "profiles", f"traffic_table_{config}.txt" if table else f"traffic_{config}_{precision}.txt")
     src = os.path.join(ROOT, "paper_2406_08703_amd", "csrc", "mft_gemm.hip")
     if not os.path.exists(path):
         return None
@@ -359,8 +360,8 @@ def main():
     F_mft = P.mft_flops()
     # algorithmic: the dense two-sided MFT count, forward + adjoint; executed: what the products run
     # (the fused evaluation reuses E, so forward + adjoint only; the fold executes a quarter;
-    tf_alg = 2 * F_mft * n_psf / (ms_step * 1e-3) / 1e12
     # with a shared PSF table the transforms run once per wavelength)
+    tf_alg = 2 * F_mft * n_psf / (ms_step * 1e-3) / 1e12
     from paper_2406_08703_amd import dlx as C
     samples = C.dlx_plan_table_samples(plan.plan)
     tf_exec = mft_executed_flops(P, fold, samples) * mft_runs(P, samples) / (ms_step * 1e-3) / 1e12
@@ -376,14 +377,15 @@ def main():
         inputs_b["d"][f0] = d_f0
         bf = run_form(args, w, geom, "bf16x3", fold, inputs_b, log)
         ms_b = bf["t_graph"] * 1e3 / args.steps
+        samples_b = C.dlx_plan_table_samples(bf["plan"].plan)
         gemm_b = {k: v for k, v in bf["table"].items() if stage_flops(P, k)}
         split = {"ms_per_step": round(ms_b, 4), "value": round(n_psf * args.steps / bf["t_graph"], 3),
                  "unit": "PSF evals/s", "step_ms": step_stats(bf["per_step"]),
                  "speedup_vs_fp32": round(ms_step / ms_b, 3),
                  "stage_ms_per_step": {k: round(v["ms_per_step"], 5) for k, v in bf["table"].items()},
                  "tiles": {k: f"{v[0]}x{v[1]}" for k, v in bf["plan"].tiles.items()},
-                 "roofline": gemm_roofline(P, gemm_b, bf["plan"].tiles, "bf16x3", args.config, fold,
-                                           C.dlx_plan_table_samples(bf["plan"].plan)),
+                 "products": "fp32 (on a shared PSF table)" if samples_b else "bf16x3",
+                 "roofline": gemm_roofline(P, gemm_b, bf["plan"].tiles, "bf16x3", args.config, fold, samples_b),
                  "rel_err_vs_fp64": None}
 
     cpu, parity = None, None

@@ -63,3 +63,19 @@ def test_traffic_lookup_matches_the_summary_and_guards_the_source(tmp_path, monk
     (root / "profiles" / "traffic_c3_fp32.txt").write_text("\n".join(lines) + "\n")
     monkeypatch.setattr(bench, "ROOT", str(root))
     assert bench.measured_traffic("c3", "fp32", "B3", (wm, wn)) is None
+
+
+def test_traffic_of_a_table_plans_products_has_its_own_summary():
+    path = os.path.join(bench.ROOT, "profiles", "traffic_table_c3.txt")
+    lines = open(path).read().splitlines()
+    fields = dict(l.split() for l in lines if l.split()[:1] and l.split()[0] in ("fetch_scale", "write_scale",
+                                                                                 "kernel_source_sha256"))
+    src = os.path.join(bench.ROOT, "paper_2406_08703_amd", "csrc", "mft_gemm.hip")
+    current = hashlib.sha256(open(src, "rb").read()).hexdigest() == fields["kernel_source_sha256"]
+    for stage in ("F1", "F2", "B3", "B4"):
+        row = [l.split() for l in lines if l.startswith(f"stage {stage} ")][0]
+        assert row[2].startswith("fgemm_table_kernel<")
+        wm, wn = (int(x) for x in row[2].split("<")[1].rstrip(">").split(",")[1:3])
+        want = round(1024 * (float(row[4]) * float(fields["fetch_scale"]) + float(row[5]) * float(fields["write_scale"])))
+        for precision in ("fp32", "bf16x3"):   # a table's products are FP32 in both
+            assert bench.measured_traffic("c3", precision, stage, (wm, wn), table=704) == (want if current else None)
