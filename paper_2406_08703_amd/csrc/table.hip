@@ -348,9 +348,10 @@ __device__ __forceinline__ void far_weights(const TableArgs& t, const float* src
 // weights of the NY blocks below each other. Bound by the FP64 matrix rate; the next rows' samples are
 // loaded while the current ones' products run, and the workgroups of one part of the focal grid, whatever
 // their star, follow each other on one XCD, whose L2 then holds that part of the table. The weights of a
-// product with four row groups are read together, and the path of far stars is kept small enough that three
-// waves fit a SIMD. 128 stars of 768^2 samples, 28 taps: 260 us (373 us with a read and a wait before each
-// product and two waves, 150 us of matrix instructions). KP = K / 8.
+// product with four row groups are read together, and far stars are left to another kernel, so that three
+// waves fit a SIMD. 128 stars of 768^2 samples, 28 taps: 270 us, of which the search for dark samples takes 20
+// (373 us without it, but with a read and a wait before each product and two waves; 150 us of matrix instructions).
+// KP = K / 8.
 template <int KP, int NY>
 __global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, int fs0, int nstar, int nbx, int chunk) {
   constexpr int K = 8 * KP, KS = wrow(K);
@@ -460,7 +461,8 @@ __global__ __launch_bounds__(256, 2) void table_shift_kernel(const TableArgs t, 
 // The dark blocks' samples, and all of far stars: sum_l w_l |sum_j phi_j E_l[j]|^2, the fields interpolated with
 // the same weights (they have half the image's bandwidth), a far star's with those of its tilt at each wavelength.
 // A workgroup per block, its waves share out the wavelengths. Two chains of products per wavelength where
-// the image has one for all: bound by the latency of the loads for a few blocks, by the FP64 matrix rate for many.
+// the image has one for all: bound by the latency of the loads for a few blocks, by the FP64 matrix rate for many
+// (80 stars of 256^2 samples, 32 wavelengths, a Gaussian pupil: 3.1 ms; 4.5 us where no block is dark).
 template <int KP>
 __global__ __launch_bounds__(256, 2) void table_field_kernel(const TableArgs t, const float* sources, int fs0, int chunk) {
   constexpr int K = 8 * KP, KS = wrow(K);

@@ -2,7 +2,7 @@
 
 The choice is plain C++ (csrc/table_choice.cpp), built here with g++. The limits below are those of the
 kernels in csrc/table.hip: windows of K = 16, 24 ... 80 samples, 2048 staged weight pairs, half of at most 72
-taps in a stencil, adjoint workgroups of 4 or 8 waves in 150 KiB of LDS.
+taps on either side of a derivative's band, adjoint workgroups of 4 or 8 waves in 150 KiB of LDS.
 """
 import itertools
 import os
