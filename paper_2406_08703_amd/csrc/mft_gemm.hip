@@ -588,11 +588,13 @@ struct TileRange {
 // fields serve every star and frame, so their rounding errors do not average over frames as those of one
 // transform per frame do, and are kept smaller instead: F1's pupil field arrives as the pair sums and
 // differences, rounded once (pupil_body), and F1 contracts from the centre of the pupil outwards, where the
-// partial sums of the wings' oscillating terms stay smaller; F2, which sets the core's error, adds up
-// partial sums of 64 terms. (Image error in the core, 4 frames of 2048^2 samples, 16 wavelengths: 3.8e-8, and
-// 3.7e-7 of the flat-field gradient's norm; 9e-8 and 9e-7 in one running sum, 6.6e-8 and 6.7e-7 with one
-// transform per frame. F2 takes 939 us with the partial sums, whose registers leave two workgroups per CU,
-// 865 us without.)
+// partial sums of the wings' oscillating terms stay smaller; F1 and F2 add up partial sums of 64 terms, as an
+// unaberrated pupil's core, whose terms all have one sign, gathers a running sum's rounding errors. (Image
+// error, 4 frames of 2048^2 samples, 16 wavelengths: 9e-8 in one running sum, 3.8e-8 with partial sums in F2,
+// 6.6e-8 with one transform per frame; 9e-7, 3.7e-7 and 6.7e-7 of the flat-field gradient's norm. Unaberrated
+// round pupil of 512^2, 3 wavelengths: 4.9e-7 with partial sums in F2 alone, 1.4e-7 in both, 2.5e-7 with one
+// transform per frame. Their registers leave two workgroups per CU: F2 takes 939 us with them and 865 without
+// at 4 frames of 2048^2; F1 takes 527 us on its 64 x 64 tile, 547 on 32 x 64 without, and 130 and 128 at c3.)
 // LIST (B3 of a table whose blocks are used sparsely): the k-stages start at klist[0 .. n_list), all whole.
 // The two forms of that stage share the kernel's LDS buffers, `lds`.
 template <int KIND, int WM, int WN, int PREC>
@@ -650,7 +652,7 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
   const bool conj_d = DA ? a.conj_a : a.conj_b;
   constexpr bool PAIRS = TAB && KIND == KIND_F1;   // the data operand holds sums and differences
   constexpr bool REV = TAB && KIND == KIND_F1;     // k from the middle outwards
-  constexpr bool PARTS = TAB && KIND == KIND_F2;   // a sum of partial sums over kPartStages k-stages
+  constexpr bool PARTS = TAB && (KIND == KIND_F1 || KIND == KIND_F2);   // a sum of partial sums over kPartStages stages
   constexpr int kPartStages = 4;
   const int kmid = a.kodd ? K - 1 : -1;   // the unpaired middle term of an odd contracted length
 
@@ -1185,6 +1187,30 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
       // is told to spread it, and the loads, between the MFMAs, so the pair sums and the LDS and
       // global traffic issue while the matrix pipe is busy. (One workgroup runs one PSF here.)
       set_loader(it);
+      f4 tot[PARTS ? WM : 1][PARTS ? WN : 1][4];
+      if constexpr (PARTS) {
+#pragma unroll
+        for (int bm = 0; bm < WM; ++bm)
+#pragma unroll
+          for (int bn = 0; bn < WN; ++bn)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) tot[bm][bn][c] = f4{0.f, 0.f, 0.f, 0.f};
+      }
+      auto move = [&](f4& from, f4& to) {
+        to += from;
+        from = f4{0.f, 0.f, 0.f, 0.f};
+      };
+      auto flush = [&]() {
+#pragma unroll
+        for (int bm = 0; bm < WM; ++bm)
+#pragma unroll
+          for (int bn = 0; bn < WN; ++bn) {
+            move(pr_[bm][bn], tot[bm][bn][0]);
+            move(pi_[bm][bn], tot[bm][bn][1]);
+            move(rr_[bm][bn], tot[bm][bn][2]);
+            move(ri_[bm][bn], tot[bm][bn][3]);
+          }
+      };
       if constexpr (REV) {   // the same pipeline from the last tile to the first: the partial ones come first
         auto at = [&](int t) { return k_lo + max(nk - 1 - t, 0) * BK; };
         load_tile_c(at(0));
@@ -1204,6 +1230,8 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
           load_tile_c(at(kt + 2));
           pipe_schedule();
           __syncthreads();
+          if constexpr (PARTS)
+            if (kt % kPartStages == kPartStages - 1) flush();
         }
         mma(smem + (kt & 1) * BUF_EL);
       } else {
@@ -1215,30 +1243,6 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
           store_tile(smem, std::true_type{});
         load_tile_c(at(1));
         __syncthreads();
-        f4 tot[PARTS ? WM : 1][PARTS ? WN : 1][4];
-        if constexpr (PARTS) {
-#pragma unroll
-          for (int bm = 0; bm < WM; ++bm)
-#pragma unroll
-            for (int bn = 0; bn < WN; ++bn)
-#pragma unroll
-              for (int c = 0; c < 4; ++c) tot[bm][bn][c] = f4{0.f, 0.f, 0.f, 0.f};
-        }
-        auto move = [&](f4& from, f4& to) {
-          to += from;
-          from = f4{0.f, 0.f, 0.f, 0.f};
-        };
-        auto flush = [&]() {
-#pragma unroll
-          for (int bm = 0; bm < WM; ++bm)
-#pragma unroll
-            for (int bn = 0; bn < WN; ++bn) {
-              move(pr_[bm][bn], tot[bm][bn][0]);
-              move(pi_[bm][bn], tot[bm][bn][1]);
-              move(rr_[bm][bn], tot[bm][bn][2]);
-              move(ri_[bm][bn], tot[bm][bn][3]);
-            }
-        };
         int kt = 0;
         for (; kt + 1 < nfull; ++kt) {   // the next tile is full: one basic block per stage
           mma(smem + (kt & 1) * BUF_EL);
@@ -1257,18 +1261,18 @@ __device__ __forceinline__ void fgemm_body(const GemmArgs& a, int lin, const flo
           }
           __syncthreads();
         }
-        if constexpr (PARTS) {
-          flush();
+      }
+      if constexpr (PARTS) {
+        flush();
 #pragma unroll
-          for (int bm = 0; bm < WM; ++bm)
+        for (int bm = 0; bm < WM; ++bm)
 #pragma unroll
-            for (int bn = 0; bn < WN; ++bn) {
-              pr_[bm][bn] = tot[bm][bn][0];
-              pi_[bm][bn] = tot[bm][bn][1];
-              rr_[bm][bn] = tot[bm][bn][2];
-              ri_[bm][bn] = tot[bm][bn][3];
-            }
-        }
+          for (int bn = 0; bn < WN; ++bn) {
+            pr_[bm][bn] = tot[bm][bn][0];
+            pi_[bm][bn] = tot[bm][bn][1];
+            rr_[bm][bn] = tot[bm][bn][2];
+            ri_[bm][bn] = tot[bm][bn][3];
+          }
       }
     } else if (nk > 0) {
       // B4: the same pipeline over a stream of tiles that runs through the workgroup's PSFs and
